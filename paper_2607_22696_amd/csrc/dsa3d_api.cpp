@@ -53,6 +53,9 @@ dsa3d_status check_desc(const dsa3d_desc* d, dsa3d::Geometry* g, uint64_t* rows,
   g->N = (int)N;
   g->scale = d->scale != 0.0f ? d->scale : 1.0f / std::sqrt((float)d->head_dim);
   g->scale_log2 = g->scale * 1.4426950408889634f;
+  g->by_heads = dsa3d::fast_div(g->heads);
+  g->by_khw = dsa3d::fast_div(g->kh * g->kw);
+  g->by_kw = dsa3d::fast_div(g->kw);
   g->win_frames = dsa3d::window_frames(*g, (int)(d->head_dim * esz));
   *rows = R;
   *io_bytes = R * d->head_dim * esz;

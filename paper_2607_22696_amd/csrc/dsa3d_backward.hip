@@ -31,7 +31,7 @@
 // The predicted-weights variant reads no K: one sweep (phase 1 with the given logits, the
 // bin counts' ranks not kept) and a finalize of one thread per point that claims its slot
 // from a fill cursor take phases 1 and 3.
-#include "dsa3d_device.h"
+#include "dsa3d_slots.h"
 
 namespace dsa3d {
 namespace {
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_sweep_k
     int i, j;
     // All lanes of a group share the token: a whole group is idle or active, so neither the
     // group reductions nor the point sharing ever mix an idle group into an active one.
-    if (!pencil_cell(po, tl, wave * LY::kGroups + grp, i, j)) continue;
+    if (!query_token<D, BF16>(po, g, tl, wave * LY::kGroups + grp, i, j)) continue;
     const int n = t * HW + i * g.W + j;
     const int64_t row = ((int64_t)b * g.N + n) * g.heads + m;
 
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_vpass_k
     const int t = tl.frame;
     const RowWindow win = make_window<LY::kRowBytes>(g, v, v, b, m, t);  // V rows only
     int i, j;
-    if (!pencil_cell(po, tl, wave * LY::kGroups + grp, i, j)) continue;  // a whole group idles
+    if (!query_token<D, BF16>(po, g, tl, wave * LY::kGroups + grp, i, j)) continue;  // a whole group idles
     const int n = t * HW + i * g.W + j;
     const int64_t row = ((int64_t)b * g.N + n) * g.heads + m;
     const uint4 gr = load16(gb, row * LY::kRowBytes + lane_off);
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((
     const int t = tl.frame;
     const RowWindow win = make_window<LY::kRowBytes>(g, k, k, b, m, t);  // K rows only
     int i, j;
-    if (!pencil_cell(po, tl, wave * LY::kGroups + grp, i, j)) continue;  // a whole group idles
+    if (!query_token<D, BF16>(po, g, tl, wave * LY::kGroups + grp, i, j)) continue;  // a whole group idles
     const int n = t * HW + i * g.W + j;
     const int64_t row = ((int64_t)b * g.N + n) * g.heads + m;
     const uint4 qr = load16(qb, row * LY::kRowBytes + lane_off);

@@ -11,9 +11,6 @@
 
 #include "dsa3d_internal.h"
 
-#define DSA3D_TILE_FN __host__ __device__ inline __attribute__((always_inline))
-#include "tile_order.h"
-
 namespace dsa3d {
 namespace dev {
 
@@ -336,15 +333,6 @@ constexpr int slot_words() {
 // ---------------------------------------------------------------------------- launch shape
 
 constexpr int kMaxBlocks = 1 << 22;  // grid cap; larger problems loop over tiles
-
-// Pencil order of the query-owned kernels: tiles of kRowsPerBlock tokens inside pencils of
-// about 12 x 12 tokens of a frame.  Measured on one MI355X at 64x68x120, 24 heads x 128,
-// 3x5x5, offsets U[-8,8]: forward 159 / 162 / 197 ms and sweep 199 / 201 / 220 ms with
-// pencils of about 12 x 12 / 16 x 16 / 24 x 24 tokens.
-template <int D, bool BF16>
-inline PencilOrder query_order(const Geometry& g) {
-  return plan_pencils(g.B * g.heads, g.T, g.H, g.W, Layout<D, BF16>::kRowsPerBlock, 12, 12);
-}
 
 // Workgroups for `vtiles` virtual tiles: at most kMaxBlocks, a multiple of 8 when capped so
 // that a workgroup's later tiles (v += gridDim.x) stay on its XCD.

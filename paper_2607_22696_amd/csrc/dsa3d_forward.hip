@@ -1,19 +1,22 @@
 // Forward kernel of 3D Deformable Slide Attention (MegaSlide-DiT, Section 5.2, Eq. (1)).
 //
-// Each L-lane group owns one query row.  For every point it forms the sampling position,
-// the 8 trilinear corners and their weights (computed once per row by one lane and shared
-// with ds_bpermute), loads the 8 K corner rows and
-// the 8 V corner rows (one 16-byte buffer load per lane per row; corners outside the grid
-// come back as zeros from the buffer unit), reduces the interpolated logit
-// over the group with DPP butterflies (q.K by v_dot2_f32_bf16 on bf16 data, fp32
-// accumulation) and folds the point into an online (running-max, base-2) softmax, so each
-// corner row is read once.  Nothing per point is written to memory; the output row and
-// its LSE are stored once.
+// A query's P points have 8 P corner rows of K and of V, and the rate at which a compute unit takes
+// row requests bounds a kernel that loads them all.  A tile goes one of two ways, by the spread
+// of its points (compact_tile):
+//  * slots_tile: four neighbouring queries of a wave read each distinct voxel of their points
+//    once (dsa3d_slots.h), logits first, then one softmax, then the weighted sum of V;
+//  * gather_tile: an L-lane group owns one query row, loads the 8 K and 8 V rows of each point
+//    (16-byte buffer loads, zeros outside the grid) and folds the point into an online softmax.
+// Measured, gather against slots where the points are compact (U[-8, 8] offsets always gather):
+// 64x68x120, 24 heads x 128, 3x3x3, offsets N(0, 1): 48.2 -> 25.6 ms; 16x34x60, 24 x 128, 3x7x7:
+// 14.5 -> 6.6 ms; 64x34x60, 16 x 64, 3x3x3, U[-2, 2]: 4.27 -> 3.9 ms; 2 x 9x33x47, 6 x 64 fp32:
+// 0.67 -> 0.46 ms.  Nothing per point is written to memory; the output row and its LSE are stored
+// once.
 //
 // Memory order: tiles are handed out in pencils (tile_order.h): each XCD walks one pencil of
-// about 16 x 16 tokens of a (batch, head) frame by frame, so the K/V rows its in-flight
+// about 12 x 12 tokens of a (batch, head) frame by frame, so the K/V rows its in-flight
 // queries reach stay in its L2.
-#include "dsa3d_device.h"
+#include "dsa3d_slots.h"
 
 namespace dsa3d {
 namespace {
@@ -31,10 +34,10 @@ using namespace dev;
 // PW (the predicted-weights variant): the logit of a point is given (`logits`, one fp32 per
 // (row, point)) instead of scale <q, k_p>, so neither q nor the K corners are read.
 template <int D, bool BF16, bool PW>
-__global__ __launch_bounds__(kBlockThreads) void fwd_kernel(
-    Geometry g, const void* __restrict__ q, const void* __restrict__ k, const void* __restrict__ v,
-    const float* __restrict__ logits, const float* __restrict__ offsets, void* __restrict__ out,
-    float* __restrict__ lse, PencilOrder po) {
+__device__ inline __attribute__((always_inline)) void gather_tile(
+    const Geometry& g, const PencilOrder& po, const PencilTile& tl, const void* __restrict__ q,
+    const void* __restrict__ k, const void* __restrict__ v, const float* __restrict__ logits,
+    const float* __restrict__ offsets, void* __restrict__ out, float* __restrict__ lse, int4* pts) {
   using LY = Layout<D, BF16>;
   constexpr int L = LY::kLanes;
   constexpr int VEC = LY::kVec;
@@ -50,98 +53,219 @@ __global__ __launch_bounds__(kBlockThreads) void fwd_kernel(
   // The point each lane formed for the current chunk, read back by its row's lanes: corner
   // indices, weights, and for the global-load path its window flag and cell.  A row's lanes
   // are in one wave, whose LDS accesses complete in order: no barrier.
-  __shared__ int4 pts[slot_words<L, 5>()];
   int4* const mine_at = pts + slot_of<L, 5>(threadIdx.x);
 
-  for (int64_t vt = blockIdx.x; vt < po.vtiles; vt += gridDim.x) {
-    PencilTile tl;
-    if (!pencil_tile(po, vt, tl)) continue;  // the whole block: no pencil left on this XCD
-    const int b = tl.group / g.heads, m = tl.group % g.heads;
-    const int t = tl.frame;
-    const RowWindow win = make_window<LY::kRowBytes>(g, k, v, b, m, t);
+  const int b = tl.group / g.by_heads, m = tl.group - b * g.heads;
+  const int t = tl.frame;
+  const RowWindow win = make_window<LY::kRowBytes>(g, k, v, b, m, t);
+  int i, j;
+  const bool active = query_token<D, BF16>(po, g, tl, wave * LY::kGroups + grp, i, j);
+  if (!active) {  // an idle row computes on a valid token and stores nothing
+    i = min(i, g.H - 1);
+    j = min(j, g.W - 1);
+  }
+  const int n = t * HW + i * g.W + j;
+  const int64_t row = ((int64_t)b * g.N + n) * g.heads + m;
+
+  uint4 qr = make_uint4(0u, 0u, 0u, 0u);
+  if constexpr (!PW) qr = load16(qb, row * LY::kRowBytes + lane_off);
+  const float* off = offsets + row * g.P * 3;
+  float o[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) o[e] = 0.0f;
+  float mx = -INFINITY, l = 0.0f;
+
+  for (int p0 = 0; p0 < g.P; p0 += L) {
+    // this lane's point of the chunk
+    const int pm = min(p0 + sub, g.P - 1);
+    const int it = pm / g.by_khw, rp = pm - it * khw, ih = rp / g.by_kw, iw = rp - ih * g.kw;
+    {
+      Point mine;
+      make_point(g, win, t, i, j, it - rt, ih - rh, iw - rw, off[3 * pm], off[3 * pm + 1],
+                 off[3 * pm + 2], mine);
+      mine_at[0] = make_int4(mine.vidx[0], mine.vidx[1], mine.vidx[2], mine.vidx[3]);
+      mine_at[1] = make_int4(mine.vidx[4], mine.vidx[5], mine.vidx[6], mine.vidx[7]);
+      mine_at[2] = make_int4(__float_as_int(mine.w[0]), __float_as_int(mine.w[1]),
+                             __float_as_int(mine.w[2]), __float_as_int(mine.w[3]));
+      mine_at[3] = make_int4(__float_as_int(mine.w[4]), __float_as_int(mine.w[5]),
+                             __float_as_int(mine.w[6]), __float_as_int(mine.w[7]));
+      mine_at[4] = make_int4((int)mine.slow, mine.cx, mine.cy, mine.cz);
+    }
+    float mylog2 = 0.0f;  // PW: this lane's point's logit, base 2
+    if constexpr (PW) mylog2 = logits[row * g.P + pm] * kLog2e;
+    const int nk = min(L, g.P - p0);
+    for (int kk = 0; kk < nk; ++kk) {
+      const int src = (grp * L + kk) << 2;
+      const int4* at = pts + slot_of<L, 5>(wave * 64 + grp * L) + kk * 5;
+      const int4 i0 = at[0], i1 = at[1], w0 = at[2], w1 = at[3];
+      Point pt;
+      pt.vidx[0] = i0.x; pt.vidx[1] = i0.y; pt.vidx[2] = i0.z; pt.vidx[3] = i0.w;
+      pt.vidx[4] = i1.x; pt.vidx[5] = i1.y; pt.vidx[6] = i1.z; pt.vidx[7] = i1.w;
+      pt.w[0] = __int_as_float(w0.x); pt.w[1] = __int_as_float(w0.y);
+      pt.w[2] = __int_as_float(w0.z); pt.w[3] = __int_as_float(w0.w);
+      pt.w[4] = __int_as_float(w1.x); pt.w[5] = __int_as_float(w1.y);
+      pt.w[6] = __int_as_float(w1.z); pt.w[7] = __int_as_float(w1.w);
+      uint4 vr[8];
+      float s2;
+      if constexpr (PW) {
+        load_stashed_corners<LY::kRowBytes, false>(g, win, kb, vb, b, m, lane_off, at + 4,
+                                                   pt.vidx, nullptr, vr);
+        s2 = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(mylog2)));
+      } else {
+        uint4 kr[8];
+        load_stashed_corners<LY::kRowBytes, true>(g, win, kb, vb, b, m, lane_off, at + 4,
+                                                  pt.vidx, kr, vr);
+        float sp = 0.0f;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) sp = fmaf(pt.w[c], chunk_dot<BF16>(qr, kr[c]), sp);
+        s2 = group_sum<L>(sp) * g.scale_log2;
+      }
+      // One exponential per point: a new maximum rescales the running sums by
+      // 2^(old max - new max) and enters with weight exactly 1; otherwise the point enters
+      // with 2^(s - max).  (A first finite logit takes the first branch: 2^-inf = 0.)  A
+      // given logit of -inf enters with weight 0 even while the maximum is still -inf,
+      // where s - max would be NaN.
+      const bool up = s2 > mx;
+      float ex = exp2f(up ? mx - s2 : s2 - mx);
+      if constexpr (PW) ex = s2 == -INFINITY ? 0.0f : ex;
+      const float corr = up ? ex : 1.0f;
+      const float e = up ? 1.0f : ex;
+      l = fmaf(l, corr, e);
+      mx = up ? s2 : mx;
+#pragma unroll
+      for (int x = 0; x < VEC; ++x) o[x] *= corr;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) chunk_axpy<BF16>(o, e * pt.w[c], vr[c]);
+    }
+  }
+  if (active) {
+    const float inv = 1.0f / l;
+    char* ob = static_cast<char*>(out) + row * LY::kRowBytes + lane_off;
+    if constexpr (BF16) {
+      uint4 wv;
+      wv.x = bf16_bits(o[0] * inv) | (bf16_bits(o[1] * inv) << 16);
+      wv.y = bf16_bits(o[2] * inv) | (bf16_bits(o[3] * inv) << 16);
+      wv.z = bf16_bits(o[4] * inv) | (bf16_bits(o[5] * inv) << 16);
+      wv.w = bf16_bits(o[6] * inv) | (bf16_bits(o[7] * inv) << 16);
+      *reinterpret_cast<uint4*>(ob) = wv;
+    } else {
+      *reinterpret_cast<float4*>(ob) = make_float4(o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
+    }
+    if (lse != nullptr && sub == 0) lse[row] = (mx + log2f(l)) * kLn2;
+  }
+}
+
+// The same for tiles whose points lie close together, reading each voxel of four neighbouring
+// queries once (dsa3d_slots.h).  A chunk of points (all of them up to 32, or 80) has its logits
+// complete before its softmax, so one maximum is taken per chunk and only rows of several chunks
+// rescale.
+template <int D, bool BF16, bool PW, int R, bool WHOLE>
+__device__ inline __attribute__((always_inline)) void slots_tile(
+    const Geometry& g, const PencilOrder& po, const PencilTile& tl, const void* __restrict__ q,
+    const void* __restrict__ k, const void* __restrict__ v, const float* __restrict__ logits,
+    const float* __restrict__ offsets, void* __restrict__ out, float* __restrict__ lse,
+    SlotLds<R>& lds) {
+  using LY = Layout<D, BF16>;
+  using U = SlotSum<D, BF16>;
+  constexpr int L = kSlotLanes;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int qi = lane / L, lp = lane % L;
+  float* const val = lds.val[qi];
+  const int HW = g.H * g.W;
+
+  for (int e0 = kSlotQueries * wave; e0 < po.run * kSlotQueries;
+       e0 += kWavesPerBlock * kSlotQueries) {
     int i, j;
-    const bool active = pencil_cell(po, tl, wave * LY::kGroups + grp, i, j);
-    if (!active) {  // an idle row computes on a valid token and stores nothing
-      i = tl.pr * po.ph;
-      j = tl.pc * po.pw;
-    }
-    const int n = t * HW + i * g.W + j;
-    const int64_t row = ((int64_t)b * g.N + n) * g.heads + m;
-
-    uint4 qr = make_uint4(0u, 0u, 0u, 0u);
-    if constexpr (!PW) qr = load16(qb, row * LY::kRowBytes + lane_off);
+    const bool active = slot_token(po, g, tl, e0 + qi, i, j);
+    if (__builtin_amdgcn_ballot_w64(active) == 0) continue;
+    j = min(j, g.W - 1);  // an idle query computes on a valid token and stores nothing
+    const int b = tl.group / g.by_heads, m = tl.group - b * g.heads;
+    const int t = tl.frame;
+    const SlotWindow win = slot_window<LY::kRowBytes>(g, b, m, t);
+    const int64_t row = ((int64_t)b * g.N + (t * HW + i * g.W + j)) * g.heads + m;
     const float* off = offsets + row * g.P * 3;
-    float o[VEC];
+    int64_t qrow[kSlotQueries];
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) o[e] = 0.0f;
-    float mx = -INFINITY, l = 0.0f;
+    for (int w = 0; w < kSlotQueries; ++w)
+      qrow[w] = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(row >> 32), w * L)
+                           << 32) |
+                          (uint32_t)__builtin_amdgcn_readlane((int)row, w * L));
+    float mx = -INFINITY, l = 0.0f;  // of this lane's query
+    float o[U::kVec];                // of this lane's query, channels kVec (lane % kLanes) ..
+#pragma unroll
+    for (int x = 0; x < U::kVec; ++x) o[x] = 0.0f;
 
-    for (int p0 = 0; p0 < g.P; p0 += L) {
-      // this lane's point of the chunk
-      const int pm = min(p0 + sub, g.P - 1);
-      const int it = pm / khw, ih = (pm - it * khw) / g.kw, iw = pm - it * khw - ih * g.kw;
-      {
-        Point mine;
-        make_point(g, win, t, i, j, it - rt, ih - rh, iw - rw, off[3 * pm], off[3 * pm + 1],
-                   off[3 * pm + 2], mine);
-        mine_at[0] = make_int4(mine.vidx[0], mine.vidx[1], mine.vidx[2], mine.vidx[3]);
-        mine_at[1] = make_int4(mine.vidx[4], mine.vidx[5], mine.vidx[6], mine.vidx[7]);
-        mine_at[2] = make_int4(__float_as_int(mine.w[0]), __float_as_int(mine.w[1]),
-                               __float_as_int(mine.w[2]), __float_as_int(mine.w[3]));
-        mine_at[3] = make_int4(__float_as_int(mine.w[4]), __float_as_int(mine.w[5]),
-                               __float_as_int(mine.w[6]), __float_as_int(mine.w[7]));
-        mine_at[4] = make_int4((int)mine.slow, mine.cx, mine.cy, mine.cz);
-      }
-      float mylog2 = 0.0f;  // PW: this lane's point's logit, base 2
-      if constexpr (PW) mylog2 = logits[row * g.P + pm] * kLog2e;
-      const int nk = min(L, g.P - p0);
-      for (int kk = 0; kk < nk; ++kk) {
-        const int src = (grp * L + kk) << 2;
-        const int4* at = pts + slot_of<L, 5>(wave * 64 + grp * L) + kk * 5;
-        const int4 i0 = at[0], i1 = at[1], w0 = at[2], w1 = at[3];
-        Point pt;
-        pt.vidx[0] = i0.x; pt.vidx[1] = i0.y; pt.vidx[2] = i0.z; pt.vidx[3] = i0.w;
-        pt.vidx[4] = i1.x; pt.vidx[5] = i1.y; pt.vidx[6] = i1.z; pt.vidx[7] = i1.w;
-        pt.w[0] = __int_as_float(w0.x); pt.w[1] = __int_as_float(w0.y);
-        pt.w[2] = __int_as_float(w0.z); pt.w[3] = __int_as_float(w0.w);
-        pt.w[4] = __int_as_float(w1.x); pt.w[5] = __int_as_float(w1.y);
-        pt.w[6] = __int_as_float(w1.z); pt.w[7] = __int_as_float(w1.w);
-        uint4 vr[8];
-        float s2;
-        if constexpr (PW) {
-          load_stashed_corners<LY::kRowBytes, false>(g, win, kb, vb, b, m, lane_off, at + 4,
-                                                     pt.vidx, nullptr, vr);
-          s2 = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(mylog2)));
-        } else {
-          uint4 kr[8];
-          load_stashed_corners<LY::kRowBytes, true>(g, win, kb, vb, b, m, lane_off, at + 4,
-                                                    pt.vidx, kr, vr);
-          float sp = 0.0f;
+    for (int c0 = 0; c0 < g.P;) {
+      // equal chunks, as few as the rounds allow
+      const int left = g.P - c0, chunks = (left + R * L - 1) / (R * L);
+      int npts = (left + chunks - 1) / chunks;
+      SlotPoint pt[R];
+      float s[R];
 #pragma unroll
-          for (int c = 0; c < 8; ++c) sp = fmaf(pt.w[c], chunk_dot<BF16>(qr, kr[c]), sp);
-          s2 = group_sum<L>(sp) * g.scale_log2;
+      for (int r = 0; r < R; ++r) {
+        s[r] = -INFINITY;
+        if (r * L >= npts) break;
+        const int p = c0 + min(r * L + lp, npts - 1);
+        pt[r].set(g, t, i, j, p, off + 3 * p);
+        if constexpr (PW) s[r] = logits[row * g.P + p] * kLog2e;
+      }
+      bool global;
+      int n;
+      npts = number_slots<R, WHOLE>(g, win, (uint32_t)g.heads * LY::kRowBytes, lds, pt, npts, n, global);
+      if constexpr (!PW) {
+        SlotVecs<D, BF16> vec;
+        vec.load(static_cast<const char*>(q), qrow);
+        row_dots<D, BF16, R>(slot_rows<LY::kRowBytes>(g, k, win, b, m, global), lds, vec, n);
+      }
+      float mc = mx;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (r * L >= npts) break;
+        if constexpr (!PW) {
+          float w[8], d[8];
+          pt[r].weights(w);
+          pt[r].read(val, d);
+          s[r] = 0.0f;
+#pragma unroll
+          for (int c = 0; c < 8; ++c) s[r] = fmaf(w[c], d[c], s[r]);
+          s[r] *= g.scale_log2;
         }
-        // One exponential per point: a new maximum rescales the running sums by
-        // 2^(old max - new max) and enters with weight exactly 1; otherwise the point enters
-        // with 2^(s - max).  (A first finite logit takes the first branch: 2^-inf = 0.)  A
-        // given logit of -inf enters with weight 0 even while the maximum is still -inf,
-        // where s - max would be NaN.
-        const bool up = s2 > mx;
-        float ex = exp2f(up ? mx - s2 : s2 - mx);
-        if constexpr (PW) ex = s2 == -INFINITY ? 0.0f : ex;
-        const float corr = up ? ex : 1.0f;
-        const float e = up ? 1.0f : ex;
-        l = fmaf(l, corr, e);
-        mx = up ? s2 : mx;
-#pragma unroll
-        for (int x = 0; x < VEC; ++x) o[x] *= corr;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) chunk_axpy<BF16>(o, e * pt.w[c], vr[c]);
+        if (r * L + lp >= npts) s[r] = -INFINITY;
+        mc = fmaxf(mc, s[r]);
       }
+      mc = lane_maxf<L>(mc);
+      const float corr = mx == mc ? 1.0f : exp2f(mx - mc);  // the first chunk: 0 (or of zeros)
+      mx = mc;
+      clear_coefs<R>(lds, n);
+      float lc = 0.0f;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (r * L >= npts) break;
+        // a logit of -inf has weight 0 also while the maximum is -inf, where s - max is NaN; the
+        // maximum has weight 1 also where it is +inf
+        const float e = s[r] == -INFINITY ? 0.0f : s[r] == mx ? 1.0f : exp2f(s[r] - mx);
+        s[r] = r * L + lp < npts ? e : 0.0f;
+        lc += s[r];
+      }
+      lc = group_sum<L>(lc);
+      l = fmaf(l, corr, lc);
+      const float fix = slot_scale(lc);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (r * L >= npts) break;
+        if (r * L + lp < npts) add_coefs(pt[r], val, s[r] * fix);
+      }
+      float sum[U::kVec];
+      row_sums<D, BF16, R>(slot_rows<LY::kRowBytes>(g, v, win, b, m, global), lds, n, sum);
+#pragma unroll
+      for (int x = 0; x < U::kVec; ++x) o[x] = fmaf(o[x], corr, sum[x] * (lc / kSlotOne));
+      c0 += npts;
     }
-    if (active) {
-      const float inv = 1.0f / l;
-      char* ob = static_cast<char*>(out) + row * LY::kRowBytes + lane_off;
+    if (!active) continue;
+    const float inv = 1.0f / l;
+    if (lp < U::kLanes) {
+      char* ob = static_cast<char*>(out) + row * LY::kRowBytes + 16 * lp;
       if constexpr (BF16) {
         uint4 wv;
         wv.x = bf16_bits(o[0] * inv) | (bf16_bits(o[1] * inv) << 16);
@@ -150,11 +274,37 @@ __global__ __launch_bounds__(kBlockThreads) void fwd_kernel(
         wv.w = bf16_bits(o[6] * inv) | (bf16_bits(o[7] * inv) << 16);
         *reinterpret_cast<uint4*>(ob) = wv;
       } else {
-        *reinterpret_cast<float4*>(ob) = make_float4(o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
+        *reinterpret_cast<float4*>(ob) =
+            make_float4(o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
       }
-      if (lse != nullptr && sub == 0) lse[row] = (mx + log2f(l)) * kLn2;
+    }
+    if (lse != nullptr && lp == 0) lse[row] = (mx + log2f(l)) * kLn2;
+  }
+}
+
+// A tile goes one way or the other by the spread of its points (R = 0: every tile gathers).  Three
+// waves per SIMD either way, and the same LDS.
+template <int D, bool BF16, bool PW, int R, bool WHOLE>
+__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(R > 0 ? 3 : 1))) void
+fwd_kernel(Geometry g, const void* __restrict__ q, const void* __restrict__ k,
+           const void* __restrict__ v, const float* __restrict__ logits,
+           const float* __restrict__ offsets, void* __restrict__ out, float* __restrict__ lse,
+           PencilOrder po, int64_t vt0) {
+  constexpr size_t kPts = slot_words<Layout<D, BF16>::kLanes, 5>() * sizeof(int4);
+  constexpr size_t kSlots = R > 0 ? kWavesPerBlock * sizeof(SlotLds<R>) : 0;
+  __shared__ __attribute__((aligned(16))) char lds[kPts > kSlots ? kPts : kSlots];
+  PencilTile tl;
+  if (!pencil_tile(po, vt0 + blockIdx.x, tl)) return;  // no pencil left on this XCD
+  if constexpr (R > 0) {
+    if (compact_tile(g, po, tl, offsets)) {  // the same in every wave
+      slots_tile<D, BF16, PW, R, WHOLE>(
+          g, po, tl, q, k, v, logits, offsets, out, lse,
+          reinterpret_cast<SlotLds<R>*>(lds)[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)]);
+      return;
     }
   }
+  gather_tile<D, BF16, PW>(g, po, tl, q, k, v, logits, offsets, out, lse,
+                           reinterpret_cast<int4*>(lds));
 }
 
 // ---------------------------------------------------------------------------- launch
@@ -163,13 +313,27 @@ template <int D, bool BF16>
 hipError_t fwd_dispatch(const Geometry& g, const void* q, const void* k, const void* v,
                         const float* logits, const float* off, void* out, float* lse,
                         hipStream_t s) {
-  const PencilOrder po = query_order<D, BF16>(g);
-  const int blocks = grid_blocks(po.vtiles);
-  void* args[] = {(void*)&g,   (void*)&q,   (void*)&k,   (void*)&v,    (void*)&logits,
-                  (void*)&off, (void*)&out, (void*)&lse, (void*)&po};
-  const void* kern = logits != nullptr ? reinterpret_cast<const void*>(&fwd_kernel<D, BF16, true>)
-                                       : reinterpret_cast<const void*>(&fwd_kernel<D, BF16, false>);
-  return hipLaunchKernel(kern, dim3(blocks), dim3(kBlockThreads), args, 0, s);
+  const PencilOrder po = query_order<D, BF16>(g, true);
+  const bool pw = logits != nullptr;
+#define DSA3D_FWD(R, WHOLE)                                                    \
+  (pw ? reinterpret_cast<const void*>(&fwd_kernel<D, BF16, true, R, WHOLE>)   \
+      : reinterpret_cast<const void*>(&fwd_kernel<D, BF16, false, R, WHOLE>))
+  const void* kern;
+  if constexpr (slot_rows_ok<D, BF16>()) {
+    const bool whole = g.win_frames == g.T;
+    if (g.P <= 2 * kSlotLanes)
+      kern = whole ? DSA3D_FWD(2, true) : DSA3D_FWD(2, false);
+    else
+      kern = whole ? DSA3D_FWD(5, true) : DSA3D_FWD(5, false);
+  } else {
+    kern = DSA3D_FWD(0, false);
+  }
+#undef DSA3D_FWD
+  return launch_tiles(po.vtiles, [&](int64_t vt0, int blocks) {
+    void* args[] = {(void*)&g,   (void*)&q,   (void*)&k,   (void*)&v,  (void*)&logits,
+                    (void*)&off, (void*)&out, (void*)&lse, (void*)&po, (void*)&vt0};
+    return hipLaunchKernel(kern, dim3(blocks), dim3(kBlockThreads), args, 0, s);
+  });
 }
 
 }  // namespace

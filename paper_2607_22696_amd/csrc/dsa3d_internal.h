@@ -4,6 +4,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#ifndef DSA3D_TILE_FN
+#define DSA3D_TILE_FN __host__ __device__ inline __attribute__((always_inline))
+#endif
+#include "tile_order.h"
+
 namespace dsa3d {
 
 // Problem geometry as the kernels see it (validated on the host).
@@ -15,6 +20,7 @@ struct Geometry {
   float scale;        // logit scale (natural-log units)
   float scale_log2;   // scale * log2(e): logits are kept in base 2 inside the kernels
   int win_frames;     // frames per K/V buffer window (0: corners are read with global loads)
+  FastDiv by_heads, by_khw, by_kw;  // heads, kh * kw and kw as divisors
 };
 
 // Frames of a K/V buffer window: a structured buffer addresses < 4 GB from its base and its

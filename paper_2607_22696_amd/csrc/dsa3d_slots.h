@@ -1,0 +1,755 @@
+// Distinct-voxel slots: how the query-owned kernels read a corner row once for four queries.
+//
+// The P sampling points of a query have 8 P trilinear corners, but its points share most of their
+// voxels, and so do neighbouring queries: with offsets of about one token the 4 x 216 corners of
+// four neighbours under a 3x3x3 kernel are 267 distinct voxels, and the 4 x 1176 of a 3x7x7 kernel
+// 792.  What bounds a kernel that loads every corner is the rate at which a compute unit takes
+// row requests, so here a wave first gives every distinct voxel of its four queries a slot and
+// then sweeps the slots: a sweep forms each slot row's dot product with the four queries' vectors
+// (row_dots), the points combine their eight values from LDS, and a sweep for weighted sums
+// (row_sums) reads each row once with each query's summed coefficient of all corners on it.
+//
+// A wave holds four neighbours along x, 16 lanes each, one point per lane and round.  Slots come
+// from a bitmap of the wave's box of voxels (32 along x in a word, 16 x 16 words): every point sets
+// the two bits of its four corner pairs, a scan over the words' bit counts numbers the set bits,
+// and the slot of a pair's lower x corner is the number of bits below it (its upper corner has the
+// next slot).  Points that leave the box, or need more slots than there are, are taken a round at
+// a time with slot = 8 lane + corner and the same sweeps: always correct, but slow, so tiles
+// whose points spread far are left to the kernels that load every corner (compact_tile).
+//
+// The sweeps use the matrix cores for bf16 rows:
+//  * row_dots: lane l reads 16 bytes of the row of slot l / 4, so that four neighbouring lanes
+//    read 64 contiguous bytes (with the 16 slots on neighbouring lanes a load takes four times
+//    as long).  As the A of v_mfma_f32_16x16x32_bf16 that lane is row l % 16 = 4 (slot % 4) +
+//    chunk and K group slot / 4; column n = 4 a + c of B holds the vector's chunk c in K group a
+//    and zeros elsewhere, so result (4 s + c, 4 a + c) is what chunk c of slot 4 a + s adds.
+//  * row_sums: the slots are the products' K.  A row is read whole by D / 8 lanes; after eight
+//    loads a lane holds 8 channels of 8 slots, and byte permutes pair them into the B operand of
+//    one product per channel.  A holds the slots' coefficients byte by byte (a byte is exact in
+//    bf16), one byte of one query per row, so that one product takes them all.
+// fp32 rows take the vector ALU: products and sums in fp32.
+//
+// Coefficients are summed per slot in LDS as 32-bit fixed-point numbers, 2^30 standing for the sum
+// of the magnitudes of the query's coefficients: each corner adds at most 2^-31 of that sum as
+// rounding, less than the rounding of an fp32 sum of the row.  (An LDS float add takes 194
+// cycles of a compute unit per instruction and an integer add 11, with addresses as they come
+// here.)
+#pragma once
+
+#include "dsa3d_device.h"
+
+namespace dsa3d {
+namespace dev {
+
+typedef __bf16 slot_bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float slot_f32x4_t __attribute__((ext_vector_type(4)));
+
+constexpr int kSlotQueries = 4;  // per wave, neighbours along x
+constexpr int kSlotLanes = 16;   // lanes (points of a round) per query
+constexpr int kSlotBoxX = 32, kSlotBoxY = 16, kSlotBoxZ = 16;
+constexpr int kSlotWords = kSlotBoxY * kSlotBoxZ;  // four per lane
+static_assert(kSlotWords == 256, "four words per lane");
+
+// R rounds of points are numbered together: up to 32 points of a query in 512 slots, or 80 in 640
+// (a round of 64 lanes on its own needs 512).  LDS holds four workgroups of the first kind on a
+// compute unit and three of the second.
+template <int R>
+constexpr int slot_cap() { return R <= 2 ? 512 : 640; }
+
+// A wave's slots: the voxel of each, and per query its dot product or coefficient.  The bitmap
+// (bits and the number of slots before a word) is needed only until the slots are numbered.
+template <int R>
+struct SlotLds {
+  __attribute__((aligned(16))) uint32_t list[slot_cap<R>()];
+  union {
+    __attribute__((aligned(16))) uint2 words[kSlotWords];
+    // 16 words of padding: the four queries' values of a slot lie on different banks
+    __attribute__((aligned(16))) float val[kSlotQueries][slot_cap<R>() + 16];
+  };
+};
+
+// Lanes of one wave exchange data through LDS, whose accesses a wave makes in order: only the
+// compiler has to keep them so.
+__device__ inline __attribute__((always_inline)) void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// ---------------------------------------------------------------------------- lane reductions
+
+template <int CTRL>
+__device__ inline __attribute__((always_inline)) int dpp_movi(int x) {
+  return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xF, 0xF, false);
+}
+
+// op over the N (16 or 64) lanes of a query or of the wave; every lane gets the result.
+template <int N, class Op>
+__device__ inline __attribute__((always_inline)) int lane_reduce(int x, Op op) {
+  x = op(x, dpp_movi<0xB1>(x));   // lane ^ 1
+  x = op(x, dpp_movi<0x4E>(x));   // lane ^ 2
+  x = op(x, dpp_movi<0x141>(x));  // the other quad of 8
+  x = op(x, dpp_movi<0x140>(x));  // the other half of 16
+  if constexpr (N == 64) {
+    const auto r = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
+    x = op((int)r[0], (int)r[1]);
+    const auto s = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+    x = op((int)s[0], (int)s[1]);
+  }
+  return x;
+}
+template <int N>
+__device__ inline __attribute__((always_inline)) int lane_min(int x) {
+  return lane_reduce<N>(x, [](int a, int b) { return a < b ? a : b; });
+}
+template <int N>
+__device__ inline __attribute__((always_inline)) float lane_maxf(float x) {
+  return __int_as_float(lane_reduce<N>(__float_as_int(x), [](int a, int b) {
+    return __float_as_int(fmaxf(__int_as_float(a), __int_as_float(b)));
+  }));
+}
+// Inclusive scan over the wave.
+__device__ inline __attribute__((always_inline)) uint32_t lane_scan(uint32_t v) {
+  int x = (int)v;
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1, 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2, 3
+  return (uint32_t)x;
+}
+
+// ---------------------------------------------------------------------------- tiles
+
+// Where tiles may be taken by slots, a cell of the pencil order is four tokens along x.  Token e of
+// a tile: false if it is past the pencil or the grid.
+__device__ inline __attribute__((always_inline)) bool slot_token(const PencilOrder& po,
+                                                                 const Geometry& g,
+                                                                 const PencilTile& tl, int e,
+                                                                 int& i, int& j) {
+  int cell;
+  const bool in = pencil_cell(po, tl, e / kSlotQueries, i, cell);
+  j = cell * kSlotQueries + e % kSlotQueries;
+  return in && j < g.W;
+}
+
+// Whether a tile is worth numbering: the points (up to 64) of its first token, with their corners,
+// span at most kCompactBox voxels.
+constexpr int kCompactBox = 1400;
+
+__device__ inline __attribute__((always_inline)) bool compact_tile(const Geometry& g,
+                                                                   const PencilOrder& po,
+                                                                   const PencilTile& tl,
+                                                                   const float* offsets) {
+  const int b = tl.group / g.by_heads, m = tl.group - b * g.heads;
+  int i, j;
+  slot_token(po, g, tl, 0, i, j);
+  i = min(i, g.H - 1);  // a tile past a ragged pencil's end: any token will do
+  j = min(j, g.W - 1);
+  const int64_t row = ((int64_t)b * g.N + ((tl.frame * g.H + i) * g.W + j)) * g.heads + m;
+  const int p = min((int)(threadIdx.x & 63), g.P - 1);
+  const float* off = offsets + (row * g.P + p) * 3;
+  const int it = p / g.by_khw, rp = p - it * (g.kh * g.kw), ih = rp / g.by_kw, iw = rp - ih * g.kw;
+  int x, y, z;
+  float f;
+  axis((float)(j + iw - (g.kw - 1) / 2), off[0], g.W, x, f);
+  axis((float)(i + ih - (g.kh - 1) / 2), off[1], g.H, y, f);
+  axis((float)(tl.frame + it - (g.kt - 1) / 2), off[2], g.T, z, f);
+  // extents, each at most 256 so that the product stays in range
+  const int ex = min(-lane_min<64>(-x) - lane_min<64>(x), 255) + 2;
+  const int ey = min(-lane_min<64>(-y) - lane_min<64>(y), 255) + 2;
+  const int ez = min(-lane_min<64>(-z) - lane_min<64>(z), 255) + 2;
+  return __builtin_amdgcn_readfirstlane(ex * ey * ez) <= kCompactBox;
+}
+
+// ---------------------------------------------------------------------------- rows
+
+// Byte offset of a voxel outside the grid: beyond every buffer (a window ends below it), and
+// adding a row's bytes to it does not wrap.
+constexpr uint32_t kNoVoxel = 0xfffff000u;
+
+struct SlotWindow {
+  int t0, frames;  // window [t0, t0 + frames); frames == 0: no window
+  int64_t base;    // byte offset of head m's row of its first token
+  uint32_t bytes;  // from there to the end of the window
+};
+
+template <int ROW_BYTES>
+__device__ inline __attribute__((always_inline)) SlotWindow slot_window(const Geometry& g, int b,
+                                                                       int m, int t) {
+  SlotWindow w;
+  w.frames = g.win_frames;
+  w.t0 = w.frames > 0 ? min(max(t - (w.frames - 1) / 2, 0), g.T - w.frames) : 0;
+  w.base = (((int64_t)b * g.T + w.t0) * g.H * g.W * g.heads + m) * ROW_BYTES;
+  const uint64_t span = (uint64_t)w.frames * g.H * g.W * g.heads * ROW_BYTES;
+  w.bytes = w.frames > 0 ? (uint32_t)(span - (uint32_t)m * ROW_BYTES) : 0u;
+  return w;
+}
+
+// Rows of one (batch item, head): a raw buffer over the window of frames around the tile when
+// every corner of the wave lies in it (an entry is the byte offset of the voxel's row), else the
+// batch item's tokens through global loads (an entry is the token).
+struct SlotRows {
+  __amdgpu_buffer_rsrc_t rsrc;
+  const char* base;  // head m's row of the batch item's first token
+  uint32_t tok_bytes;
+  bool global;       // wave-uniform
+};
+
+template <int ROW_BYTES>
+__device__ inline __attribute__((always_inline)) SlotRows slot_rows(const Geometry& g,
+                                                                    const void* x,
+                                                                    const SlotWindow& w, int b,
+                                                                    int m, bool global) {
+  SlotRows r;
+  r.rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(static_cast<const char*>(x) + w.base),
+                                             (short)0, (int)w.bytes, kBufferFlags);
+  r.base = static_cast<const char*>(x) + ((int64_t)b * g.N * g.heads + m) * ROW_BYTES;
+  r.tok_bytes = (uint32_t)g.heads * ROW_BYTES;
+  r.global = global;
+  return r;
+}
+
+// 16 bytes at `off` of the row of list entry e (zeros for a voxel outside the grid).
+template <bool GLOBAL>
+__device__ inline __attribute__((always_inline)) uint4 slot_load(const SlotRows& r, uint32_t e,
+                                                                 uint32_t off) {
+  if constexpr (GLOBAL) {
+    uint4 x = make_uint4(0u, 0u, 0u, 0u);
+    if (e != kNoVoxel)
+      x = *reinterpret_cast<const uint4*>(r.base + (uint64_t)e * r.tok_bytes + off);
+    return x;
+  } else {
+    return __builtin_bit_cast(
+        uint4, __builtin_amdgcn_raw_buffer_load_b128(r.rsrc, (int)(e + off), 0, 0));
+  }
+}
+
+// ---------------------------------------------------------------------------- points
+
+// One sampling point of a lane: cell, fractions and the slots of its four corner pairs.
+struct SlotPoint {
+  int x, y, z;
+  float fx, fy, fz;
+  uint32_t s01, s23;  // slots of the lower x corners of pairs e = 2 cz + cy, 16 bits each
+
+  __device__ inline __attribute__((always_inline)) void set(const Geometry& g, int t, int i, int j,
+                                                            int p, const float* off) {
+    const int it = p / g.by_khw, r = p - it * (g.kh * g.kw), ih = r / g.by_kw, iw = r - ih * g.kw;
+    axis((float)(j + iw - (g.kw - 1) / 2), off[0], g.W, x, fx);
+    axis((float)(i + ih - (g.kh - 1) / 2), off[1], g.H, y, fy);
+    axis((float)(t + it - (g.kt - 1) / 2), off[2], g.T, z, fz);
+  }
+  __device__ inline __attribute__((always_inline)) int slot(int e) const {
+    const uint32_t s = e < 2 ? s01 : s23;
+    return (int)(e & 1 ? s >> 16 : s & 0xffffu);
+  }
+  // weights of the corners c = 4 cz + 2 cy + cx
+  __device__ inline __attribute__((always_inline)) void weights(float (&w)[8]) const {
+    const float ax[2] = {1.0f - fx, fx}, ay[2] = {1.0f - fy, fy}, az[2] = {1.0f - fz, fz};
+#pragma unroll
+    for (int c = 0; c < 8; ++c) w[c] = ax[c & 1] * (ay[(c >> 1) & 1] * az[c >> 2]);
+  }
+  // the point's eight values of its query's `val`
+  __device__ inline __attribute__((always_inline)) void read(const float* val,
+                                                             float (&v)[8]) const {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float* p = val + slot(e);
+      v[2 * e] = p[0];
+      v[2 * e + 1] = p[1];
+    }
+  }
+};
+
+// WHOLE: the window spans all frames, so no corner can lie outside it.
+//
+// Numbers the slots of a wave's queries for rounds of points (npts per query) and writes the
+// voxel list.  In: pt[r], the lane's point of round r (lanes past the end repeat a point of the
+// range).  Returns the number of points taken per query: npts, or one round's when they do not
+// fit the box or the slots; n: the slot count; `global`: the list holds tokens.
+template <int R, bool WHOLE>
+__device__ inline __attribute__((always_inline)) int number_slots(const Geometry& g,
+                                                                  const SlotWindow& win,
+                                                                  uint32_t tok_bytes,
+                                                                  SlotLds<R>& lds,
+                                                                  SlotPoint (&pt)[R], int npts,
+                                                                  int& n, bool& global) {
+  constexpr int L = kSlotLanes;
+  const int lane = threadIdx.x & 63;
+  // the box starts at the smallest cell
+  int x0 = pt[0].x, y0 = pt[0].y, z0 = pt[0].z;
+#pragma unroll
+  for (int r = 1; r < R; ++r) {
+    if (r * L >= npts) break;
+    x0 = min(x0, pt[r].x);
+    y0 = min(y0, pt[r].y);
+    z0 = min(z0, pt[r].z);
+  }
+  x0 = __builtin_amdgcn_readfirstlane(lane_min<64>(x0));
+  y0 = __builtin_amdgcn_readfirstlane(lane_min<64>(y0));
+  z0 = __builtin_amdgcn_readfirstlane(lane_min<64>(z0));
+  bool out = false, slow = !WHOLE && win.frames == 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (r * L >= npts) break;
+    out = out || pt[r].x - x0 > kSlotBoxX - 2 || pt[r].y - y0 > kSlotBoxY - 2 ||
+          pt[r].z - z0 > kSlotBoxZ - 2;
+#pragma unroll
+    for (int c = 0; c < 2 && !WHOLE; ++c)
+      slow = slow || ((unsigned)(pt[r].z + c) < (unsigned)g.T &&
+                      (unsigned)(pt[r].z + c - win.t0) >= (unsigned)win.frames);
+  }
+  bool fits = __builtin_amdgcn_ballot_w64(out) == 0;
+  global = !WHOLE && __builtin_amdgcn_ballot_w64(slow) != 0;
+  n = 0;
+  wave_sync();
+  if (fits) {
+    uint4* w4 = reinterpret_cast<uint4*>(lds.words) + 2 * lane;
+    w4[0] = make_uint4(0u, 0u, 0u, 0u);
+    w4[1] = make_uint4(0u, 0u, 0u, 0u);
+    wave_sync();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (r * L >= npts) break;
+      const uint32_t bits = 3u << (pt[r].x - x0);
+      const int at = (pt[r].z - z0) * kSlotBoxY + pt[r].y - y0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        __hip_atomic_fetch_or(&lds.words[at + (e & 1) + (e >> 1) * kSlotBoxY].x, bits,
+                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    }
+    wave_sync();
+    uint4 a = w4[0], b = w4[1];
+    const uint32_t n0 = __popc(a.x), n1 = n0 + __popc(a.z), n2 = n1 + __popc(b.x),
+                   n3 = n2 + __popc(b.z);
+    const uint32_t incl = lane_scan(n3), s = incl - n3;
+    n = __builtin_amdgcn_readlane((int)incl, 63);
+    a.y = s;
+    a.w = s + n0;
+    b.y = s + n1;
+    b.w = s + n2;
+    w4[0] = a;
+    w4[1] = b;
+    wave_sync();
+    fits = n <= slot_cap<R>();
+  }
+  if (fits) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (r * L >= npts) break;
+      const uint32_t below = (1u << (pt[r].x - x0)) - 1u;
+      const int at = (pt[r].z - z0) * kSlotBoxY + pt[r].y - y0;
+      uint32_t s[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint2 w = lds.words[at + (e & 1) + (e >> 1) * kSlotBoxY];
+        s[e] = w.y + __popc(w.x & below);
+      }
+      pt[r].s01 = s[0] | (s[1] << 16);
+      pt[r].s23 = s[2] | (s[3] << 16);
+    }
+  } else {
+    npts = min(npts, L);
+    n = 64 * 8;
+    pt[0].s01 = (uint32_t)(8 * lane) * 0x10001u + 0x20000u;
+    pt[0].s23 = pt[0].s01 + 0x40004u;
+  }
+  // the list: corners on one voxel write the same entry
+  const int HW = g.H * g.W;
+  const uint32_t step = global ? 1u : tok_bytes;
+  const uint32_t dy = (uint32_t)g.W * step, dz = (uint32_t)HW * step;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (r * L >= npts) break;
+    const int x = pt[r].x, y = pt[r].y, z = pt[r].z;
+    // modulo 2^32: only the sums of corners inside the grid are used, and those are exact
+    const uint32_t org = (uint32_t)(z - (global ? 0 : win.t0)) * dz + (uint32_t)y * dy +
+                         (uint32_t)x * step;
+    const bool okx[2] = {(unsigned)x < (unsigned)g.W, (unsigned)(x + 1) < (unsigned)g.W};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool ok = (unsigned)(y + (e & 1)) < (unsigned)g.H &&
+                      (unsigned)(z + (e >> 1)) < (unsigned)g.T;
+      const uint32_t o = org + ((e & 1) ? dy : 0u) + ((e >> 1) ? dz : 0u);
+      uint32_t* p = lds.list + pt[r].slot(e);
+      p[0] = ok && okx[0] ? o : kNoVoxel;
+      p[1] = ok && okx[1] ? o + step : kNoVoxel;
+    }
+  }
+  wave_sync();
+  if (n + lane < ((n + 63) & ~63)) lds.list[n + lane] = kNoVoxel;  // the sweeps' last batch
+  wave_sync();
+  return npts;
+}
+
+// ---------------------------------------------------------------------------- dot products
+
+// The four queries' vectors as row_dots takes them: bf16, the B operand of each 32-channel block;
+// fp32, the lane's 16 bytes of the row.
+template <int D, bool BF16>
+struct SlotVecs {
+  static constexpr int kParts = BF16 ? D / 32 : 1;
+  uint4 f[kSlotQueries][kParts];
+  __device__ inline __attribute__((always_inline)) void load(const char* x,
+                                                             const int64_t (&row)[kSlotQueries]) {
+    constexpr int64_t kRowBytes = D * (BF16 ? 2 : 4);
+    const int lane = threadIdx.x & 63;
+    const bool mine = !BF16 || (lane >> 4) == ((lane >> 2) & 3);
+#pragma unroll
+    for (int w = 0; w < kSlotQueries; ++w)
+#pragma unroll
+      for (int k = 0; k < kParts; ++k) {
+        f[w][k] = make_uint4(0u, 0u, 0u, 0u);
+        if (mine)
+          f[w][k] = *reinterpret_cast<const uint4*>(
+              x + row[w] * kRowBytes + (BF16 ? 64 * k + 16 * (lane & 3) : 16 * (lane % (D / 4))));
+      }
+  }
+};
+
+// val[w][s] = <vector of query w, row of slot s> for n slots.
+template <int D, bool BF16, bool GLOBAL, int R>
+__device__ inline __attribute__((always_inline)) void row_dots_of(const SlotRows& rows,
+                                                                  SlotLds<R>& lds,
+                                                                  const SlotVecs<D, BF16>& vec,
+                                                                  int n) {
+  const int lane = threadIdx.x & 63;
+  if constexpr (BF16) {
+    constexpr int KS = D / 32;
+    const uint32_t off = 16u * (lane & 3);
+    float* const out = &lds.val[lane & 3][(lane & 12) + (lane >> 4)];
+    for (int base = 0; base < n; base += 32) {
+      uint4 a[2][KS];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint32_t e = lds.list[base + 16 * h + (lane >> 2)];  // past the end: no voxel
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) a[h][ks] = slot_load<GLOBAL>(rows, e, off + 64u * ks);
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        float s[kSlotQueries];
+#pragma unroll
+        for (int w = 0; w < kSlotQueries; ++w) {
+          slot_f32x4_t c = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks)
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(slot_bf16x8_t, a[h][ks]),
+                __builtin_bit_cast(slot_bf16x8_t, vec.f[w][ks]), c, 0, 0, 0);
+          // lane l: results (4 (l / 16) + i, l % 16); chunk l % 4 of slot 4 ((l / 4) % 4) + l / 16
+          const float lo = lane & 1 ? c[1] : c[0], hi = lane & 1 ? c[3] : c[2];
+          s[w] = lane & 2 ? hi : lo;
+        }
+        // the sum over the four lanes of a slot, query l % 4's in lane l
+        const float u0 = (lane & 1 ? s[1] : s[0]) + dpp_mov<0xB1>(lane & 1 ? s[0] : s[1]);
+        const float u1 = (lane & 1 ? s[3] : s[2]) + dpp_mov<0xB1>(lane & 1 ? s[2] : s[3]);
+        out[base + 16 * h] = (lane & 2 ? u1 : u0) + dpp_mov<0x4E>(lane & 2 ? u0 : u1);
+      }
+    }
+  } else {
+    constexpr int L = D / 4, SPL = 64 / L;
+    const int sub = lane % L, grp = lane / L;
+    for (int base = 0; base < n; base += 8 * SPL) {
+      uint4 a[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        a[i] = slot_load<GLOBAL>(rows, lds.list[base + i * SPL + grp], 16u * sub);
+#pragma unroll
+      for (int w = 0; w < kSlotQueries; ++w) {
+        float keep = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float s = group_sum<L>(chunk_dot<false>(vec.f[w][0], a[i]));
+          keep = sub == i ? s : keep;
+        }
+        if (sub < 8) lds.val[w][base + sub * SPL + grp] = keep;
+      }
+    }
+  }
+}
+
+template <int D, bool BF16, int R>
+__device__ inline __attribute__((always_inline)) void row_dots(const SlotRows& rows,
+                                                               SlotLds<R>& lds,
+                                                               const SlotVecs<D, BF16>& vec,
+                                                               int n) {
+  if (!rows.global)
+    row_dots_of<D, BF16, false, R>(rows, lds, vec, n);
+  else
+    row_dots_of<D, BF16, true, R>(rows, lds, vec, n);
+  wave_sync();
+}
+
+// ---------------------------------------------------------------------------- weighted sums
+
+// Lanes that read a row of row_sums (16 bytes each) and the channels a lane ends up with: lane l
+// gets channels kVec (l % kLanes) .. of a query's sum.
+template <int D, bool BF16>
+struct SlotSum {
+  static constexpr int kLanes = D * (BF16 ? 2 : 4) / 16;
+  static constexpr int kVec = BF16 ? 8 : 4;
+  static constexpr int kPer = 64 / kLanes;  // rows per load
+  static constexpr int kBatch = 8 * kPer;   // slots of eight loads: load i takes slots 8 k + i
+};
+
+// Clears the coefficients of n slots (and of the rest of the last batch).
+template <int R>
+__device__ inline __attribute__((always_inline)) void clear_coefs(SlotLds<R>& lds, int n) {
+  const int lane = threadIdx.x & 63;
+  wave_sync();
+  for (int s = 4 * (lane & 15); s < ((n + 63) & ~63); s += 64)
+    *reinterpret_cast<float4*>(&lds.val[lane >> 4][s]) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  wave_sync();
+}
+
+// The factor that takes coefficients whose magnitudes sum to `sum` to fixed point.
+constexpr float kSlotOne = 1073741824.0f;  // 2^30
+__device__ inline __attribute__((always_inline)) float slot_scale(float sum) {
+  return kSlotOne / fmaxf(sum, 0x1p-60f);
+}
+
+// Adds a point's corner coefficients c * (its corner weights) to its query's slots; c in fixed
+// point.
+__device__ inline __attribute__((always_inline)) void add_coefs(const SlotPoint& pt, float* val,
+                                                                float c) {
+  float w[8];
+  pt.weights(w);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    int* p = reinterpret_cast<int*>(val) + pt.slot(e);
+    __hip_atomic_fetch_add(p, __float2int_rn(w[2 * e] * c), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WAVEFRONT);
+    __hip_atomic_fetch_add(p + 1, __float2int_rn(w[2 * e + 1] * c), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WAVEFRONT);
+  }
+}
+
+// The part that lane l keeps of per-lane sums of the four queries: query l / 16, summed over the
+// lanes that hold the same channels.
+template <int LANES>
+__device__ inline __attribute__((always_inline)) float keep_sum(const float (&q)[kSlotQueries]) {
+  float s[kSlotQueries];
+#pragma unroll
+  for (int w = 0; w < kSlotQueries; ++w)
+    s[w] = LANES == 8 ? q[w] + dpp_mov<0x128>(q[w]) : q[w];  // row_ror:8
+  // each swap hands one half (one row) of the first over for one of the second
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(s[0]), __float_as_uint(s[2]),
+                                                  false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(s[1]), __float_as_uint(s[3]),
+                                                  false, false);
+  const float s02 = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const float s13 = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  const auto c = __builtin_amdgcn_permlane16_swap(__float_as_uint(s02), __float_as_uint(s13), false,
+                                                  false);
+  return __uint_as_float(c[0]) + __uint_as_float(c[1]);
+}
+
+// sum[x] = sum over n slots of val[query][s] * row s (the coefficients as they are, in fixed point),
+// in fp32 on the vector ALU.  SAFE: a row whose coefficient is zero is not touched.
+template <int D, bool BF16, bool GLOBAL, bool SAFE, int R>
+__device__ inline __attribute__((always_inline)) void row_sums_valu(
+    const SlotRows& rows, const SlotLds<R>& lds, int n, float (&sum)[SlotSum<D, BF16>::kVec]) {
+  using U = SlotSum<D, BF16>;
+  const int lane = threadIdx.x & 63, sub = lane % U::kLanes, grp = lane / U::kLanes;
+  float part[kSlotQueries][U::kVec];
+#pragma unroll
+  for (int w = 0; w < kSlotQueries; ++w)
+#pragma unroll
+    for (int x = 0; x < U::kVec; ++x) part[w][x] = 0.0f;
+  for (int base = 0; base < n; base += U::kBatch) {
+    const int at = base + 8 * grp;
+    uint4 a[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) a[i] = slot_load<GLOBAL>(rows, lds.list[at + i], 16u * sub);
+#pragma unroll
+    for (int w = 0; w < kSlotQueries; ++w) {
+      const int4* c4 = reinterpret_cast<const int4*>(&lds.val[w][at]);
+      const int4 ca = c4[0], cb = c4[1];
+      const int c[8] = {ca.x, ca.y, ca.z, ca.w, cb.x, cb.y, cb.z, cb.w};
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (!SAFE || c[i] != 0) chunk_axpy<BF16>(part[w], (float)c[i], a[i]);
+    }
+  }
+#pragma unroll
+  for (int x = 0; x < U::kVec; ++x) {
+    const float q[kSlotQueries] = {part[0][x], part[1][x], part[2][x], part[3][x]};
+    sum[x] = keep_sum<U::kLanes>(q);
+  }
+}
+
+// The same on the matrix cores (bf16 rows).  Lane l reads the row of slot base + 8 (l / kLanes) +
+// i; as the products' B its column is l % 16 and its K group l / 16, so a 16-lane group holds
+// SETS = 16 / kLanes sets of rows side by side.  A's row 4 s + p holds byte p (the top one signed) of
+// the coefficients of set s % SETS for query SETS (s / SETS) + t in product t; result element p
+// of lane group G is then byte p's share of the sum of set G % SETS, meant for the columns of
+// that set.
+template <int D, bool GLOBAL, int R>
+__device__ inline __attribute__((always_inline)) void row_sums_mfma(const SlotRows& rows,
+                                                                    const SlotLds<R>& lds, int n,
+                                                                    float (&sum)[8]) {
+  using U = SlotSum<D, true>;
+  constexpr int SETS = 16 / U::kLanes;
+  static_assert(SETS == 1 || SETS == 2, "head_dim 64 or 128");
+  const int lane = threadIdx.x & 63, sub = lane % U::kLanes, grp = lane / U::kLanes;
+  const int a_s = (lane >> 2) & 3, a_set = a_s % SETS, a_q = a_s / SETS * SETS;
+  const int shift = 8 * (lane & 3);
+  const float bias = (lane & 3) == 3 ? 128.0f : 0.0f;
+  slot_f32x4_t acc[SETS][8];
+#pragma unroll
+  for (int t = 0; t < SETS; ++t)
+#pragma unroll
+    for (int x = 0; x < 8; ++x) acc[t][x] = slot_f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int base = 0; base < n; base += U::kBatch) {
+    uint32_t e[8];
+    {
+      const uint4* l4 = reinterpret_cast<const uint4*>(lds.list + base + 8 * grp);
+      const uint4 ea = l4[0], eb = l4[1];
+      e[0] = ea.x; e[1] = ea.y; e[2] = ea.z; e[3] = ea.w;
+      e[4] = eb.x; e[5] = eb.y; e[6] = eb.z; e[7] = eb.w;
+    }
+    uint4 r[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = slot_load<GLOBAL>(rows, e[i], 16u * sub);
+    slot_bf16x8_t a[SETS];
+#pragma unroll
+    for (int t = 0; t < SETS; ++t) {
+      const uint4* c4 = reinterpret_cast<const uint4*>(
+          &lds.val[a_q + t][base + 8 * ((lane >> 4) * SETS + a_set)]);
+      const uint4 ca = c4[0], cb = c4[1];
+      const uint32_t c[8] = {ca.x, ca.y, ca.z, ca.w, cb.x, cb.y, cb.z, cb.w};
+      uint32_t u[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i)  // this lane's byte: at most 8 bits, so exact as a bf16
+        u[i] = __float_as_uint((float)(((c[i] ^ 0x80000000u) >> shift) & 255u) - bias);
+      a[t] = __builtin_bit_cast(
+          slot_bf16x8_t, make_uint4(__builtin_amdgcn_perm(u[1], u[0], 0x07060302u),
+                                    __builtin_amdgcn_perm(u[3], u[2], 0x07060302u),
+                                    __builtin_amdgcn_perm(u[5], u[4], 0x07060302u),
+                                    __builtin_amdgcn_perm(u[7], u[6], 0x07060302u)));
+    }
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      uint32_t lo[4], hi[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint4 ra = r[2 * i], rb = r[2 * i + 1];
+        const uint32_t ua = w == 0 ? ra.x : w == 1 ? ra.y : w == 2 ? ra.z : ra.w;
+        const uint32_t ub = w == 0 ? rb.x : w == 1 ? rb.y : w == 2 ? rb.z : rb.w;
+        lo[i] = __builtin_amdgcn_perm(ub, ua, 0x05040100u);
+        hi[i] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
+      }
+      const slot_bf16x8_t bl =
+          __builtin_bit_cast(slot_bf16x8_t, make_uint4(lo[0], lo[1], lo[2], lo[3]));
+      const slot_bf16x8_t bh =
+          __builtin_bit_cast(slot_bf16x8_t, make_uint4(hi[0], hi[1], hi[2], hi[3]));
+#pragma unroll
+      for (int t = 0; t < SETS; ++t) {
+        acc[t][2 * w] =
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t], bl, acc[t][2 * w], 0, 0, 0);
+        acc[t][2 * w + 1] =
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t], bh, acc[t][2 * w + 1], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int x = 0; x < 8; ++x) {
+    float s[SETS];
+#pragma unroll
+    for (int t = 0; t < SETS; ++t) {
+      s[t] = fmaf(acc[t][x][3], 0x1p24f, fmaf(acc[t][x][2], 0x1p16f,
+                                              fmaf(acc[t][x][1], 0x1p8f, acc[t][x][0])));
+      if constexpr (SETS == 2) {
+        // lane groups 2 h and 2 h + 1 hold sets 0 and 1 of query 2 h + t: the sum of the two
+        s[t] = (lane & 15) / U::kLanes == ((lane >> 4) & 1) ? s[t] : 0.0f;
+        s[t] += dpp_mov<0x128>(s[t]);  // row_ror:8
+        const auto h = __builtin_amdgcn_permlane16_swap(__float_as_uint(s[t]),
+                                                        __float_as_uint(s[t]), false, false);
+        s[t] = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+      }
+    }
+    sum[x] = SETS == 2 && (lane & 16) ? s[SETS - 1] : s[0];
+  }
+}
+
+// sum[x]: channel kVec (l % kLanes) + x of the sum over n slots of coefficient * row for query
+// l / 16, the coefficients in fixed point.  An infinite or NaN row value meets the zero
+// coefficients of the queries that do not sample it, and on the matrix cores the zero bytes of
+// those that do, and gives NaN; a wave that sees a NaN takes its sums again without them.
+template <int D, bool BF16, bool GLOBAL, int R>
+__device__ inline __attribute__((always_inline)) void row_sums_of(
+    const SlotRows& rows, const SlotLds<R>& lds, int n, float (&sum)[SlotSum<D, BF16>::kVec]) {
+  if constexpr (BF16)
+    row_sums_mfma<D, GLOBAL, R>(rows, lds, n, sum);
+  else
+    row_sums_valu<D, false, GLOBAL, false, R>(rows, lds, n, sum);
+  bool nan = false;
+#pragma unroll
+  for (int x = 0; x < SlotSum<D, BF16>::kVec; ++x) nan = nan || sum[x] != sum[x];
+  if (__builtin_amdgcn_ballot_w64(nan) != 0)
+    row_sums_valu<D, BF16, GLOBAL, true, R>(rows, lds, n, sum);
+}
+
+template <int D, bool BF16, int R>
+__device__ inline __attribute__((always_inline)) void row_sums(
+    const SlotRows& rows, const SlotLds<R>& lds, int n, float (&sum)[SlotSum<D, BF16>::kVec]) {
+  wave_sync();
+  if (!rows.global)
+    row_sums_of<D, BF16, false, R>(rows, lds, n, sum);
+  else
+    row_sums_of<D, BF16, true, R>(rows, lds, n, sum);
+  wave_sync();
+}
+
+// ---------------------------------------------------------------------------- launch shape
+
+// Whether the slot kernels are built for this row size.
+template <int D, bool BF16>
+constexpr bool slot_rows_ok() {
+  return SlotSum<D, BF16>::kLanes == 8 || SlotSum<D, BF16>::kLanes == 16;
+}
+
+// Pencil order of the query-owned kernels.  Where the slot kernels are built, cells of four tokens
+// along x, else single tokens.  A tile is a workgroup's rows with a row on kLanes lanes.  Pencils are about 12 x 12 tokens: at 64x68x120, 24
+// heads x 128, 3x5x5, offsets U[-8, 8], the forward took 159 / 162 / 197 ms with pencils of about
+// 12 x 12 / 16 x 16 / 24 x 24 tokens.
+// A grid whose tiles would leave compute units idle gets smaller ones, down to one cell, of which a
+// workgroup's other waves have nothing (4x8x8 tokens, 2 heads x 32, fp32: 17.6 -> 10.6 us).
+constexpr int kFillTiles = 512;  // two workgroups per compute unit
+
+template <int D, bool BF16>
+inline PencilOrder query_order(const Geometry& g, bool fill = false) {
+  constexpr int Q = slot_rows_ok<D, BF16>() ? kSlotQueries : 1;
+  int run = Layout<D, BF16>::kRowsPerBlock / Q;
+  const int64_t cells = (int64_t)g.B * g.heads * g.T * g.H * ((g.W + Q - 1) / Q);
+  while (fill && Q > 1 && run > 1 && cells < (int64_t)run * kFillTiles) run /= 2;
+  return plan_pencils(g.B * g.heads, g.T, g.H, (g.W + Q - 1) / Q, run, 12, 12 / Q);
+}
+
+// Token e of a tile in that order; false if it is past the pencil or the grid.
+template <int D, bool BF16>
+__device__ inline __attribute__((always_inline)) bool query_token(const PencilOrder& po,
+                                                                  const Geometry& g,
+                                                                  const PencilTile& tl, int e,
+                                                                  int& i, int& j) {
+  if constexpr (slot_rows_ok<D, BF16>())
+    return slot_token(po, g, tl, e, i, j) && e < po.run * kSlotQueries;
+  return pencil_cell(po, tl, e, i, j);
+}
+
+// Launches one workgroup per virtual tile, at most kMaxBlocks (a multiple of 8, which keeps a tile
+// on its XCD) at a time: launch(first tile, workgroups).  The kernels hold no loop over tiles, as
+// one makes the compiler keep everything that does not depend on the tile in registers.
+template <class Launch>
+hipError_t launch_tiles(int64_t vtiles, Launch launch) {
+  hipError_t e = hipSuccess;
+  for (int64_t vt0 = 0; vt0 < vtiles && e == hipSuccess; vt0 += kMaxBlocks)
+    e = launch(vt0, grid_blocks(vtiles - vt0));
+  return e;
+}
+
+}  // namespace dev
+}  // namespace dsa3d

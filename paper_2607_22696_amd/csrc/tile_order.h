@@ -28,6 +28,27 @@ namespace dsa3d {
 
 constexpr int kPencilXcds = 8;
 
+// Division of 0 <= n < 2^31 by a positive int fixed on the host, as a multiplication (the
+// round-up method of Granlund and Montgomery): the kernels' index arithmetic per tile and per
+// point is a few divisions, which the GPU has no instruction for.
+struct FastDiv {
+  uint32_t d, m, s;
+};
+
+DSA3D_TILE_FN FastDiv fast_div(int d) {
+  FastDiv f;
+  f.d = (uint32_t)d;
+  f.s = 0;
+  while (f.s < 31 && (1u << f.s) < f.d) ++f.s;
+  f.m = (uint32_t)((((uint64_t)1 << 32) * (((uint64_t)1 << f.s) - f.d)) / f.d + 1);
+  return f;
+}
+
+DSA3D_TILE_FN int operator/(int n, const FastDiv& f) {
+  const uint32_t t = (uint32_t)(((uint64_t)(uint32_t)n * f.m) >> 32);
+  return (int)((t + (uint32_t)n) >> f.s);
+}
+
 struct PencilOrder {
   int frames, rows, cols;  // cell grid of one (batch, head) group
   int ph, pw;              // pencil size in cells
@@ -37,6 +58,7 @@ struct PencilOrder {
   int64_t pencil_tiles;    // tiles per pencil, frames * runs
   int64_t pencils;         // groups * np_r * np_c
   int64_t vtiles;          // virtual tiles: 8 * ceil(pencils / 8) * pencil_tiles
+  FastDiv by_tiles, by_group, by_cols, by_runs, by_pw;  // the divisors of pencil_tile, pencil_cell
 };
 
 DSA3D_TILE_FN PencilOrder pencils_of(int groups, int frames, int rows, int cols, int run, int nr,
@@ -54,6 +76,12 @@ DSA3D_TILE_FN PencilOrder pencils_of(int groups, int frames, int rows, int cols,
   o.pencil_tiles = (int64_t)frames * o.runs;
   o.pencils = (int64_t)groups * o.np_r * o.np_c;
   o.vtiles = (o.pencils + kPencilXcds - 1) / kPencilXcds * kPencilXcds * o.pencil_tiles;
+  // below 2^31 virtual tiles every divisor fits (the kernels divide in 64 bits above)
+  o.by_tiles = fast_div(o.vtiles < ((int64_t)1 << 31) ? (int)o.pencil_tiles : 1);
+  o.by_group = fast_div(o.np_r * o.np_c);
+  o.by_cols = fast_div(o.np_c);
+  o.by_runs = fast_div(o.runs);
+  o.by_pw = fast_div(o.pw);
   return o;
 }
 
@@ -95,17 +123,27 @@ struct PencilTile {
 
 // Tile of virtual tile v; false for a tile past the last pencil (the XCD has no pencil left).
 DSA3D_TILE_FN bool pencil_tile(const PencilOrder& o, int64_t v, PencilTile& t) {
-  const int64_t xcd = v % kPencilXcds, slot = v / kPencilXcds;
-  const int64_t g = slot / o.pencil_tiles * kPencilXcds + xcd;
+  const int xcd = (int)(v % kPencilXcds);
+  const int64_t slot = v / kPencilXcds;
+  int64_t g, k;
+  if (o.vtiles < ((int64_t)1 << 31)) {
+    const int p = (int)slot / o.by_tiles;
+    g = (int64_t)p * kPencilXcds + xcd;
+    k = (int)slot - p * (int)o.pencil_tiles;
+  } else {
+    g = slot / o.pencil_tiles * kPencilXcds + xcd;
+    k = slot % o.pencil_tiles;
+  }
   if (g >= o.pencils) return false;
-  const int64_t k = slot % o.pencil_tiles;
   const int per_group = o.np_r * o.np_c;
-  t.group = (int)(g / per_group);
-  const int p = (int)(g % per_group);
-  t.pr = p / o.np_c;
-  t.pc = p % o.np_c;
-  t.frame = (int)(k / o.runs);
-  t.u0 = (int)(k % o.runs) * o.run;
+  // a pencil holds at least one tile, so below 2^31 tiles its number fits too; a huge order has
+  // at most 2^31 pencils all the same (one per cell of a grid of fewer than 2^31 rows)
+  t.group = (int)g / o.by_group;
+  const int p = (int)g - t.group * per_group;
+  t.pr = p / o.by_cols;
+  t.pc = p - t.pr * o.np_c;
+  t.frame = o.vtiles < ((int64_t)1 << 31) ? (int)k / o.by_runs : (int)(k / o.runs);
+  t.u0 = (int)(k - (int64_t)t.frame * o.runs) * o.run;
   return true;
 }
 
@@ -114,7 +152,7 @@ DSA3D_TILE_FN bool pencil_tile(const PencilOrder& o, int64_t v, PencilTile& t) {
 DSA3D_TILE_FN bool pencil_cell(const PencilOrder& o, const PencilTile& t, int e, int& row,
                                int& col) {
   const int u = t.u0 + e;
-  const int y = u / o.pw, x = u - y * o.pw;
+  const int y = u / o.by_pw, x = u - y * o.pw;
   row = t.pr * o.ph + y;
   col = t.pc * o.pw + x;
   return u < o.ph * o.pw && row < o.rows && col < o.cols;
