@@ -28,6 +28,11 @@
 //     sums as matrix products (weights x q / dout rows) on the matrix cores; fp32: one
 //     L-lane group per 2 x 2 block of a frame, w_c * coefficient * q and * dout accumulated
 //     in registers.
+// Where rows are large enough (backward_rounds), a tile whose points lie close together leaves the
+// V corners to phase 3: phase 1 only counts its points, and phase 3 reads each distinct voxel of
+// four neighbouring queries once per sweep (bwd_slots_tile, dsa3d_slots.h): dots of the V rows with
+// dout, of the K rows with q, and the sum of K rows for dq with Delta known.  V and K pass at
+// 16x34x60, 24 heads x 128, 3x7x7, offsets N(0, 1): 23.0 -> 17.5 ms.
 // The predicted-weights variant reads no K: one sweep (phase 1 with the given logits, the
 // bin counts' ranks not kept) and a finalize of one thread per point that claims its slot
 // from a fill cursor take phases 1 and 3.
@@ -118,7 +123,7 @@ __global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_sweep_k
     int i, j;
     // All lanes of a group share the token: a whole group is idle or active, so neither the
     // group reductions nor the point sharing ever mix an idle group into an active one.
-    if (!query_token<D, BF16>(po, g, tl, wave * LY::kGroups + grp, i, j)) continue;
+    if (!query_token<false>(po, g, tl, wave * LY::kGroups + grp, i, j)) continue;
     const int n = t * HW + i * g.W + j;
     const int64_t row = ((int64_t)b * g.N + n) * g.heads + m;
 
@@ -355,11 +360,11 @@ __device__ inline __attribute__((always_inline)) void fetch_point(const Point& m
 
 // V pass: per point da_p = <dout, v_p> and B_p = sum_c dw_c/dpos <dout, V_c> into the V half
 // of the record; every point is counted into the bin of its cell.
-template <int D, bool BF16>
-__global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_vpass_kernel(
-    Geometry g, const void* __restrict__ v, const float* __restrict__ offsets,
-    const void* __restrict__ dout, RecV* __restrict__ recv, uint32_t* __restrict__ counts,
-    uint32_t* __restrict__ ranks, PencilOrder po) {
+template <int D, bool BF16, bool SLOTS>
+__device__ inline __attribute__((always_inline)) void vpass_tile(
+    const Geometry& g, const PencilOrder& po, const PencilTile& tl, const void* __restrict__ v,
+    const float* __restrict__ offsets, const void* __restrict__ dout, RecV* __restrict__ recv,
+    uint32_t* __restrict__ counts, uint32_t* __restrict__ ranks, int4* pts) {
   using LY = Layout<D, BF16>;
   constexpr int L = LY::kLanes;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -377,117 +382,170 @@ __global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_vpass_k
   // fetch indices and fractions with ds_bpermute and rebuild the rest, which measured faster
   // there (2.98 against 3.10 ms at 64x34x60; 88.7 against 87.2 ms at 64x68x120, head_dim 128).
   constexpr bool kSlots = L >= 16;
-  __shared__ int4 pts[kSlots ? slot_words<L, 9>() : 1];  // 8 words used, 9 for the banks
   int4* const mine_at = pts + (kSlots ? slot_of<L, 9>(threadIdx.x) : 0);
 
-  for (int64_t vt = blockIdx.x; vt < po.vtiles; vt += gridDim.x) {
-    PencilTile tl;
-    if (!pencil_tile(po, vt, tl)) continue;
-    const int bh = tl.group;
-    const int b = bh / g.heads, m = bh % g.heads;
-    const int t = tl.frame;
-    const RowWindow win = make_window<LY::kRowBytes>(g, v, v, b, m, t);  // V rows only
-    int i, j;
-    if (!query_token<D, BF16>(po, g, tl, wave * LY::kGroups + grp, i, j)) continue;  // a whole group idles
-    const int n = t * HW + i * g.W + j;
-    const int64_t row = ((int64_t)b * g.N + n) * g.heads + m;
-    const uint4 gr = load16(gb, row * LY::kRowBytes + lane_off);
-    const float* off = offsets + row * g.P * 3;
-    int pm = min(sub, g.P - 1);  // this lane's point of the chunk (clamped in the last one)
-    float ox = off[3 * pm], oy = off[3 * pm + 1], oz = off[3 * pm + 2];
-    for (int p0 = 0; p0 < g.P; p0 += L) {
-      const int it = pm / khw, ih = (pm - it * khw) / g.kw, iw = pm - it * khw - ih * g.kw;
-      Point mine;
-      make_point(g, win, t, i, j, it - rt, ih - rh, iw - rw, ox, oy, oz, mine);
-      if constexpr (kSlots) {
-        const float* ax = mine.ax;
-        const float* ay = mine.ay;
-        const float* az = mine.az;
-        mine_at[0] = make_int4(mine.vidx[0], mine.vidx[1], mine.vidx[2], mine.vidx[3]);
-        mine_at[1] = make_int4(mine.vidx[4], mine.vidx[5], mine.vidx[6], mine.vidx[7]);
-        mine_at[2] = make_int4(__float_as_int(mine.w[0]), __float_as_int(mine.w[1]),
-                               __float_as_int(mine.w[2]), __float_as_int(mine.w[3]));
-        mine_at[3] = make_int4(__float_as_int(mine.w[4]), __float_as_int(mine.w[5]),
-                               __float_as_int(mine.w[6]), __float_as_int(mine.w[7]));
-        mine_at[4] = make_int4(__float_as_int(ay[0] * az[0]), __float_as_int(ay[1] * az[0]),
-                               __float_as_int(ay[0] * az[1]), __float_as_int(ay[1] * az[1]));
-        mine_at[5] = make_int4(__float_as_int(ax[0] * az[0]), __float_as_int(ax[1] * az[0]),
-                               __float_as_int(ax[0] * az[1]), __float_as_int(ax[1] * az[1]));
-        mine_at[6] = make_int4(__float_as_int(ax[0] * ay[0]), __float_as_int(ax[1] * ay[0]),
-                               __float_as_int(ax[0] * ay[1]), __float_as_int(ax[1] * ay[1]));
-        mine_at[7] = make_int4((int)mine.slow, mine.cx, mine.cy, mine.cz);
-      }
-      const bool own = p0 + sub < g.P;
-      // the point's rank in its bin: the K pass puts its entry at bin start + rank (the
-      // returning atomic's latency is covered by the chunk's corner loads)
-      uint32_t rank = 0u;
-      if (own && cell_inside(g, mine.cx, mine.cy, mine.cz))
-        rank = __hip_atomic_fetch_add(counts + cell_index(g, bh, mine.cx, mine.cy, mine.cz), 1u,
-                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      pm = min(p0 + L + sub, g.P - 1);  // next chunk's offsets, in flight during this one
-      ox = off[3 * pm];
-      oy = off[3 * pm + 1];
-      oz = off[3 * pm + 2];
-      const int nk = min(L, g.P - p0);
-      float4 rec = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      for (int kk = 0; kk < nk; ++kk) {
-        uint4 vr[8];
-        float w[8], gx[4], gy[4], gz[4];
-        if constexpr (!kSlots) {
-          const int src = (grp * L + kk) << 2;
-          Point pt;
-          fetch_point(mine, src, pt);
-          load_shared_corners<LY::kRowBytes, false>(g, win, vb, vb, b, m, lane_off, mine, src,
-                                                    pt.vidx, nullptr, vr);
+  const int bh = tl.group;
+  const int b = bh / g.by_heads, m = bh - b * g.heads;
+  const int t = tl.frame;
+  const RowWindow win = make_window<LY::kRowBytes>(g, v, v, b, m, t);  // V rows only
+  int i, j;
+  if (!query_token<SLOTS>(po, g, tl, wave * LY::kGroups + grp, i, j)) return;  // a whole group idles
+  const int n = t * HW + i * g.W + j;
+  const int64_t row = ((int64_t)b * g.N + n) * g.heads + m;
+  const uint4 gr = load16(gb, row * LY::kRowBytes + lane_off);
+  const float* off = offsets + row * g.P * 3;
+  int pm = min(sub, g.P - 1);  // this lane's point of the chunk (clamped in the last one)
+  float ox = off[3 * pm], oy = off[3 * pm + 1], oz = off[3 * pm + 2];
+  for (int p0 = 0; p0 < g.P; p0 += L) {
+    const int it = pm / g.by_khw, rp = pm - it * khw, ih = rp / g.by_kw, iw = rp - ih * g.kw;
+    Point mine;
+    make_point(g, win, t, i, j, it - rt, ih - rh, iw - rw, ox, oy, oz, mine);
+    if constexpr (kSlots) {
+      const float* ax = mine.ax;
+      const float* ay = mine.ay;
+      const float* az = mine.az;
+      mine_at[0] = make_int4(mine.vidx[0], mine.vidx[1], mine.vidx[2], mine.vidx[3]);
+      mine_at[1] = make_int4(mine.vidx[4], mine.vidx[5], mine.vidx[6], mine.vidx[7]);
+      mine_at[2] = make_int4(__float_as_int(mine.w[0]), __float_as_int(mine.w[1]),
+                             __float_as_int(mine.w[2]), __float_as_int(mine.w[3]));
+      mine_at[3] = make_int4(__float_as_int(mine.w[4]), __float_as_int(mine.w[5]),
+                             __float_as_int(mine.w[6]), __float_as_int(mine.w[7]));
+      mine_at[4] = make_int4(__float_as_int(ay[0] * az[0]), __float_as_int(ay[1] * az[0]),
+                             __float_as_int(ay[0] * az[1]), __float_as_int(ay[1] * az[1]));
+      mine_at[5] = make_int4(__float_as_int(ax[0] * az[0]), __float_as_int(ax[1] * az[0]),
+                             __float_as_int(ax[0] * az[1]), __float_as_int(ax[1] * az[1]));
+      mine_at[6] = make_int4(__float_as_int(ax[0] * ay[0]), __float_as_int(ax[1] * ay[0]),
+                             __float_as_int(ax[0] * ay[1]), __float_as_int(ax[1] * ay[1]));
+      mine_at[7] = make_int4((int)mine.slow, mine.cx, mine.cy, mine.cz);
+    }
+    const bool own = p0 + sub < g.P;
+    // the point's rank in its bin: the K pass puts its entry at bin start + rank (the
+    // returning atomic's latency is covered by the chunk's corner loads)
+    uint32_t rank = 0u;
+    if (own && cell_inside(g, mine.cx, mine.cy, mine.cz))
+      rank = __hip_atomic_fetch_add(counts + cell_index(g, bh, mine.cx, mine.cy, mine.cz), 1u,
+                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    pm = min(p0 + L + sub, g.P - 1);  // next chunk's offsets, in flight during this one
+    ox = off[3 * pm];
+    oy = off[3 * pm + 1];
+    oz = off[3 * pm + 2];
+    const int nk = min(L, g.P - p0);
+    float4 rec = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int kk = 0; kk < nk; ++kk) {
+      uint4 vr[8];
+      float w[8], gx[4], gy[4], gz[4];
+      if constexpr (!kSlots) {
+        const int src = (grp * L + kk) << 2;
+        Point pt;
+        fetch_point(mine, src, pt);
+        load_shared_corners<LY::kRowBytes, false>(g, win, vb, vb, b, m, lane_off, mine, src,
+                                                  pt.vidx, nullptr, vr);
 #pragma unroll
-          for (int c = 0; c < 8; ++c) w[c] = pt.w[c];
+        for (int c = 0; c < 8; ++c) w[c] = pt.w[c];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            gx[e] = pt.ay[e & 1] * pt.az[e >> 1];
-            gy[e] = pt.ax[e & 1] * pt.az[e >> 1];
-            gz[e] = pt.ax[e & 1] * pt.ay[e >> 1];
-          }
-        } else {
-          const int4* at = pts + slot_of<L, 9>(wave * 64 + grp * L) + kk * 9;
-          int vidx[8];
-          const int4 i0 = at[0], i1 = at[1];
-          vidx[0] = i0.x; vidx[1] = i0.y; vidx[2] = i0.z; vidx[3] = i0.w;
-          vidx[4] = i1.x; vidx[5] = i1.y; vidx[6] = i1.z; vidx[7] = i1.w;
-          load_stashed_corners<LY::kRowBytes, false>(g, win, vb, vb, b, m, lane_off, at + 7,
-                                                     vidx, nullptr, vr);
-          const int4 w0 = at[2], w1 = at[3], x4 = at[4], y4 = at[5], z4 = at[6];
-          w[0] = __int_as_float(w0.x); w[1] = __int_as_float(w0.y);
-          w[2] = __int_as_float(w0.z); w[3] = __int_as_float(w0.w);
-          w[4] = __int_as_float(w1.x); w[5] = __int_as_float(w1.y);
-          w[6] = __int_as_float(w1.z); w[7] = __int_as_float(w1.w);
-          gx[0] = __int_as_float(x4.x); gx[1] = __int_as_float(x4.y);
-          gx[2] = __int_as_float(x4.z); gx[3] = __int_as_float(x4.w);
-          gy[0] = __int_as_float(y4.x); gy[1] = __int_as_float(y4.y);
-          gy[2] = __int_as_float(y4.z); gy[3] = __int_as_float(y4.w);
-          gz[0] = __int_as_float(z4.x); gz[1] = __int_as_float(z4.y);
-          gz[2] = __int_as_float(z4.z); gz[3] = __int_as_float(z4.w);
+        for (int e = 0; e < 4; ++e) {
+          gx[e] = pt.ay[e & 1] * pt.az[e >> 1];
+          gy[e] = pt.ax[e & 1] * pt.az[e >> 1];
+          gz[e] = pt.ax[e & 1] * pt.ay[e >> 1];
         }
-        float dap = 0.0f, b3[3] = {0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          const int cx = c & 1, cy = (c >> 1) & 1, cz = c >> 2;
-          const float dvv = chunk_dot<BF16>(gr, vr[c]);
-          dap = fmaf(w[c], dvv, dap);
-          b3[0] = fmaf(cx ? gx[c >> 1] : -gx[c >> 1], dvv, b3[0]);
-          b3[1] = fmaf(cy ? gy[cx + 2 * cz] : -gy[cx + 2 * cz], dvv, b3[1]);
-          b3[2] = fmaf(cz ? gz[c & 3] : -gz[c & 3], dvv, b3[2]);
-        }
-        const float da = group_sum<L>(dap);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) b3[a] = group_sum<L>(b3[a]);
-        if (sub == kk) rec = make_float4(da, b3[0], b3[1], b3[2]);
+      } else {
+        const int4* at = pts + slot_of<L, 9>(wave * 64 + grp * L) + kk * 9;
+        int vidx[8];
+        const int4 i0 = at[0], i1 = at[1];
+        vidx[0] = i0.x; vidx[1] = i0.y; vidx[2] = i0.z; vidx[3] = i0.w;
+        vidx[4] = i1.x; vidx[5] = i1.y; vidx[6] = i1.z; vidx[7] = i1.w;
+        load_stashed_corners<LY::kRowBytes, false>(g, win, vb, vb, b, m, lane_off, at + 7,
+                                                   vidx, nullptr, vr);
+        const int4 w0 = at[2], w1 = at[3], x4 = at[4], y4 = at[5], z4 = at[6];
+        w[0] = __int_as_float(w0.x); w[1] = __int_as_float(w0.y);
+        w[2] = __int_as_float(w0.z); w[3] = __int_as_float(w0.w);
+        w[4] = __int_as_float(w1.x); w[5] = __int_as_float(w1.y);
+        w[6] = __int_as_float(w1.z); w[7] = __int_as_float(w1.w);
+        gx[0] = __int_as_float(x4.x); gx[1] = __int_as_float(x4.y);
+        gx[2] = __int_as_float(x4.z); gx[3] = __int_as_float(x4.w);
+        gy[0] = __int_as_float(y4.x); gy[1] = __int_as_float(y4.y);
+        gy[2] = __int_as_float(y4.z); gy[3] = __int_as_float(y4.w);
+        gz[0] = __int_as_float(z4.x); gz[1] = __int_as_float(z4.y);
+        gz[2] = __int_as_float(z4.z); gz[3] = __int_as_float(z4.w);
       }
-      if (own) {
-        *reinterpret_cast<float4*>(recv + row * g.P + p0 + sub) = rec;
-        ranks[row * g.P + p0 + sub] = rank;
+      float dap = 0.0f, b3[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const int cx = c & 1, cy = (c >> 1) & 1, cz = c >> 2;
+        const float dvv = chunk_dot<BF16>(gr, vr[c]);
+        dap = fmaf(w[c], dvv, dap);
+        b3[0] = fmaf(cx ? gx[c >> 1] : -gx[c >> 1], dvv, b3[0]);
+        b3[1] = fmaf(cy ? gy[cx + 2 * cz] : -gy[cx + 2 * cz], dvv, b3[1]);
+        b3[2] = fmaf(cz ? gz[c & 3] : -gz[c & 3], dvv, b3[2]);
       }
+      const float da = group_sum<L>(dap);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) b3[a] = group_sum<L>(b3[a]);
+      if (sub == kk) rec = make_float4(da, b3[0], b3[1], b3[2]);
+    }
+    if (own) {
+      *reinterpret_cast<float4*>(recv + row * g.P + p0 + sub) = rec;
+      ranks[row * g.P + p0 + sub] = rank;
     }
   }
+}
+
+constexpr int kCountPoints = 4;
+
+// The counting alone, for the tiles whose points the slots will take: 16 lanes per token.
+__device__ inline __attribute__((always_inline)) void count_tile(
+    const Geometry& g, const PencilOrder& po, const PencilTile& tl,
+    const float* __restrict__ offsets, uint32_t* __restrict__ counts,
+    uint32_t* __restrict__ ranks) {
+  const int bh = tl.group, b = bh / g.by_heads, m = bh - b * g.heads;
+  const int lp = threadIdx.x % kSlotLanes;
+  for (int e = threadIdx.x / kSlotLanes; e < po.run * kSlotQueries;
+       e += kBlockThreads / kSlotLanes) {
+    int i, j;
+    if (!slot_token(po, g, tl, e, i, j)) continue;
+    const int64_t row = ((int64_t)b * g.N + ((tl.frame * g.H + i) * g.W + j)) * g.heads + m;
+    const float* off = offsets + row * g.P * 3;
+    // several points per lane at a time: their offsets, then their counts, are in flight together
+    for (int p0 = lp; p0 < g.P; p0 += kCountPoints * kSlotLanes) {
+      SlotPoint pt[kCountPoints];
+      uint32_t rank[kCountPoints];
+#pragma unroll
+      for (int u = 0; u < kCountPoints; ++u) {
+        const int p = min(p0 + u * kSlotLanes, g.P - 1);
+        pt[u].set(g, tl.frame, i, j, p, off + 3 * p);
+      }
+#pragma unroll
+      for (int u = 0; u < kCountPoints; ++u) {
+        rank[u] = 0u;
+        if (p0 + u * kSlotLanes < g.P && cell_inside(g, pt[u].x, pt[u].y, pt[u].z))
+          rank[u] = __hip_atomic_fetch_add(
+              counts + cell_index(g, bh, pt[u].x, pt[u].y, pt[u].z), 1u, __ATOMIC_RELAXED,
+              __HIP_MEMORY_SCOPE_AGENT);
+      }
+#pragma unroll
+      for (int u = 0; u < kCountPoints; ++u)
+        if (p0 + u * kSlotLanes < g.P) ranks[row * g.P + p0 + u * kSlotLanes] = rank[u];
+    }
+  }
+}
+
+// SLOTS: compact tiles are only counted here.
+template <int D, bool BF16, bool SLOTS>
+__global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_vpass_kernel(
+    Geometry g, const void* __restrict__ v, const float* __restrict__ offsets,
+    const void* __restrict__ dout, RecV* __restrict__ recv, uint32_t* __restrict__ counts,
+    uint32_t* __restrict__ ranks, PencilOrder po, int64_t vt0) {
+  constexpr int L = Layout<D, BF16>::kLanes;
+  __shared__ int4 pts[L >= 16 ? slot_words<L, 9>() : 1];  // 8 words used, 9 for the banks
+  PencilTile tl;
+  if (!pencil_tile(po, vt0 + blockIdx.x, tl)) return;
+  if constexpr (SLOTS) {
+    if (compact_tile(g, po, tl, offsets, kBackwardBox)) {
+      count_tile(g, po, tl, offsets, counts, ranks);
+      return;
+    }
+  }
+  vpass_tile<D, BF16, SLOTS>(g, po, tl, v, offsets, dout, recv, counts, ranks, pts);
 }
 
 // K pass: alpha_p from the logit and the forward's LSE, A_p = sum_c dw_c/dpos <q, K_c> (the
@@ -497,17 +555,13 @@ __global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_vpass_k
 // points in registers until the row's end; HOLD == 0: it writes them to the records and reads
 // them back.  Holding them measured 131.4 -> 127.0 ms at 64x68x120 (3x5x5, head_dim 128) and
 // 4.76 -> 4.37 ms at 64x34x60 (3x3x3, head_dim 64).
-template <int D, bool BF16, int HOLD>
-// Four waves per SIMD at head_dim 128 with bf16 (128 registers, 40 bytes spilled outside the
-// point loop): 133.2 -> 131.5 ms at 64x68x120 (3x5x5), 240.0 -> 236.0 ms (3x7x7); at head_dim
-// 64 the same hint cost 4% (4.81 -> 5.00 ms at 64x34x60), so three stay there.
-__global__ __launch_bounds__(kBlockThreads) __attribute__((
-    amdgpu_waves_per_eu((D) <= 64 ? 3 : (BF16 ? 4 : 1)))) void bwd_kpass_kernel(
-    Geometry g, const void* __restrict__ q, const void* __restrict__ k,
-    const float* __restrict__ offsets, const float* __restrict__ lse, float* __restrict__ dq,
-    RecK* __restrict__ reck, const RecV* __restrict__ recv, const uint32_t* __restrict__ starts,
-    const uint32_t* __restrict__ ranks, float* __restrict__ doff, Entry* __restrict__ entries,
-    PencilOrder po) {
+template <int D, bool BF16, int HOLD, bool SLOTS>
+__device__ inline __attribute__((always_inline)) void kpass_tile(
+    const Geometry& g, const PencilOrder& po, const PencilTile& tl, const void* __restrict__ q,
+    const void* __restrict__ k, const float* __restrict__ offsets, const float* __restrict__ lse,
+    float* __restrict__ dq, RecK* __restrict__ reck, const RecV* __restrict__ recv,
+    const uint32_t* __restrict__ starts, const uint32_t* __restrict__ ranks,
+    float* __restrict__ doff, Entry* __restrict__ entries, int4* pts) {
   using LY = Layout<D, BF16>;
   constexpr int L = LY::kLanes;
   constexpr int VEC = LY::kVec;
@@ -524,141 +578,395 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((
   // magnitudes of the weights' position derivatives (the products of two axis weights),
   // window flag and cell, and the point's da_p.  The owner forms them once instead of every
   // lane of the row rebuilding them, which the VALU-bound point loop feels.
-  __shared__ int4 pts[slot_words<L, 9>()];
   int4* const mine_at = pts + slot_of<L, 9>(threadIdx.x);
 
-  for (int64_t vt = blockIdx.x; vt < po.vtiles; vt += gridDim.x) {
-    PencilTile tl;
-    if (!pencil_tile(po, vt, tl)) continue;
-    const int bh = tl.group;
-    const int b = bh / g.heads, m = bh % g.heads;
-    const int t = tl.frame;
-    const RowWindow win = make_window<LY::kRowBytes>(g, k, k, b, m, t);  // K rows only
+  const int bh = tl.group;
+  const int b = bh / g.by_heads, m = bh - b * g.heads;
+  const int t = tl.frame;
+  const RowWindow win = make_window<LY::kRowBytes>(g, k, k, b, m, t);  // K rows only
+  int i, j;
+  if (!query_token<SLOTS>(po, g, tl, wave * LY::kGroups + grp, i, j)) return;  // a whole group idles
+  const int n = t * HW + i * g.W + j;
+  const int64_t row = ((int64_t)b * g.N + n) * g.heads + m;
+  const uint4 qr = load16(qb, row * LY::kRowBytes + lane_off);
+  const float lse2 = lse[row] * kLog2e;
+  const float* off = offsets + row * g.P * 3;
+  RecK* krow = reck + row * g.P;
+  const RecV* vrow = recv + row * g.P;
+  float ak[VEC], bk[VEC];
+#pragma unroll
+  for (int x = 0; x < VEC; ++x) {
+    ak[x] = 0.0f;
+    bk[x] = 0.0f;
+  }
+  float delta = 0.0f;
+  float4 hold[HOLD > 0 ? HOLD : 1];
+#pragma unroll
+  for (int h = 0; h < (HOLD > 0 ? HOLD : 1); ++h) hold[h] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  int pm = min(sub, g.P - 1);
+  float ox = off[3 * pm], oy = off[3 * pm + 1], oz = off[3 * pm + 2];
+  for (int p0 = 0; p0 < g.P; p0 += L) {
+    const int it = pm / g.by_khw, rp = pm - it * khw, ih = rp / g.by_kw, iw = rp - ih * g.kw;
+    {
+      Point mine;
+      make_point(g, win, t, i, j, it - rt, ih - rh, iw - rw, ox, oy, oz, mine);
+      const float my_da = vrow[pm].dalpha;  // this lane's point's da_p (V pass)
+      const float* ax = mine.ax;
+      const float* ay = mine.ay;
+      const float* az = mine.az;
+      mine_at[0] = make_int4(mine.vidx[0], mine.vidx[1], mine.vidx[2], mine.vidx[3]);
+      mine_at[1] = make_int4(mine.vidx[4], mine.vidx[5], mine.vidx[6], mine.vidx[7]);
+      mine_at[2] = make_int4(__float_as_int(mine.w[0]), __float_as_int(mine.w[1]),
+                             __float_as_int(mine.w[2]), __float_as_int(mine.w[3]));
+      mine_at[3] = make_int4(__float_as_int(mine.w[4]), __float_as_int(mine.w[5]),
+                             __float_as_int(mine.w[6]), __float_as_int(mine.w[7]));
+      // |dw_c/dx| = ay az, |dw_c/dy| = ax az, |dw_c/dz| = ax ay, by the corner's other two bits
+      mine_at[4] = make_int4(__float_as_int(ay[0] * az[0]), __float_as_int(ay[1] * az[0]),
+                             __float_as_int(ay[0] * az[1]), __float_as_int(ay[1] * az[1]));
+      mine_at[5] = make_int4(__float_as_int(ax[0] * az[0]), __float_as_int(ax[1] * az[0]),
+                             __float_as_int(ax[0] * az[1]), __float_as_int(ax[1] * az[1]));
+      mine_at[6] = make_int4(__float_as_int(ax[0] * ay[0]), __float_as_int(ax[1] * ay[0]),
+                             __float_as_int(ax[0] * ay[1]), __float_as_int(ax[1] * ay[1]));
+      mine_at[7] = make_int4((int)mine.slow, mine.cx, mine.cy, mine.cz);
+      mine_at[8] = make_int4(__float_as_int(my_da), 0, 0, 0);
+    }
+    const bool own = p0 + sub < g.P;
+    pm = min(p0 + L + sub, g.P - 1);
+    ox = off[3 * pm];
+    oy = off[3 * pm + 1];
+    oz = off[3 * pm + 2];
+    const int nk = min(L, g.P - p0);
+    float4 rec = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int kk = 0; kk < nk; ++kk) {
+      const int4* at = pts + slot_of<L, 9>(wave * 64 + grp * L) + kk * 9;
+      int vidx[8];
+      {
+        const int4 i0 = at[0], i1 = at[1];
+        vidx[0] = i0.x; vidx[1] = i0.y; vidx[2] = i0.z; vidx[3] = i0.w;
+        vidx[4] = i1.x; vidx[5] = i1.y; vidx[6] = i1.z; vidx[7] = i1.w;
+      }
+      uint4 kr[8];
+      load_stashed_corners<LY::kRowBytes, false>(g, win, kb, kb, b, m, lane_off, at + 7, vidx,
+                                                 nullptr, kr);
+      float w[8], gx[4], gy[4], gz[4];
+      {
+        const int4 w0 = at[2], w1 = at[3], x4 = at[4], y4 = at[5], z4 = at[6];
+        w[0] = __int_as_float(w0.x); w[1] = __int_as_float(w0.y);
+        w[2] = __int_as_float(w0.z); w[3] = __int_as_float(w0.w);
+        w[4] = __int_as_float(w1.x); w[5] = __int_as_float(w1.y);
+        w[6] = __int_as_float(w1.z); w[7] = __int_as_float(w1.w);
+        gx[0] = __int_as_float(x4.x); gx[1] = __int_as_float(x4.y);
+        gx[2] = __int_as_float(x4.z); gx[3] = __int_as_float(x4.w);
+        gy[0] = __int_as_float(y4.x); gy[1] = __int_as_float(y4.y);
+        gy[2] = __int_as_float(y4.z); gy[3] = __int_as_float(y4.w);
+        gz[0] = __int_as_float(z4.x); gz[1] = __int_as_float(z4.y);
+        gz[2] = __int_as_float(z4.z); gz[3] = __int_as_float(z4.w);
+      }
+      float sp = 0.0f, a3[3] = {0.0f, 0.0f, 0.0f};
+      float kp[VEC];
+#pragma unroll
+      for (int x = 0; x < VEC; ++x) kp[x] = 0.0f;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const int cx = c & 1, cy = (c >> 1) & 1, cz = c >> 2;
+        const float qk = chunk_dot<BF16>(qr, kr[c]);
+        sp = fmaf(w[c], qk, sp);
+        // dw_c/dpos: + for the upper corner of an axis, - for the lower
+        a3[0] = fmaf(cx ? gx[c >> 1] : -gx[c >> 1], qk, a3[0]);
+        a3[1] = fmaf(cy ? gy[cx + 2 * cz] : -gy[cx + 2 * cz], qk, a3[1]);
+        a3[2] = fmaf(cz ? gz[c & 3] : -gz[c & 3], qk, a3[2]);
+        chunk_axpy<BF16>(kp, w[c], kr[c]);
+      }
+      const float alpha = exp2f(group_sum<L>(sp) * g.scale_log2 - lse2);
+      const float da = __int_as_float(at[8].x);
+      delta = fmaf(alpha, da, delta);
+      const float ada = alpha * da;
+#pragma unroll
+      for (int x = 0; x < VEC; ++x) {
+        ak[x] = fmaf(ada, kp[x], ak[x]);
+        bk[x] = fmaf(alpha, kp[x], bk[x]);
+      }
+#pragma unroll
+      for (int a = 0; a < 3; ++a) a3[a] = group_sum<L>(a3[a]);
+      if (sub == kk) rec = make_float4(alpha, a3[0], a3[1], a3[2]);
+    }
+    if constexpr (HOLD > 0) {
+#pragma unroll
+      for (int h = HOLD - 1; h > 0; --h) hold[h] = hold[h - 1];
+      hold[0] = rec;
+    } else {
+      if (own) *reinterpret_cast<float4*>(krow + p0 + sub) = rec;
+    }
+  }
+  float* dqr = dq + row * D + sub * VEC;
+#pragma unroll
+  for (int x = 0; x < VEC; x += 4)
+    *reinterpret_cast<float4*>(dqr + x) =
+        make_float4(g.scale * fmaf(-delta, bk[x], ak[x]), g.scale * fmaf(-delta, bk[x + 1], ak[x + 1]),
+                    g.scale * fmaf(-delta, bk[x + 2], ak[x + 2]),
+                    g.scale * fmaf(-delta, bk[x + 3], ak[x + 3]));
+  // Delta is known: finish the row's points
+  finish_row<L, HOLD>(g, krow, hold, vrow, off, ranks + row * g.P, delta, bh, n, t, i, j, sub,
+                      doff + row * g.P * 3, starts, entries);
+}
+
+// d_offsets of a point and, where its cell is binned, its entry.  `slot` is its bin's start + its
+// rank, ~0 for none.
+__device__ inline __attribute__((always_inline)) void finish_point(
+    const Geometry& g, const SlotPoint& pt, const float4& rk, const float4& rv, float delta,
+    uint32_t slot, int n, float* __restrict__ d, Entry* __restrict__ entries) {
+  const float dd = rv.x - delta, sa = g.scale * dd;
+  d[0] = rk.x * fmaf(sa, rk.y, rv.y);
+  d[1] = rk.x * fmaf(sa, rk.z, rv.z);
+  d[2] = rk.x * fmaf(sa, rk.w, rv.w);
+  if (slot == 0xffffffffu) return;
+  entries[slot] = Entry{n, rk.x, g.scale * rk.x * dd, pt.fx, pt.fy, pt.fz};
+}
+
+// sum_c w_c v_c and sum_c (dw_c / dpos) v_c of a point's corner values.
+__device__ inline __attribute__((always_inline)) float4 corner_sums(const SlotPoint& pt,
+                                                                    const float (&v)[8]) {
+  const float ax[2] = {1.0f - pt.fx, pt.fx}, ay[2] = {1.0f - pt.fy, pt.fy},
+              az[2] = {1.0f - pt.fz, pt.fz};
+  float s = 0.0f, x = 0.0f, y = 0.0f, z = 0.0f;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const int cx = c & 1, cy = (c >> 1) & 1, cz = c >> 2;
+    const float yz = ay[cy] * az[cz], xz = ax[cx] * az[cz], xy = ax[cx] * ay[cy];
+    s = fmaf(ax[cx] * yz, v[c], s);
+    x = fmaf(cx ? yz : -yz, v[c], x);
+    y = fmaf(cy ? xz : -xz, v[c], y);
+    z = fmaf(cz ? xy : -xy, v[c], z);
+  }
+  return make_float4(s, x, y, z);
+}
+
+// Both passes over a compact tile at once (dsa3d_slots.h): the dot products of the slots' V rows
+// with dout and of their K rows with q, per point da_p, B_p, alpha_p and A_p, Delta, and then,
+// with ds_p known, dq as the slots' weighted sum of K rows.  A row whose points are numbered
+// together keeps their values in registers (R <= 2) or finds them where it left them in the
+// records; a row of several chunks goes through the chunks again for dq.
+template <int D, bool BF16, int R, bool WHOLE>
+__device__ inline __attribute__((always_inline)) void bwd_slots_tile(
+    const Geometry& g, const PencilOrder& po, const PencilTile& tl, const void* __restrict__ q,
+    const void* __restrict__ k, const void* __restrict__ v, const float* __restrict__ offsets,
+    const float* __restrict__ lse, const void* __restrict__ dout, float* __restrict__ dq,
+    RecK* __restrict__ reck, RecV* __restrict__ recv, const uint32_t* __restrict__ starts,
+    const uint32_t* __restrict__ ranks, float* __restrict__ doff, Entry* __restrict__ entries,
+    SlotLds& lds) {
+  using LY = Layout<D, BF16>;
+  using U = SlotSum<D, BF16>;
+  constexpr int L = kSlotLanes;
+  const int lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int qi = lane / L, lp = lane % L;
+  float* const val = lds.val[qi];
+  const int HW = g.H * g.W;
+  const int bh = tl.group, b = bh / g.by_heads, m = bh - b * g.heads, t = tl.frame;
+  const SlotWindow win = slot_window<LY::kRowBytes>(g, b, m, t);
+
+  for (int e0 = kSlotQueries * wave; e0 < po.run * kSlotQueries;
+       e0 += kWavesPerBlock * kSlotQueries) {
     int i, j;
-    if (!query_token<D, BF16>(po, g, tl, wave * LY::kGroups + grp, i, j)) continue;  // a whole group idles
+    const bool active = slot_token(po, g, tl, e0 + qi, i, j);
+    if (__builtin_amdgcn_ballot_w64(active) == 0) continue;
+    j = min(j, g.W - 1);  // an idle query computes on a valid token and stores nothing
     const int n = t * HW + i * g.W + j;
     const int64_t row = ((int64_t)b * g.N + n) * g.heads + m;
-    const uint4 qr = load16(qb, row * LY::kRowBytes + lane_off);
-    const float lse2 = lse[row] * kLog2e;
     const float* off = offsets + row * g.P * 3;
-    RecK* krow = reck + row * g.P;
-    const RecV* vrow = recv + row * g.P;
-    float ak[VEC], bk[VEC];
+    float4* const krow = reinterpret_cast<float4*>(reck + row * g.P);
+    float4* const vrow = reinterpret_cast<float4*>(recv + row * g.P);
+    const uint32_t* rrow = ranks + row * g.P;
+    float* drow = doff + row * g.P * 3;
+    const float lse2 = lse[row] * kLog2e;
+    int64_t qrow[kSlotQueries];
 #pragma unroll
-    for (int x = 0; x < VEC; ++x) {
-      ak[x] = 0.0f;
-      bk[x] = 0.0f;
-    }
+    for (int w = 0; w < kSlotQueries; ++w)
+      qrow[w] = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(row >> 32), w * L)
+                           << 32) |
+                          (uint32_t)__builtin_amdgcn_readlane((int)row, w * L));
     float delta = 0.0f;
-    float4 hold[HOLD > 0 ? HOLD : 1];
+    float sum[U::kVec];
 #pragma unroll
-    for (int h = 0; h < (HOLD > 0 ? HOLD : 1); ++h) hold[h] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    int pm = min(sub, g.P - 1);
-    float ox = off[3 * pm], oy = off[3 * pm + 1], oz = off[3 * pm + 2];
-    for (int p0 = 0; p0 < g.P; p0 += L) {
-      const int it = pm / khw, ih = (pm - it * khw) / g.kw, iw = pm - it * khw - ih * g.kw;
-      {
-        Point mine;
-        make_point(g, win, t, i, j, it - rt, ih - rh, iw - rw, ox, oy, oz, mine);
-        const float my_da = vrow[pm].dalpha;  // this lane's point's da_p (V pass)
-        const float* ax = mine.ax;
-        const float* ay = mine.ay;
-        const float* az = mine.az;
-        mine_at[0] = make_int4(mine.vidx[0], mine.vidx[1], mine.vidx[2], mine.vidx[3]);
-        mine_at[1] = make_int4(mine.vidx[4], mine.vidx[5], mine.vidx[6], mine.vidx[7]);
-        mine_at[2] = make_int4(__float_as_int(mine.w[0]), __float_as_int(mine.w[1]),
-                               __float_as_int(mine.w[2]), __float_as_int(mine.w[3]));
-        mine_at[3] = make_int4(__float_as_int(mine.w[4]), __float_as_int(mine.w[5]),
-                               __float_as_int(mine.w[6]), __float_as_int(mine.w[7]));
-        // |dw_c/dx| = ay az, |dw_c/dy| = ax az, |dw_c/dz| = ax ay, by the corner's other two bits
-        mine_at[4] = make_int4(__float_as_int(ay[0] * az[0]), __float_as_int(ay[1] * az[0]),
-                               __float_as_int(ay[0] * az[1]), __float_as_int(ay[1] * az[1]));
-        mine_at[5] = make_int4(__float_as_int(ax[0] * az[0]), __float_as_int(ax[1] * az[0]),
-                               __float_as_int(ax[0] * az[1]), __float_as_int(ax[1] * az[1]));
-        mine_at[6] = make_int4(__float_as_int(ax[0] * ay[0]), __float_as_int(ax[1] * ay[0]),
-                               __float_as_int(ax[0] * ay[1]), __float_as_int(ax[1] * ay[1]));
-        mine_at[7] = make_int4((int)mine.slow, mine.cx, mine.cy, mine.cz);
-        mine_at[8] = make_int4(__float_as_int(my_da), 0, 0, 0);
+    for (int x = 0; x < U::kVec; ++x) sum[x] = 0.0f;
+    bool again = false;  // the second time through the chunks
+
+    for (int c0 = 0;;) {
+      const int left = g.P - c0, chunks = (left + R * L - 1) / (R * L);
+      int npts = (left + chunks - 1) / chunks;
+      SlotPoint pt[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (r * L >= npts) break;
+        const int p = c0 + min(r * L + lp, npts - 1);
+        pt[r].set(g, t, i, j, p, off + 3 * p);
       }
-      const bool own = p0 + sub < g.P;
-      pm = min(p0 + L + sub, g.P - 1);
-      ox = off[3 * pm];
-      oy = off[3 * pm + 1];
-      oz = off[3 * pm + 2];
-      const int nk = min(L, g.P - p0);
-      float4 rec = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      for (int kk = 0; kk < nk; ++kk) {
-        const int4* at = pts + slot_of<L, 9>(wave * 64 + grp * L) + kk * 9;
-        int vidx[8];
-        {
-          const int4 i0 = at[0], i1 = at[1];
-          vidx[0] = i0.x; vidx[1] = i0.y; vidx[2] = i0.z; vidx[3] = i0.w;
-          vidx[4] = i1.x; vidx[5] = i1.y; vidx[6] = i1.z; vidx[7] = i1.w;
-        }
-        uint4 kr[8];
-        load_stashed_corners<LY::kRowBytes, false>(g, win, kb, kb, b, m, lane_off, at + 7, vidx,
-                                                   nullptr, kr);
-        float w[8], gx[4], gy[4], gz[4];
-        {
-          const int4 w0 = at[2], w1 = at[3], x4 = at[4], y4 = at[5], z4 = at[6];
-          w[0] = __int_as_float(w0.x); w[1] = __int_as_float(w0.y);
-          w[2] = __int_as_float(w0.z); w[3] = __int_as_float(w0.w);
-          w[4] = __int_as_float(w1.x); w[5] = __int_as_float(w1.y);
-          w[6] = __int_as_float(w1.z); w[7] = __int_as_float(w1.w);
-          gx[0] = __int_as_float(x4.x); gx[1] = __int_as_float(x4.y);
-          gx[2] = __int_as_float(x4.z); gx[3] = __int_as_float(x4.w);
-          gy[0] = __int_as_float(y4.x); gy[1] = __int_as_float(y4.y);
-          gy[2] = __int_as_float(y4.z); gy[3] = __int_as_float(y4.w);
-          gz[0] = __int_as_float(z4.x); gz[1] = __int_as_float(z4.y);
-          gz[2] = __int_as_float(z4.z); gz[3] = __int_as_float(z4.w);
-        }
-        float sp = 0.0f, a3[3] = {0.0f, 0.0f, 0.0f};
-        float kp[VEC];
+      bool global;
+      int ns;
+      npts = number_slots<R, WHOLE>(g, win, (uint32_t)g.heads * LY::kRowBytes, lds, pt, npts, ns,
+                                    global);
+      const bool single = npts == g.P;
+      constexpr bool kKeep = R <= 2;
+      float4 rk[kKeep ? R : 1], rv[kKeep ? R : 1];
+      if (!again) {
+        SlotVecs<D, BF16> vec;
+        vec.load(static_cast<const char*>(dout), qrow);
+        row_dots<D, BF16>(slot_rows<LY::kRowBytes>(g, v, win, b, m, global), lds, vec, ns);
 #pragma unroll
-        for (int x = 0; x < VEC; ++x) kp[x] = 0.0f;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          const int cx = c & 1, cy = (c >> 1) & 1, cz = c >> 2;
-          const float qk = chunk_dot<BF16>(qr, kr[c]);
-          sp = fmaf(w[c], qk, sp);
-          // dw_c/dpos: + for the upper corner of an axis, - for the lower
-          a3[0] = fmaf(cx ? gx[c >> 1] : -gx[c >> 1], qk, a3[0]);
-          a3[1] = fmaf(cy ? gy[cx + 2 * cz] : -gy[cx + 2 * cz], qk, a3[1]);
-          a3[2] = fmaf(cz ? gz[c & 3] : -gz[c & 3], qk, a3[2]);
-          chunk_axpy<BF16>(kp, w[c], kr[c]);
+        for (int r = 0; r < R; ++r) {
+          if (r * L >= npts) break;
+          float d[8];
+          pt[r].read(val, d);
+          const float4 y = corner_sums(pt[r], d);
+          if constexpr (kKeep) rv[r] = y;
+          if ((!kKeep || !single) && active && r * L + lp < npts) vrow[c0 + r * L + lp] = y;
         }
-        const float alpha = exp2f(group_sum<L>(sp) * g.scale_log2 - lse2);
-        const float da = __int_as_float(at[8].x);
-        delta = fmaf(alpha, da, delta);
-        const float ada = alpha * da;
+        wave_sync();
+        vec.load(static_cast<const char*>(q), qrow);
+        row_dots<D, BF16>(slot_rows<LY::kRowBytes>(g, k, win, b, m, global), lds, vec, ns);
+        float part = 0.0f;
 #pragma unroll
-        for (int x = 0; x < VEC; ++x) {
-          ak[x] = fmaf(ada, kp[x], ak[x]);
-          bk[x] = fmaf(alpha, kp[x], bk[x]);
+        for (int r = 0; r < R; ++r) {
+          if (r * L >= npts) break;
+          float d[8];
+          pt[r].read(val, d);
+          float4 y = corner_sums(pt[r], d);
+          y.x = exp2f(y.x * g.scale_log2 - lse2);
+          if constexpr (kKeep) rk[r] = y;
+          if (r * L + lp < npts) {
+            const int p = c0 + r * L + lp;
+            part = fmaf(y.x, kKeep ? rv[r].x : active ? vrow[p].x : 0.0f, part);
+            if ((!kKeep || !single) && active) krow[p] = y;
+          }
         }
-#pragma unroll
-        for (int a = 0; a < 3; ++a) a3[a] = group_sum<L>(a3[a]);
-        if (sub == kk) rec = make_float4(alpha, a3[0], a3[1], a3[2]);
+        delta += group_sum<L>(part);
       }
-      if constexpr (HOLD > 0) {
+      if (again || single) {
+        // ds_p of the chunk's points, and their magnitudes' sum for the fixed point
+        float ds[R], mag = 0.0f;
 #pragma unroll
-        for (int h = HOLD - 1; h > 0; --h) hold[h] = hold[h - 1];
-        hold[0] = rec;
-      } else {
-        if (own) *reinterpret_cast<float4*>(krow + p0 + sub) = rec;
+        for (int r = 0; r < R; ++r) {
+          ds[r] = 0.0f;
+          if (r * L >= npts) break;
+          if (active && r * L + lp < npts) {
+            const int p = c0 + r * L + lp;
+            float alpha, da;
+            if (!kKeep || again) {
+              alpha = krow[p].x;
+              da = vrow[p].x;
+            } else {
+              alpha = rk[kKeep ? r : 0].x;
+              da = rv[kKeep ? r : 0].x;
+            }
+            ds[r] = alpha * (da - delta);
+            mag += fabsf(ds[r]);
+          }
+        }
+        mag = group_sum<L>(mag);
+        const float fix = slot_scale(mag);
+        clear_coefs(lds, ns);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          if (r * L >= npts) break;
+          if (r * L + lp < npts) add_coefs(pt[r], val, ds[r] * fix);
+        }
+        if constexpr (kKeep) {
+          if (single) {  // the points are done with before the sums need the registers
+            uint32_t slot[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+              if (r * L >= npts) break;
+              const bool in = cell_inside(g, pt[r].x, pt[r].y, pt[r].z);
+              slot[r] = 0xffffffffu;
+              if (in && active && r * L + lp < npts)
+                slot[r] = starts[cell_index(g, bh, pt[r].x, pt[r].y, pt[r].z)] + rrow[r * L + lp];
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+              if (r * L >= npts) break;
+              if (active && r * L + lp < npts)
+                finish_point(g, pt[r], rk[r], rv[r], delta, slot[r], n, drow + 3 * (r * L + lp),
+                             entries);
+            }
+          }
+        }
+        float part[U::kVec];
+        row_sums<D, BF16>(slot_rows<LY::kRowBytes>(g, k, win, b, m, global), lds, ns, part);
+#pragma unroll
+        for (int x = 0; x < U::kVec; ++x) sum[x] = fmaf(part[x], mag / kSlotOne, sum[x]);
+      }
+      if (single) break;
+      c0 += npts;
+      if (c0 >= g.P) {
+        if (again) break;
+        again = true;
+        c0 = 0;
       }
     }
-    float* dqr = dq + row * D + sub * VEC;
+    if (!active) continue;
+    if (lp < U::kLanes) {
+      float* dqr = dq + row * D + lp * U::kVec;
 #pragma unroll
-    for (int x = 0; x < VEC; x += 4)
-      *reinterpret_cast<float4*>(dqr + x) =
-          make_float4(g.scale * fmaf(-delta, bk[x], ak[x]), g.scale * fmaf(-delta, bk[x + 1], ak[x + 1]),
-                      g.scale * fmaf(-delta, bk[x + 2], ak[x + 2]),
-                      g.scale * fmaf(-delta, bk[x + 3], ak[x + 3]));
-    // Delta is known: finish the row's points
-    finish_row<L, HOLD>(g, krow, hold, vrow, off, ranks + row * g.P, delta, bh, n, t, i, j, sub,
-                        doff + row * g.P * 3, starts, entries);
+      for (int x = 0; x < U::kVec; x += 4)
+        *reinterpret_cast<float4*>(dqr + x) =
+            make_float4(g.scale * sum[x], g.scale * sum[x + 1], g.scale * sum[x + 2],
+                        g.scale * sum[x + 3]);
+    }
+    if (R > 2 || again) {
+      // a lane reads the records it wrote, four points at a time for their loads' sake
+      for (int p0 = lp; p0 < g.P; p0 += 4 * L) {
+        SlotPoint pt[4];
+        float4 rk[4], rv[4];
+        uint32_t slot[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int p = min(p0 + u * L, g.P - 1);
+          rk[u] = krow[p];
+          rv[u] = vrow[p];
+          slot[u] = rrow[p];
+          pt[u].set(g, t, i, j, p, off + 3 * p);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          slot[u] = cell_inside(g, pt[u].x, pt[u].y, pt[u].z)
+                        ? starts[cell_index(g, bh, pt[u].x, pt[u].y, pt[u].z)] + slot[u]
+                        : 0xffffffffu;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (p0 + u * L < g.P)
+            finish_point(g, pt[u], rk[u], rv[u], delta, slot[u], n, drow + 3 * (p0 + u * L),
+                         entries);
+      }
+    }
   }
+}
+
+// R > 0: compact tiles take the slots, three waves per SIMD.  R = 0: every tile gathers; four
+// waves per SIMD at head_dim 128 with bf16 (133.2 -> 131.5 ms at 64x68x120, 3x5x5, U[-8, 8]).
+template <int D, bool BF16, int HOLD, int R, bool WHOLE>
+__global__ __launch_bounds__(kBlockThreads) __attribute__((
+    amdgpu_waves_per_eu(R > 0 || D <= 64 ? 3 : (BF16 ? 4 : 1)))) void bwd_kpass_kernel(
+    Geometry g, const void* __restrict__ q, const void* __restrict__ k,
+    const void* __restrict__ v, const float* __restrict__ offsets, const float* __restrict__ lse,
+    const void* __restrict__ dout, float* __restrict__ dq, RecK* __restrict__ reck,
+    RecV* __restrict__ recv, const uint32_t* __restrict__ starts,
+    const uint32_t* __restrict__ ranks, float* __restrict__ doff, Entry* __restrict__ entries,
+    PencilOrder po, int64_t vt0) {
+  constexpr size_t kPts = slot_words<Layout<D, BF16>::kLanes, 9>() * sizeof(int4);
+  constexpr size_t kSlots = R > 0 ? kWavesPerBlock * sizeof(SlotLds) : 0;
+  __shared__ __attribute__((aligned(16))) char lds[kPts > kSlots ? kPts : kSlots];
+  PencilTile tl;
+  if (!pencil_tile(po, vt0 + blockIdx.x, tl)) return;
+  if constexpr (R > 0) {
+    if (compact_tile(g, po, tl, offsets, kBackwardBox)) {
+      bwd_slots_tile<D, BF16, R, WHOLE>(
+          g, po, tl, q, k, v, offsets, lse, dout, dq, reck, recv, starts, ranks, doff, entries,
+          reinterpret_cast<SlotLds*>(lds)[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)]);
+      return;
+    }
+  }
+  kpass_tile<D, BF16, HOLD, (R > 0)>(g, po, tl, q, k, offsets, lse, dq, reck, recv, starts, ranks, doff,
+                            entries, reinterpret_cast<int4*>(lds));
 }
 
 // ---------------------------------------------------------------------------- 2. scan
@@ -890,7 +1198,7 @@ template <int D, bool BF16, bool PW>
 __global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_gather_kernel(
     Geometry g, const void* __restrict__ q, const void* __restrict__ dout,
     const uint32_t* __restrict__ starts, const Entry* __restrict__ entries, float* __restrict__ dk,
-    float* __restrict__ dv, PencilOrder po) {
+    float* __restrict__ dv, PencilOrder po, int64_t vt0) {
   using LY = Layout<D, BF16>;
   constexpr int L = LY::kLanes;
   constexpr int VEC = LY::kVec;
@@ -898,63 +1206,61 @@ __global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_gather_
   const int grp = lane / L, sub = lane % L;
   const uint32_t tok_bytes = (uint32_t)g.heads * LY::kRowBytes;  // one token's rows, all heads
 
-  for (int64_t vt = blockIdx.x; vt < po.vtiles; vt += gridDim.x) {
-    PencilTile tl;
-    if (!pencil_tile(po, vt, tl)) continue;
-    const int bh = tl.group;
-    const int b = bh / g.heads, m = bh % g.heads;
-    int by, bx;  // the group's 2 x 2 block (cell of the pencil grid)
-    if (!pencil_cell(po, tl, wave * LY::kGroups + grp, by, bx)) continue;
-    const int64_t head_off = ((int64_t)b * g.N * g.heads + m) * LY::kRowBytes + sub * 16;
-    const char* qh = static_cast<const char*>(q) + head_off;
-    const char* gh = static_cast<const char*>(dout) + head_off;
-    const int x0 = 2 * bx, y0 = 2 * by, z = tl.frame;
-    const bool hasx1 = x0 + 1 < g.W, hasy1 = y0 + 1 < g.H;
-    BlockAcc<VEC> acc;
+  PencilTile tl;
+  if (!pencil_tile(po, vt0 + blockIdx.x, tl)) return;
+  const int bh = tl.group;
+  const int b = bh / g.by_heads, m = bh - b * g.heads;
+  int by, bx;  // the group's 2 x 2 block (cell of the pencil grid)
+  if (!pencil_cell(po, tl, wave * LY::kGroups + grp, by, bx)) return;
+  const int64_t head_off = ((int64_t)b * g.N * g.heads + m) * LY::kRowBytes + sub * 16;
+  const char* qh = static_cast<const char*>(q) + head_off;
+  const char* gh = static_cast<const char*>(dout) + head_off;
+  const int x0 = 2 * bx, y0 = 2 * by, z = tl.frame;
+  const bool hasx1 = x0 + 1 < g.W, hasy1 = y0 + 1 < g.H;
+  BlockAcc<VEC> acc;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+  for (int c = 0; c < 4; ++c) {
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        acc.k[c][e] = 0.0f;
-        acc.v[c][e] = 0.0f;
-      }
+    for (int e = 0; e < VEC; ++e) {
+      acc.k[c][e] = 0.0f;
+      acc.v[c][e] = 0.0f;
     }
+  }
 #pragma unroll 1
-    for (int cz = 0; cz < 2; ++cz) {  // cell plane z - 1 + cz; voxel z is its upper corner for cz = 0
-      uint32_t r[3][4];
+  for (int cz = 0; cz < 2; ++cz) {  // cell plane z - 1 + cz; voxel z is its upper corner for cz = 0
+    uint32_t r[3][4];
 #pragma unroll
-      for (int yr = 0; yr < 3; ++yr) {
-        if (yr == 2 && !hasy1) {  // cell row y0 + 1 is outside the cell grid: nothing to gather
-          r[yr][0] = r[yr][1] = r[yr][2] = r[yr][3] = 0u;
-          continue;
-        }
-        const int64_t ci = cell_index(g, bh, x0 - 1, y0 - 1 + yr, z - 1 + cz);
-        r[yr][0] = starts[ci];
-        r[yr][1] = starts[ci + 1];
-        r[yr][2] = starts[ci + 2];
-        r[yr][3] = hasx1 ? starts[ci + 3] : r[yr][2];
+    for (int yr = 0; yr < 3; ++yr) {
+      if (yr == 2 && !hasy1) {  // cell row y0 + 1 is outside the cell grid: nothing to gather
+        r[yr][0] = r[yr][1] = r[yr][2] = r[yr][3] = 0u;
+        continue;
       }
-      const bool zlow = cz == 1;
-      gather_run<D, BF16, PW, 0>(qh, gh, tok_bytes, entries, r[0][0], r[0][1], r[0][2], r[0][3], zlow, acc);
-      gather_run<D, BF16, PW, 1>(qh, gh, tok_bytes, entries, r[1][0], r[1][1], r[1][2], r[1][3], zlow, acc);
-      gather_run<D, BF16, PW, 2>(qh, gh, tok_bytes, entries, r[2][0], r[2][1], r[2][2], r[2][3], zlow, acc);
+      const int64_t ci = cell_index(g, bh, x0 - 1, y0 - 1 + yr, z - 1 + cz);
+      r[yr][0] = starts[ci];
+      r[yr][1] = starts[ci + 1];
+      r[yr][2] = starts[ci + 2];
+      r[yr][3] = hasx1 ? starts[ci + 3] : r[yr][2];
     }
+    const bool zlow = cz == 1;
+    gather_run<D, BF16, PW, 0>(qh, gh, tok_bytes, entries, r[0][0], r[0][1], r[0][2], r[0][3], zlow, acc);
+    gather_run<D, BF16, PW, 1>(qh, gh, tok_bytes, entries, r[1][0], r[1][1], r[1][2], r[1][3], zlow, acc);
+    gather_run<D, BF16, PW, 2>(qh, gh, tok_bytes, entries, r[2][0], r[2][1], r[2][2], r[2][3], zlow, acc);
+  }
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int xi = c & 1, yi = c >> 1;
-      if ((xi == 1 && !hasx1) || (yi == 1 && !hasy1)) continue;
-      const int64_t row =
-          ((int64_t)b * g.N + (int64_t)(z * g.H + y0 + yi) * g.W + x0 + xi) * g.heads + m;
-      float* dkr = dk + row * D + sub * VEC;
-      float* dvr = dv + row * D + sub * VEC;
+  for (int c = 0; c < 4; ++c) {
+    const int xi = c & 1, yi = c >> 1;
+    if ((xi == 1 && !hasx1) || (yi == 1 && !hasy1)) continue;
+    const int64_t row =
+        ((int64_t)b * g.N + (int64_t)(z * g.H + y0 + yi) * g.W + x0 + xi) * g.heads + m;
+    float* dkr = dk + row * D + sub * VEC;
+    float* dvr = dv + row * D + sub * VEC;
 #pragma unroll
-      for (int e = 0; e < VEC; e += 4) {
-        if constexpr (!PW)
-          *reinterpret_cast<float4*>(dkr + e) =
-              make_float4(acc.k[c][e], acc.k[c][e + 1], acc.k[c][e + 2], acc.k[c][e + 3]);
-        *reinterpret_cast<float4*>(dvr + e) =
-            make_float4(acc.v[c][e], acc.v[c][e + 1], acc.v[c][e + 2], acc.v[c][e + 3]);
-      }
+    for (int e = 0; e < VEC; e += 4) {
+      if constexpr (!PW)
+        *reinterpret_cast<float4*>(dkr + e) =
+            make_float4(acc.k[c][e], acc.k[c][e + 1], acc.k[c][e + 2], acc.k[c][e + 3]);
+      *reinterpret_cast<float4*>(dvr + e) =
+          make_float4(acc.v[c][e], acc.v[c][e + 1], acc.v[c][e + 2], acc.v[c][e + 3]);
     }
   }
 }
@@ -1097,7 +1403,8 @@ template <int D, bool PW>
 __global__ __launch_bounds__(64 * gather_waves<D>()) __attribute__((amdgpu_waves_per_eu(D <= 64 ? 3 : 2)))
 void bwd_gather_mfma_kernel(Geometry g, const void* __restrict__ q, const void* __restrict__ dout,
                             const uint32_t* __restrict__ starts, const Entry* __restrict__ entries,
-                            float* __restrict__ dk, float* __restrict__ dv, PencilOrder po) {
+                            float* __restrict__ dk, float* __restrict__ dv, PencilOrder po,
+                            int64_t vt0) {
   constexpr int NW = gather_waves<D>();
   constexpr int DB = D / 16;     // 16-channel blocks: two products each (hi, lo) per tensor
   constexpr int LPR = D / 8;     // lanes per row when copying rows (16 bytes each)
@@ -1111,186 +1418,184 @@ void bwd_gather_mfma_kernel(Geometry g, const void* __restrict__ q, const void* 
   const bool upper = lane >= 32;  // dV coefficients (else dK)
   const int own = lane & 31;      // the entry whose coefficients this lane forms
 
-  for (int64_t vt = blockIdx.x; vt < po.vtiles; vt += gridDim.x) {
-    PencilTile tl;
-    if (!pencil_tile(po, vt, tl)) continue;
-    int by, bx;  // the wave's 4 x 2 x 2 block: cell (by, bx) of the pencil grid, frame pair tl.frame
-    if (!pencil_cell(po, tl, wave, by, bx)) continue;
-    const int bh = tl.group;
-    const int b = bh / g.heads, m = bh % g.heads;
-    const int x0 = 4 * bx, y0 = 2 * by, z0 = 2 * tl.frame;
-    const int nx = min(5, g.W - x0 + 1);  // cells x0 - 1 .. x0 + nx - 2 exist
-    const bool hasy1 = y0 + 1 < g.H, hasz1 = z0 + 1 < g.T;
-    const int64_t head_off = ((int64_t)b * g.N * g.heads + m) * (2 * D) + (lane % LPR) * 16;
-    const char* qh = static_cast<const char*>(q) + head_off;
-    const char* gh = static_cast<const char*>(dout) + head_off;
+  PencilTile tl;
+  if (!pencil_tile(po, vt0 + blockIdx.x, tl)) return;
+  int by, bx;  // the wave's 4 x 2 x 2 block: cell (by, bx) of the pencil grid, frame pair tl.frame
+  if (!pencil_cell(po, tl, wave, by, bx)) return;
+  const int bh = tl.group;
+  const int b = bh / g.by_heads, m = bh - b * g.heads;
+  const int x0 = 4 * bx, y0 = 2 * by, z0 = 2 * tl.frame;
+  const int nx = min(5, g.W - x0 + 1);  // cells x0 - 1 .. x0 + nx - 2 exist
+  const bool hasy1 = y0 + 1 < g.H, hasz1 = z0 + 1 < g.T;
+  const int64_t head_off = ((int64_t)b * g.N * g.heads + m) * (2 * D) + (lane % LPR) * 16;
+  const char* qh = static_cast<const char*>(q) + head_off;
+  const char* gh = static_cast<const char*>(dout) + head_off;
 
-    // the non-empty runs, in order: lane r < 9 looks at cell row y0 - 1 + r % 3, plane z0 - 1 + r / 3
-    bool has = false;
-    uint32_t c[6] = {0u, 0u, 0u, 0u, 0u, 0u};
-    if (lane < 9) {
-      const int yr = lane % 3, zr = lane / 3;
-      if ((yr < 2 || hasy1) && (zr < 2 || hasz1)) {
-        const int64_t ci = cell_index(g, bh, x0 - 1, y0 - 1 + yr, z0 - 1 + zr);
+  // the non-empty runs, in order: lane r < 9 looks at cell row y0 - 1 + r % 3, plane z0 - 1 + r / 3
+  bool has = false;
+  uint32_t c[6] = {0u, 0u, 0u, 0u, 0u, 0u};
+  if (lane < 9) {
+    const int yr = lane % 3, zr = lane / 3;
+    if ((yr < 2 || hasy1) && (zr < 2 || hasz1)) {
+      const int64_t ci = cell_index(g, bh, x0 - 1, y0 - 1 + yr, z0 - 1 + zr);
 #pragma unroll
-        for (int i = 0; i < 6; ++i) c[i] = starts[ci + min(i, nx)];
-        has = c[0] < c[5];
+      for (int i = 0; i < 6; ++i) c[i] = starts[ci + min(i, nx)];
+      has = c[0] < c[5];
+    }
+  }
+  // lane r < 9 keeps its run's bounds in c[]; the wave reads the runs in lane order with
+  // readlane, `left` marking the lanes whose runs are still ahead
+  const uint64_t hm = __builtin_amdgcn_ballot_w64(has);
+  auto next_run = [&](GatherPos& d) {
+    if (d.left != 0ull) {
+      const int lr = __builtin_amdgcn_readfirstlane(__builtin_ctzll(d.left));
+      d.left &= d.left - 1ull;
+      d.u = __builtin_amdgcn_readlane(c[0], lr);
+      d.m1 = __builtin_amdgcn_readlane(c[1], lr);
+      d.m2 = __builtin_amdgcn_readlane(c[2], lr);
+      d.m3 = __builtin_amdgcn_readlane(c[3], lr);
+      d.m4 = __builtin_amdgcn_readlane(c[4], lr);
+      d.end = __builtin_amdgcn_readlane(c[5], lr);
+      d.rc = lr;
+    } else {
+      d.u = d.end = d.m1 = d.m2 = d.m3 = d.m4 = 0u;
+      d.rc = 0;
+    }
+  };
+  auto advance = [&](GatherPos& d) {
+    d.u += kGB;
+    if (d.u >= d.end) next_run(d);
+  };
+  // this lane's part of its entry (clamped to the run; the coefficient is zeroed outside it)
+  auto fetch = [&](const GatherPos& d, GatherEntry& en) {
+    en.idx = d.u + own;
+    const char* p = reinterpret_cast<const char*>(entries + min(en.idx, d.end - 1u));
+    en.raw = *reinterpret_cast<const uint4*>(p + (upper ? 8 : 0));
+  };
+  auto weights = [&](const GatherPos& d, const GatherEntry& en) {
+    // the other half's words: lanes 0-31 get (fy, fz), lanes 32-63 get alpha
+    const auto sz = __builtin_amdgcn_permlane32_swap(en.raw.z, en.raw.z, false, false);
+    const auto sw = __builtin_amdgcn_permlane32_swap(en.raw.w, en.raw.w, false, false);
+    const auto sy = __builtin_amdgcn_permlane32_swap(en.raw.y, en.raw.y, false, false);
+    const float coef = __uint_as_float(upper ? sy[0] : en.raw.z);
+    const float fx = __uint_as_float(upper ? en.raw.y : en.raw.w);
+    const float fy = __uint_as_float(upper ? en.raw.z : sz[1]);
+    const float fz = __uint_as_float(upper ? en.raw.w : sw[1]);
+    const uint32_t i = en.idx;
+    const int rcx = -1 + (i >= d.m1 ? 1 : 0) + (i >= d.m2 ? 1 : 0) + (i >= d.m3 ? 1 : 0) +
+                    (i >= d.m4 ? 1 : 0);
+    if (PW && !upper) return;
+    uint32_t hi[8], lo[8];
+    weight_rows(i < d.end ? coef : 0.0f, fx, fy, fz, rcx, d.rc % 3 - 1, d.rc / 3 - 1, hi, lo);
+    const int sel = upper ? 0 : 2;
+    const int h0 = gather_at_half(own), h1 = 16 - h0;  // bytes of voxels 0..7 and 8..15
+    char* ah = reinterpret_cast<char*>(L.a[sel]) + gather_at_at(own);
+    char* al = reinterpret_cast<char*>(L.a[sel + 1]) + gather_at_at(own);
+    *reinterpret_cast<uint4*>(ah + h0) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    *reinterpret_cast<uint4*>(ah + h1) = make_uint4(hi[4], hi[5], hi[6], hi[7]);
+    *reinterpret_cast<uint4*>(al + h0) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+    *reinterpret_cast<uint4*>(al + h1) = make_uint4(lo[4], lo[5], lo[6], lo[7]);
+  };
+  uint4 rq[NI], rg[NI];
+  bool part = false;  // the batch ends inside: its rows past the end are zeroed in LDS
+  auto issue_rows = [&](const GatherPos& d, const GatherEntry& en) {
+    part = d.end - d.u < (uint32_t)kGB;
+#pragma unroll
+    for (int t = 0; t < NI; ++t) {
+      const int e = lane / LPR + RPI * t;
+      // entry e's token, from lane e (lanes 0-31 hold n), for the LPR lanes of its row
+      const uint32_t n = (uint32_t)__builtin_amdgcn_ds_bpermute(e << 2, (int)en.raw.x);
+      const uint64_t o = (uint64_t)n * tok_bytes;
+      if (d.u + e < d.end) {  // rows past the run's end are not loaded
+        if constexpr (!PW) rq[t] = *reinterpret_cast<const uint4*>(qh + o);
+        rg[t] = *reinterpret_cast<const uint4*>(gh + o);
       }
     }
-    // lane r < 9 keeps its run's bounds in c[]; the wave reads the runs in lane order with
-    // readlane, `left` marking the lanes whose runs are still ahead
-    const uint64_t hm = __builtin_amdgcn_ballot_w64(has);
-    auto next_run = [&](GatherPos& d) {
-      if (d.left != 0ull) {
-        const int lr = __builtin_amdgcn_readfirstlane(__builtin_ctzll(d.left));
-        d.left &= d.left - 1ull;
-        d.u = __builtin_amdgcn_readlane(c[0], lr);
-        d.m1 = __builtin_amdgcn_readlane(c[1], lr);
-        d.m2 = __builtin_amdgcn_readlane(c[2], lr);
-        d.m3 = __builtin_amdgcn_readlane(c[3], lr);
-        d.m4 = __builtin_amdgcn_readlane(c[4], lr);
-        d.end = __builtin_amdgcn_readlane(c[5], lr);
-        d.rc = lr;
-      } else {
-        d.u = d.end = d.m1 = d.m2 = d.m3 = d.m4 = 0u;
-        d.rc = 0;
-      }
-    };
-    auto advance = [&](GatherPos& d) {
-      d.u += kGB;
-      if (d.u >= d.end) next_run(d);
-    };
-    // this lane's part of its entry (clamped to the run; the coefficient is zeroed outside it)
-    auto fetch = [&](const GatherPos& d, GatherEntry& en) {
-      en.idx = d.u + own;
-      const char* p = reinterpret_cast<const char*>(entries + min(en.idx, d.end - 1u));
-      en.raw = *reinterpret_cast<const uint4*>(p + (upper ? 8 : 0));
-    };
-    auto weights = [&](const GatherPos& d, const GatherEntry& en) {
-      // the other half's words: lanes 0-31 get (fy, fz), lanes 32-63 get alpha
-      const auto sz = __builtin_amdgcn_permlane32_swap(en.raw.z, en.raw.z, false, false);
-      const auto sw = __builtin_amdgcn_permlane32_swap(en.raw.w, en.raw.w, false, false);
-      const auto sy = __builtin_amdgcn_permlane32_swap(en.raw.y, en.raw.y, false, false);
-      const float coef = __uint_as_float(upper ? sy[0] : en.raw.z);
-      const float fx = __uint_as_float(upper ? en.raw.y : en.raw.w);
-      const float fy = __uint_as_float(upper ? en.raw.z : sz[1]);
-      const float fz = __uint_as_float(upper ? en.raw.w : sw[1]);
-      const uint32_t i = en.idx;
-      const int rcx = -1 + (i >= d.m1 ? 1 : 0) + (i >= d.m2 ? 1 : 0) + (i >= d.m3 ? 1 : 0) +
-                      (i >= d.m4 ? 1 : 0);
-      if (PW && !upper) return;
-      uint32_t hi[8], lo[8];
-      weight_rows(i < d.end ? coef : 0.0f, fx, fy, fz, rcx, d.rc % 3 - 1, d.rc / 3 - 1, hi, lo);
-      const int sel = upper ? 0 : 2;
-      const int h0 = gather_at_half(own), h1 = 16 - h0;  // bytes of voxels 0..7 and 8..15
-      char* ah = reinterpret_cast<char*>(L.a[sel]) + gather_at_at(own);
-      char* al = reinterpret_cast<char*>(L.a[sel + 1]) + gather_at_at(own);
-      *reinterpret_cast<uint4*>(ah + h0) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-      *reinterpret_cast<uint4*>(ah + h1) = make_uint4(hi[4], hi[5], hi[6], hi[7]);
-      *reinterpret_cast<uint4*>(al + h0) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-      *reinterpret_cast<uint4*>(al + h1) = make_uint4(lo[4], lo[5], lo[6], lo[7]);
-    };
-    uint4 rq[NI], rg[NI];
-    bool part = false;  // the batch ends inside: its rows past the end are zeroed in LDS
-    auto issue_rows = [&](const GatherPos& d, const GatherEntry& en) {
-      part = d.end - d.u < (uint32_t)kGB;
+  };
+  auto store_rows = [&](const GatherPos& d) {
+    if (part) {
 #pragma unroll
       for (int t = 0; t < NI; ++t) {
-        const int e = lane / LPR + RPI * t;
-        // entry e's token, from lane e (lanes 0-31 hold n), for the LPR lanes of its row
-        const uint32_t n = (uint32_t)__builtin_amdgcn_ds_bpermute(e << 2, (int)en.raw.x);
-        const uint64_t o = (uint64_t)n * tok_bytes;
-        if (d.u + e < d.end) {  // rows past the run's end are not loaded
-          if constexpr (!PW) rq[t] = *reinterpret_cast<const uint4*>(qh + o);
-          rg[t] = *reinterpret_cast<const uint4*>(gh + o);
+        if (d.u + lane / LPR + RPI * t >= d.end) {
+          rq[t] = make_uint4(0, 0, 0, 0);
+          rg[t] = make_uint4(0, 0, 0, 0);
         }
       }
-    };
-    auto store_rows = [&](const GatherPos& d) {
-      if (part) {
+    }
 #pragma unroll
-        for (int t = 0; t < NI; ++t) {
-          if (d.u + lane / LPR + RPI * t >= d.end) {
-            rq[t] = make_uint4(0, 0, 0, 0);
-            rg[t] = make_uint4(0, 0, 0, 0);
-          }
-        }
-      }
-#pragma unroll
-      for (int t = 0; t < NI; ++t) {
-        const int at = gather_row_at<D>(lane / LPR + RPI * t, lane % LPR);
-        if constexpr (!PW) *reinterpret_cast<uint4*>(reinterpret_cast<char*>(L.q) + at) = rq[t];
-        *reinterpret_cast<uint4*>(reinterpret_cast<char*>(L.g) + at) = rg[t];
-      }
-    };
+    for (int t = 0; t < NI; ++t) {
+      const int at = gather_row_at<D>(lane / LPR + RPI * t, lane % LPR);
+      if constexpr (!PW) *reinterpret_cast<uint4*>(reinterpret_cast<char*>(L.q) + at) = rq[t];
+      *reinterpret_cast<uint4*>(reinterpret_cast<char*>(L.g) + at) = rg[t];
+    }
+  };
 
-    f32x4_t ck[DB], cv[DB];
+  f32x4_t ck[DB], cv[DB];
 #pragma unroll
-    for (int db = 0; db < DB; ++db) ck[db] = cv[db] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int db = 0; db < DB; ++db) ck[db] = cv[db] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 
-    // Per batch i: store its rows, fetch the entries of batch i + 2, load the rows of batch
-    // i + 1, take batch i's products, then form batch i + 1's weights (p0, p1, p2: batches i,
-    // i + 1, i + 2).
-    GatherPos p0, p1, p2;
-    p0.left = hm;
-    next_run(p0);
-    if (p0.u < p0.end) {
-      GatherEntry e1, e2;
-      {
-        GatherEntry e0;
-        fetch(p0, e0);
-        weights(p0, e0);
-        issue_rows(p0, e0);
+  // Per batch i: store its rows, fetch the entries of batch i + 2, load the rows of batch
+  // i + 1, take batch i's products, then form batch i + 1's weights (p0, p1, p2: batches i,
+  // i + 1, i + 2).
+  GatherPos p0, p1, p2;
+  p0.left = hm;
+  next_run(p0);
+  if (p0.u < p0.end) {
+    GatherEntry e1, e2;
+    {
+      GatherEntry e0;
+      fetch(p0, e0);
+      weights(p0, e0);
+      issue_rows(p0, e0);
+    }
+    p1 = p0;
+    advance(p1);
+    if (p1.u < p1.end) fetch(p1, e1);
+    p2 = p1;
+    advance(p2);
+    while (p0.u < p0.end) {
+      store_rows(p0);
+      if (p2.u < p2.end) fetch(p2, e2);
+      if (p1.u < p1.end) issue_rows(p1, e1);
+      const bf16x8_t avh = gather_a_frag(L.a[0]), avl = gather_a_frag(L.a[1]);
+      bf16x8_t akh, akl;
+      if constexpr (!PW) {
+        akh = gather_a_frag(L.a[2]);
+        akl = gather_a_frag(L.a[3]);
       }
-      p1 = p0;
-      advance(p1);
-      if (p1.u < p1.end) fetch(p1, e1);
-      p2 = p1;
-      advance(p2);
-      while (p0.u < p0.end) {
-        store_rows(p0);
-        if (p2.u < p2.end) fetch(p2, e2);
-        if (p1.u < p1.end) issue_rows(p1, e1);
-        const bf16x8_t avh = gather_a_frag(L.a[0]), avl = gather_a_frag(L.a[1]);
-        bf16x8_t akh, akl;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
         if constexpr (!PW) {
-          akh = gather_a_frag(L.a[2]);
-          akl = gather_a_frag(L.a[3]);
+          const bf16x8_t bq = gather_b_frag<D>(L.q, db);
+          ck[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(akh, bq, ck[db], 0, 0, 0);
+          ck[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(akl, bq, ck[db], 0, 0, 0);
         }
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          if constexpr (!PW) {
-            const bf16x8_t bq = gather_b_frag<D>(L.q, db);
-            ck[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(akh, bq, ck[db], 0, 0, 0);
-            ck[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(akl, bq, ck[db], 0, 0, 0);
-          }
-          const bf16x8_t bg = gather_b_frag<D>(L.g, db);
-          cv[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(avh, bg, cv[db], 0, 0, 0);
-          cv[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(avl, bg, cv[db], 0, 0, 0);
-        }
-        if (p1.u < p1.end) weights(p1, e1);
-        e1 = e2;
-        p0 = p1;
-        p1 = p2;
-        advance(p2);
+        const bf16x8_t bg = gather_b_frag<D>(L.g, db);
+        cv[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(avh, bg, cv[db], 0, 0, 0);
+        cv[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(avl, bg, cv[db], 0, 0, 0);
       }
+      if (p1.u < p1.end) weights(p1, e1);
+      e1 = e2;
+      p0 = p1;
+      p1 = p2;
+      advance(p2);
     }
+  }
 
-    // result rows 4 G + vx (G = lane / 16 = vy + 2 vz), column lane % 16 of each channel block
-    const int grp = lane >> 4, col = lane & 15;
-    const int vy = grp & 1, vz = grp >> 1;
-    if ((vy == 0 || hasy1) && (vz == 0 || hasz1)) {
-      const int64_t row0 =
-          ((int64_t)b * g.N + (int64_t)((z0 + vz) * g.H + y0 + vy) * g.W + x0) * g.heads + m;
+  // result rows 4 G + vx (G = lane / 16 = vy + 2 vz), column lane % 16 of each channel block
+  const int grp = lane >> 4, col = lane & 15;
+  const int vy = grp & 1, vz = grp >> 1;
+  if ((vy == 0 || hasy1) && (vz == 0 || hasz1)) {
+    const int64_t row0 =
+        ((int64_t)b * g.N + (int64_t)((z0 + vz) * g.H + y0 + vy) * g.W + x0) * g.heads + m;
 #pragma unroll
-      for (int vx = 0; vx < 4; ++vx) {
-        if (vx > 0 && x0 + vx >= g.W) break;
-        const int64_t row = row0 + (int64_t)vx * g.heads;
+    for (int vx = 0; vx < 4; ++vx) {
+      if (vx > 0 && x0 + vx >= g.W) break;
+      const int64_t row = row0 + (int64_t)vx * g.heads;
 #pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          if constexpr (!PW) dk[row * D + db * 16 + col] = ck[db][vx];
-          dv[row * D + db * 16 + col] = cv[db][vx];
-        }
+      for (int db = 0; db < DB; ++db) {
+        if constexpr (!PW) dk[row * D + db * 16 + col] = ck[db][vx];
+        dv[row * D + db * 16 + col] = cv[db][vx];
       }
     }
   }
@@ -1366,7 +1671,8 @@ hipError_t bwd_dispatch(const Geometry& g, const void* q, const void* k, const v
                         dim3(kBlockThreads), a, 0, s);
     if (e != hipSuccess) return e;
   }
-  const PencilOrder po = query_order<D, BF16>(g);
+  const int rounds = pw ? 0 : backward_rounds<D, BF16>(g.P);
+  const PencilOrder po = query_order<D, BF16>(g, rounds > 0);
   const int blocks = grid_blocks(po.vtiles);
   // The main operator sweeps the points twice (V pass, then K pass with the finish of each
   // row's points); the predicted-weights variant, which reads no K, sweeps them once and
@@ -1374,10 +1680,14 @@ hipError_t bwd_dispatch(const Geometry& g, const void* q, const void* k, const v
   const bool split = !pw;
   if ((e = mark(0)) != hipSuccess) return e;
   if (split) {
-    void* a[] = {(void*)&g, (void*)&v, (void*)&off, (void*)&dout, (void*)&w.recv,
-                 (void*)&w.counts, (void*)&w.ranks, (void*)&po};
-    e = hipLaunchKernel(reinterpret_cast<const void*>(&bwd_vpass_kernel<D, BF16>), dim3(blocks),
-                        dim3(kBlockThreads), a, 0, s);
+    const void* vkern = reinterpret_cast<const void*>(&bwd_vpass_kernel<D, BF16, false>);
+    if constexpr (slot_rows_ok<D, BF16>())
+      if (rounds > 0) vkern = reinterpret_cast<const void*>(&bwd_vpass_kernel<D, BF16, true>);
+    e = launch_tiles(po.vtiles, [&](int64_t vt0, int blocks) {
+      void* a[] = {(void*)&g,        (void*)&v,       (void*)&off, (void*)&dout, (void*)&w.recv,
+                   (void*)&w.counts, (void*)&w.ranks, (void*)&po,  (void*)&vt0};
+      return hipLaunchKernel(vkern, dim3(blocks), dim3(kBlockThreads), a, 0, s);
+    });
     if (e != hipSuccess) return e;
   } else {
     void* a[] = {(void*)&g,      (void*)&v,      (void*)&logits,  (void*)&off,
@@ -1406,14 +1716,28 @@ hipError_t bwd_dispatch(const Geometry& g, const void* q, const void* k, const v
   }
   if ((e = mark(2)) != hipSuccess) return e;
   if (split) {
-    void* a[] = {(void*)&g,    (void*)&q,       (void*)&k,       (void*)&off,
-                 (void*)&lse,  (void*)&dq,      (void*)&w.reck,  (void*)&w.recv, (void*)&w.starts,
-                 (void*)&w.ranks, (void*)&doff, (void*)&w.entries, (void*)&po};
     constexpr int L = Layout<D, BF16>::kLanes;
-    const void* kern = (g.P + L - 1) / L <= kHoldChunks
-                           ? reinterpret_cast<const void*>(&bwd_kpass_kernel<D, BF16, kHoldChunks>)
-                           : reinterpret_cast<const void*>(&bwd_kpass_kernel<D, BF16, 0>);
-    e = hipLaunchKernel(kern, dim3(blocks), dim3(kBlockThreads), a, 0, s);
+    const bool hold = (g.P + L - 1) / L <= kHoldChunks;
+#define DSA3D_KPASS(HOLD, R, WHOLE) \
+  reinterpret_cast<const void*>(&bwd_kpass_kernel<D, BF16, HOLD, R, WHOLE>)
+    const bool whole = g.win_frames == g.T;
+    const void* kern = hold ? DSA3D_KPASS(kHoldChunks, 0, false) : DSA3D_KPASS(0, 0, false);
+    if constexpr (slot_rows_ok<D, BF16>() && !(BF16 && D == 64)) {
+      if constexpr (BF16)  // up to 32 points are always held
+        if (rounds == 2)
+          kern = whole ? DSA3D_KPASS(kHoldChunks, 2, true) : DSA3D_KPASS(kHoldChunks, 2, false);
+      if (rounds == 5 && hold)
+        kern = whole ? DSA3D_KPASS(kHoldChunks, 5, true) : DSA3D_KPASS(kHoldChunks, 5, false);
+      if (rounds == 5 && !hold) kern = whole ? DSA3D_KPASS(0, 5, true) : DSA3D_KPASS(0, 5, false);
+    }
+#undef DSA3D_KPASS
+    e = launch_tiles(po.vtiles, [&](int64_t vt0, int blocks) {
+      void* a[] = {(void*)&g,      (void*)&q,        (void*)&k,       (void*)&v,    (void*)&off,
+                   (void*)&lse,    (void*)&dout,     (void*)&dq,      (void*)&w.reck,
+                   (void*)&w.recv, (void*)&w.starts, (void*)&w.ranks, (void*)&doff,
+                   (void*)&w.entries, (void*)&po,    (void*)&vt0};
+      return hipLaunchKernel(kern, dim3(blocks), dim3(kBlockThreads), a, 0, s);
+    });
     if (e != hipSuccess) return e;
   } else {
     const int npoints = (int)points;
@@ -1435,24 +1759,26 @@ hipError_t bwd_dispatch(const Geometry& g, const void* q, const void* k, const v
     // because the gather then reads past L2 at the ceiling of such misses.
     const PencilOrder go = plan_pencils(g.B * g.heads, (g.T + 1) / 2, (g.H + 1) / 2,
                                         (g.W + 3) / 4, NW, D >= 128 ? 8 : 16, D >= 128 ? 4 : 8);
-    const int gblocks = grid_blocks(go.vtiles);
-    void* a[] = {(void*)&g,         (void*)&q,  (void*)&dout, (void*)&w.starts,
-                 (void*)&w.entries, (void*)&dk, (void*)&dv,   (void*)&go};
     const void* kern = pw ? reinterpret_cast<const void*>(&bwd_gather_mfma_kernel<D, true>)
                           : reinterpret_cast<const void*>(&bwd_gather_mfma_kernel<D, false>);
-    e = hipLaunchKernel(kern, dim3(gblocks), dim3(64 * NW), a, 0, s);
+    e = launch_tiles(go.vtiles, [&](int64_t vt0, int gblocks) {
+      void* a[] = {(void*)&g,  (void*)&q,  (void*)&dout, (void*)&w.starts, (void*)&w.entries,
+                   (void*)&dk, (void*)&dv, (void*)&go,   (void*)&vt0};
+      return hipLaunchKernel(kern, dim3(gblocks), dim3(64 * NW), a, 0, s);
+    });
     if (e != hipSuccess) return e;
   } else {
     using LY = Layout<D, BF16>;
     // cells: 2 x 2 voxel blocks of a frame; pencils of about 32 x 32 voxels
     const PencilOrder go = plan_pencils(g.B * g.heads, g.T, (g.H + 1) / 2, (g.W + 1) / 2,
                                         LY::kRowsPerBlock, 16, 16);
-    const int gblocks = grid_blocks(go.vtiles);
-    void* a[] = {(void*)&g,         (void*)&q,  (void*)&dout, (void*)&w.starts,
-                 (void*)&w.entries, (void*)&dk, (void*)&dv,   (void*)&go};
     const void* kern = pw ? reinterpret_cast<const void*>(&bwd_gather_kernel<D, BF16, true>)
                           : reinterpret_cast<const void*>(&bwd_gather_kernel<D, BF16, false>);
-    e = hipLaunchKernel(kern, dim3(gblocks), dim3(kBlockThreads), a, 0, s);
+    e = launch_tiles(go.vtiles, [&](int64_t vt0, int gblocks) {
+      void* a[] = {(void*)&g,  (void*)&q,  (void*)&dout, (void*)&w.starts, (void*)&w.entries,
+                   (void*)&dk, (void*)&dv, (void*)&go,   (void*)&vt0};
+      return hipLaunchKernel(kern, dim3(gblocks), dim3(kBlockThreads), a, 0, s);
+    });
     if (e != hipSuccess) return e;
   }
   return mark(4);

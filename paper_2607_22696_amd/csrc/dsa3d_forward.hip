@@ -33,7 +33,7 @@ using namespace dev;
 //
 // PW (the predicted-weights variant): the logit of a point is given (`logits`, one fp32 per
 // (row, point)) instead of scale <q, k_p>, so neither q nor the K corners are read.
-template <int D, bool BF16, bool PW>
+template <int D, bool BF16, bool PW, bool SLOTS>
 __device__ inline __attribute__((always_inline)) void gather_tile(
     const Geometry& g, const PencilOrder& po, const PencilTile& tl, const void* __restrict__ q,
     const void* __restrict__ k, const void* __restrict__ v, const float* __restrict__ logits,
@@ -59,7 +59,7 @@ __device__ inline __attribute__((always_inline)) void gather_tile(
   const int t = tl.frame;
   const RowWindow win = make_window<LY::kRowBytes>(g, k, v, b, m, t);
   int i, j;
-  const bool active = query_token<D, BF16>(po, g, tl, wave * LY::kGroups + grp, i, j);
+  const bool active = query_token<SLOTS>(po, g, tl, wave * LY::kGroups + grp, i, j);
   if (!active) {  // an idle row computes on a valid token and stores nothing
     i = min(i, g.H - 1);
     j = min(j, g.W - 1);
@@ -164,11 +164,11 @@ __device__ inline __attribute__((always_inline)) void slots_tile(
     const Geometry& g, const PencilOrder& po, const PencilTile& tl, const void* __restrict__ q,
     const void* __restrict__ k, const void* __restrict__ v, const float* __restrict__ logits,
     const float* __restrict__ offsets, void* __restrict__ out, float* __restrict__ lse,
-    SlotLds<R>& lds) {
+    SlotLds& lds) {
   using LY = Layout<D, BF16>;
   using U = SlotSum<D, BF16>;
   constexpr int L = kSlotLanes;
-  const int lane = threadIdx.x & 63;
+  const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int qi = lane / L, lp = lane % L;
   float* const val = lds.val[qi];
@@ -216,7 +216,7 @@ __device__ inline __attribute__((always_inline)) void slots_tile(
       if constexpr (!PW) {
         SlotVecs<D, BF16> vec;
         vec.load(static_cast<const char*>(q), qrow);
-        row_dots<D, BF16, R>(slot_rows<LY::kRowBytes>(g, k, win, b, m, global), lds, vec, n);
+        row_dots<D, BF16>(slot_rows<LY::kRowBytes>(g, k, win, b, m, global), lds, vec, n);
       }
       float mc = mx;
 #pragma unroll
@@ -237,7 +237,7 @@ __device__ inline __attribute__((always_inline)) void slots_tile(
       mc = lane_maxf<L>(mc);
       const float corr = mx == mc ? 1.0f : exp2f(mx - mc);  // the first chunk: 0 (or of zeros)
       mx = mc;
-      clear_coefs<R>(lds, n);
+      clear_coefs(lds, n);
       float lc = 0.0f;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
@@ -257,7 +257,7 @@ __device__ inline __attribute__((always_inline)) void slots_tile(
         if (r * L + lp < npts) add_coefs(pt[r], val, s[r] * fix);
       }
       float sum[U::kVec];
-      row_sums<D, BF16, R>(slot_rows<LY::kRowBytes>(g, v, win, b, m, global), lds, n, sum);
+      row_sums<D, BF16>(slot_rows<LY::kRowBytes>(g, v, win, b, m, global), lds, n, sum);
 #pragma unroll
       for (int x = 0; x < U::kVec; ++x) o[x] = fmaf(o[x], corr, sum[x] * (lc / kSlotOne));
       c0 += npts;
@@ -291,19 +291,19 @@ fwd_kernel(Geometry g, const void* __restrict__ q, const void* __restrict__ k,
            const float* __restrict__ offsets, void* __restrict__ out, float* __restrict__ lse,
            PencilOrder po, int64_t vt0) {
   constexpr size_t kPts = slot_words<Layout<D, BF16>::kLanes, 5>() * sizeof(int4);
-  constexpr size_t kSlots = R > 0 ? kWavesPerBlock * sizeof(SlotLds<R>) : 0;
+  constexpr size_t kSlots = R > 0 ? kWavesPerBlock * sizeof(SlotLds) : 0;
   __shared__ __attribute__((aligned(16))) char lds[kPts > kSlots ? kPts : kSlots];
   PencilTile tl;
   if (!pencil_tile(po, vt0 + blockIdx.x, tl)) return;  // no pencil left on this XCD
   if constexpr (R > 0) {
-    if (compact_tile(g, po, tl, offsets)) {  // the same in every wave
+    if (compact_tile(g, po, tl, offsets, forward_box<D, BF16>())) {  // the same in every wave
       slots_tile<D, BF16, PW, R, WHOLE>(
           g, po, tl, q, k, v, logits, offsets, out, lse,
-          reinterpret_cast<SlotLds<R>*>(lds)[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)]);
+          reinterpret_cast<SlotLds*>(lds)[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)]);
       return;
     }
   }
-  gather_tile<D, BF16, PW>(g, po, tl, q, k, v, logits, offsets, out, lse,
+  gather_tile<D, BF16, PW, (R > 0)>(g, po, tl, q, k, v, logits, offsets, out, lse,
                            reinterpret_cast<int4*>(lds));
 }
 
@@ -313,20 +313,17 @@ template <int D, bool BF16>
 hipError_t fwd_dispatch(const Geometry& g, const void* q, const void* k, const void* v,
                         const float* logits, const float* off, void* out, float* lse,
                         hipStream_t s) {
-  const PencilOrder po = query_order<D, BF16>(g, true);
   const bool pw = logits != nullptr;
 #define DSA3D_FWD(R, WHOLE)                                                    \
   (pw ? reinterpret_cast<const void*>(&fwd_kernel<D, BF16, true, R, WHOLE>)   \
       : reinterpret_cast<const void*>(&fwd_kernel<D, BF16, false, R, WHOLE>))
-  const void* kern;
+  const int rounds = forward_rounds<D, BF16>(g.P);
+  const PencilOrder po = query_order<D, BF16>(g, rounds > 0, true);
+  const bool whole = g.win_frames == g.T;
+  const void* kern = DSA3D_FWD(0, false);
   if constexpr (slot_rows_ok<D, BF16>()) {
-    const bool whole = g.win_frames == g.T;
-    if (g.P <= 2 * kSlotLanes)
-      kern = whole ? DSA3D_FWD(2, true) : DSA3D_FWD(2, false);
-    else
-      kern = whole ? DSA3D_FWD(5, true) : DSA3D_FWD(5, false);
-  } else {
-    kern = DSA3D_FWD(0, false);
+    if (rounds == 2) kern = whole ? DSA3D_FWD(2, true) : DSA3D_FWD(2, false);
+    if (rounds == 5) kern = whole ? DSA3D_FWD(5, true) : DSA3D_FWD(5, false);
   }
 #undef DSA3D_FWD
   return launch_tiles(po.vtiles, [&](int64_t vt0, int blocks) {

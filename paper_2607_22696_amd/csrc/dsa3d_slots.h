@@ -50,21 +50,18 @@ constexpr int kSlotBoxX = 32, kSlotBoxY = 16, kSlotBoxZ = 16;
 constexpr int kSlotWords = kSlotBoxY * kSlotBoxZ;  // four per lane
 static_assert(kSlotWords == 256, "four words per lane");
 
-// R rounds of points are numbered together: up to 32 points of a query in 512 slots, or 80 in 640
-// (a round of 64 lanes on its own needs 512).  LDS holds four workgroups of the first kind on a
-// compute unit and three of the second.
-template <int R>
-constexpr int slot_cap() { return R <= 2 ? 512 : 640; }
+// Up to R rounds of points are numbered together, in 640 slots (a round of 64 lanes on its own
+// needs 512): LDS holds three workgroups on a compute unit, as many as the registers allow.
+constexpr int kSlotCap = 640;
 
 // A wave's slots: the voxel of each, and per query its dot product or coefficient.  The bitmap
 // (bits and the number of slots before a word) is needed only until the slots are numbered.
-template <int R>
 struct SlotLds {
-  __attribute__((aligned(16))) uint32_t list[slot_cap<R>()];
+  __attribute__((aligned(16))) uint32_t list[kSlotCap];
   union {
     __attribute__((aligned(16))) uint2 words[kSlotWords];
     // 16 words of padding: the four queries' values of a slot lie on different banks
-    __attribute__((aligned(16))) float val[kSlotQueries][slot_cap<R>() + 16];
+    __attribute__((aligned(16))) float val[kSlotQueries][kSlotCap + 16];
   };
 };
 
@@ -74,6 +71,15 @@ __device__ inline __attribute__((always_inline)) void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The lane, as a value that the compiler takes for another one at each call: what depends on the
+// lane is then formed where it is used and not kept in registers around the loops over tokens and
+// chunks (at head_dim 64 those values cost the backward 60 spilled registers).
+__device__ inline __attribute__((always_inline)) int lane_id() {
+  int l = threadIdx.x & 63;
+  asm volatile("" : "+v"(l));
+  return l;
 }
 
 // ---------------------------------------------------------------------------- lane reductions
@@ -135,13 +141,12 @@ __device__ inline __attribute__((always_inline)) bool slot_token(const PencilOrd
 }
 
 // Whether a tile is worth numbering: the points (up to 64) of its first token, with their corners,
-// span at most kCompactBox voxels.
-constexpr int kCompactBox = 1400;
-
+// span at most `limit` voxels.
 __device__ inline __attribute__((always_inline)) bool compact_tile(const Geometry& g,
                                                                    const PencilOrder& po,
                                                                    const PencilTile& tl,
-                                                                   const float* offsets) {
+                                                                   const float* offsets,
+                                                                   int limit) {
   const int b = tl.group / g.by_heads, m = tl.group - b * g.heads;
   int i, j;
   slot_token(po, g, tl, 0, i, j);
@@ -160,7 +165,7 @@ __device__ inline __attribute__((always_inline)) bool compact_tile(const Geometr
   const int ex = min(-lane_min<64>(-x) - lane_min<64>(x), 255) + 2;
   const int ey = min(-lane_min<64>(-y) - lane_min<64>(y), 255) + 2;
   const int ez = min(-lane_min<64>(-z) - lane_min<64>(z), 255) + 2;
-  return __builtin_amdgcn_readfirstlane(ex * ey * ez) <= kCompactBox;
+  return __builtin_amdgcn_readfirstlane(ex * ey * ez) <= limit;
 }
 
 // ---------------------------------------------------------------------------- rows
@@ -267,17 +272,18 @@ struct SlotPoint {
 //
 // Numbers the slots of a wave's queries for rounds of points (npts per query) and writes the
 // voxel list.  In: pt[r], the lane's point of round r (lanes past the end repeat a point of the
-// range).  Returns the number of points taken per query: npts, or one round's when they do not
-// fit the box or the slots; n: the slot count; `global`: the list holds tokens.
+// range).  Returns the number of points taken per query: npts, or half of the rounds as often as it
+// takes for their voxels to fit the slots, or one round without sharing when they leave the box;
+// n: the slot count; `global`: the list holds tokens.
 template <int R, bool WHOLE>
 __device__ inline __attribute__((always_inline)) int number_slots(const Geometry& g,
                                                                   const SlotWindow& win,
                                                                   uint32_t tok_bytes,
-                                                                  SlotLds<R>& lds,
+                                                                  SlotLds& lds,
                                                                   SlotPoint (&pt)[R], int npts,
                                                                   int& n, bool& global) {
   constexpr int L = kSlotLanes;
-  const int lane = threadIdx.x & 63;
+  const int lane = lane_id();
   // the box starts at the smallest cell
   int x0 = pt[0].x, y0 = pt[0].y, z0 = pt[0].z;
 #pragma unroll
@@ -301,12 +307,12 @@ __device__ inline __attribute__((always_inline)) int number_slots(const Geometry
       slow = slow || ((unsigned)(pt[r].z + c) < (unsigned)g.T &&
                       (unsigned)(pt[r].z + c - win.t0) >= (unsigned)win.frames);
   }
-  bool fits = __builtin_amdgcn_ballot_w64(out) == 0;
+  const bool fits = __builtin_amdgcn_ballot_w64(out) == 0;
   global = !WHOLE && __builtin_amdgcn_ballot_w64(slow) != 0;
   n = 0;
   wave_sync();
-  if (fits) {
-    uint4* w4 = reinterpret_cast<uint4*>(lds.words) + 2 * lane;
+  uint4* const w4 = reinterpret_cast<uint4*>(lds.words) + 2 * lane;
+  while (fits) {
     w4[0] = make_uint4(0u, 0u, 0u, 0u);
     w4[1] = make_uint4(0u, 0u, 0u, 0u);
     wave_sync();
@@ -326,6 +332,11 @@ __device__ inline __attribute__((always_inline)) int number_slots(const Geometry
                    n3 = n2 + __popc(b.z);
     const uint32_t incl = lane_scan(n3), s = incl - n3;
     n = __builtin_amdgcn_readlane((int)incl, 63);
+    if (n > kSlotCap) {  // at least two rounds: one round has at most 512 corners
+      npts = (npts + 2 * L - 1) / (2 * L) * L;
+      wave_sync();
+      continue;
+    }
     a.y = s;
     a.w = s + n0;
     b.y = s + n1;
@@ -333,24 +344,23 @@ __device__ inline __attribute__((always_inline)) int number_slots(const Geometry
     w4[0] = a;
     w4[1] = b;
     wave_sync();
-    fits = n <= slot_cap<R>();
-  }
-  if (fits) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       if (r * L >= npts) break;
       const uint32_t below = (1u << (pt[r].x - x0)) - 1u;
       const int at = (pt[r].z - z0) * kSlotBoxY + pt[r].y - y0;
-      uint32_t s[4];
+      uint32_t s4[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const uint2 w = lds.words[at + (e & 1) + (e >> 1) * kSlotBoxY];
-        s[e] = w.y + __popc(w.x & below);
+        s4[e] = w.y + __popc(w.x & below);
       }
-      pt[r].s01 = s[0] | (s[1] << 16);
-      pt[r].s23 = s[2] | (s[3] << 16);
+      pt[r].s01 = s4[0] | (s4[1] << 16);
+      pt[r].s23 = s4[2] | (s4[3] << 16);
     }
-  } else {
+    break;
+  }
+  if (!fits) {
     npts = min(npts, L);
     n = 64 * 8;
     pt[0].s01 = (uint32_t)(8 * lane) * 0x10001u + 0x20000u;
@@ -395,7 +405,7 @@ struct SlotVecs {
   __device__ inline __attribute__((always_inline)) void load(const char* x,
                                                              const int64_t (&row)[kSlotQueries]) {
     constexpr int64_t kRowBytes = D * (BF16 ? 2 : 4);
-    const int lane = threadIdx.x & 63;
+    const int lane = lane_id();
     const bool mine = !BF16 || (lane >> 4) == ((lane >> 2) & 3);
 #pragma unroll
     for (int w = 0; w < kSlotQueries; ++w)
@@ -410,12 +420,12 @@ struct SlotVecs {
 };
 
 // val[w][s] = <vector of query w, row of slot s> for n slots.
-template <int D, bool BF16, bool GLOBAL, int R>
+template <int D, bool BF16, bool GLOBAL>
 __device__ inline __attribute__((always_inline)) void row_dots_of(const SlotRows& rows,
-                                                                  SlotLds<R>& lds,
+                                                                  SlotLds& lds,
                                                                   const SlotVecs<D, BF16>& vec,
                                                                   int n) {
-  const int lane = threadIdx.x & 63;
+  const int lane = lane_id();
   if constexpr (BF16) {
     constexpr int KS = D / 32;
     const uint32_t off = 16u * (lane & 3);
@@ -471,15 +481,15 @@ __device__ inline __attribute__((always_inline)) void row_dots_of(const SlotRows
   }
 }
 
-template <int D, bool BF16, int R>
+template <int D, bool BF16>
 __device__ inline __attribute__((always_inline)) void row_dots(const SlotRows& rows,
-                                                               SlotLds<R>& lds,
+                                                               SlotLds& lds,
                                                                const SlotVecs<D, BF16>& vec,
                                                                int n) {
   if (!rows.global)
-    row_dots_of<D, BF16, false, R>(rows, lds, vec, n);
+    row_dots_of<D, BF16, false>(rows, lds, vec, n);
   else
-    row_dots_of<D, BF16, true, R>(rows, lds, vec, n);
+    row_dots_of<D, BF16, true>(rows, lds, vec, n);
   wave_sync();
 }
 
@@ -496,9 +506,8 @@ struct SlotSum {
 };
 
 // Clears the coefficients of n slots (and of the rest of the last batch).
-template <int R>
-__device__ inline __attribute__((always_inline)) void clear_coefs(SlotLds<R>& lds, int n) {
-  const int lane = threadIdx.x & 63;
+__device__ inline __attribute__((always_inline)) void clear_coefs(SlotLds& lds, int n) {
+  const int lane = lane_id();
   wave_sync();
   for (int s = 4 * (lane & 15); s < ((n + 63) & ~63); s += 64)
     *reinterpret_cast<float4*>(&lds.val[lane >> 4][s]) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -549,11 +558,11 @@ __device__ inline __attribute__((always_inline)) float keep_sum(const float (&q)
 
 // sum[x] = sum over n slots of val[query][s] * row s (the coefficients as they are, in fixed point),
 // in fp32 on the vector ALU.  SAFE: a row whose coefficient is zero is not touched.
-template <int D, bool BF16, bool GLOBAL, bool SAFE, int R>
+template <int D, bool BF16, bool GLOBAL, bool SAFE>
 __device__ inline __attribute__((always_inline)) void row_sums_valu(
-    const SlotRows& rows, const SlotLds<R>& lds, int n, float (&sum)[SlotSum<D, BF16>::kVec]) {
+    const SlotRows& rows, const SlotLds& lds, int n, float (&sum)[SlotSum<D, BF16>::kVec]) {
   using U = SlotSum<D, BF16>;
-  const int lane = threadIdx.x & 63, sub = lane % U::kLanes, grp = lane / U::kLanes;
+  const int lane = lane_id(), sub = lane % U::kLanes, grp = lane / U::kLanes;
   float part[kSlotQueries][U::kVec];
 #pragma unroll
   for (int w = 0; w < kSlotQueries; ++w)
@@ -587,14 +596,14 @@ __device__ inline __attribute__((always_inline)) void row_sums_valu(
 // the coefficients of set s % SETS for query SETS (s / SETS) + t in product t; result element p
 // of lane group G is then byte p's share of the sum of set G % SETS, meant for the columns of
 // that set.
-template <int D, bool GLOBAL, int R>
+template <int D, bool GLOBAL>
 __device__ inline __attribute__((always_inline)) void row_sums_mfma(const SlotRows& rows,
-                                                                    const SlotLds<R>& lds, int n,
+                                                                    const SlotLds& lds, int n,
                                                                     float (&sum)[8]) {
   using U = SlotSum<D, true>;
   constexpr int SETS = 16 / U::kLanes;
   static_assert(SETS == 1 || SETS == 2, "head_dim 64 or 128");
-  const int lane = threadIdx.x & 63, sub = lane % U::kLanes, grp = lane / U::kLanes;
+  const int lane = lane_id(), sub = lane % U::kLanes, grp = lane / U::kLanes;
   const int a_s = (lane >> 2) & 3, a_set = a_s % SETS, a_q = a_s / SETS * SETS;
   const int shift = 8 * (lane & 3);
   const float bias = (lane & 3) == 3 ? 128.0f : 0.0f;
@@ -679,64 +688,98 @@ __device__ inline __attribute__((always_inline)) void row_sums_mfma(const SlotRo
 // l / 16, the coefficients in fixed point.  An infinite or NaN row value meets the zero
 // coefficients of the queries that do not sample it, and on the matrix cores the zero bytes of
 // those that do, and gives NaN; a wave that sees a NaN takes its sums again without them.
-template <int D, bool BF16, bool GLOBAL, int R>
+template <int D, bool BF16, bool GLOBAL>
 __device__ inline __attribute__((always_inline)) void row_sums_of(
-    const SlotRows& rows, const SlotLds<R>& lds, int n, float (&sum)[SlotSum<D, BF16>::kVec]) {
+    const SlotRows& rows, const SlotLds& lds, int n, float (&sum)[SlotSum<D, BF16>::kVec]) {
   if constexpr (BF16)
-    row_sums_mfma<D, GLOBAL, R>(rows, lds, n, sum);
+    row_sums_mfma<D, GLOBAL>(rows, lds, n, sum);
   else
-    row_sums_valu<D, false, GLOBAL, false, R>(rows, lds, n, sum);
+    row_sums_valu<D, false, GLOBAL, false>(rows, lds, n, sum);
   bool nan = false;
 #pragma unroll
   for (int x = 0; x < SlotSum<D, BF16>::kVec; ++x) nan = nan || sum[x] != sum[x];
   if (__builtin_amdgcn_ballot_w64(nan) != 0)
-    row_sums_valu<D, BF16, GLOBAL, true, R>(rows, lds, n, sum);
+    row_sums_valu<D, BF16, GLOBAL, true>(rows, lds, n, sum);
 }
 
-template <int D, bool BF16, int R>
+template <int D, bool BF16>
 __device__ inline __attribute__((always_inline)) void row_sums(
-    const SlotRows& rows, const SlotLds<R>& lds, int n, float (&sum)[SlotSum<D, BF16>::kVec]) {
+    const SlotRows& rows, const SlotLds& lds, int n, float (&sum)[SlotSum<D, BF16>::kVec]) {
   wave_sync();
   if (!rows.global)
-    row_sums_of<D, BF16, false, R>(rows, lds, n, sum);
+    row_sums_of<D, BF16, false>(rows, lds, n, sum);
   else
-    row_sums_of<D, BF16, true, R>(rows, lds, n, sum);
+    row_sums_of<D, BF16, true>(rows, lds, n, sum);
   wave_sync();
 }
 
 // ---------------------------------------------------------------------------- launch shape
 
-// Whether the slot kernels are built for this row size.
+// Whether the slots are built for this row size.
 template <int D, bool BF16>
 constexpr bool slot_rows_ok() {
   return SlotSum<D, BF16>::kLanes == 8 || SlotSum<D, BF16>::kLanes == 16;
 }
 
-// Pencil order of the query-owned kernels.  Where the slot kernels are built, cells of four tokens
-// along x, else single tokens.  A tile is a workgroup's rows with a row on kLanes lanes.  Pencils are about 12 x 12 tokens: at 64x68x120, 24
-// heads x 128, 3x5x5, offsets U[-8, 8], the forward took 159 / 162 / 197 ms with pencils of about
-// 12 x 12 / 16 x 16 / 24 x 24 tokens.
-// A grid whose tiles would leave compute units idle gets smaller ones, down to one cell, of which a
-// workgroup's other waves have nothing (4x8x8 tokens, 2 heads x 32, fp32: 17.6 -> 10.6 us).
+// Rounds that a kernel instance numbers together (0: every tile gathers) for rows of P points.
+// Numbering costs a wave the same for 9 points as for 16, which rows of 128 bytes do not earn
+// back: forward at 16x34x60, 24 heads, 1x3x3, 64 bf16 channels: 0.63 ms gathering, 0.90 by slots;
+// 128 channels: 1.14 and 1.06.
+template <int D, bool BF16>
+inline int forward_rounds(int P) {
+  if (!slot_rows_ok<D, BF16>() || (P < kSlotLanes && !(BF16 && D == 128))) return 0;
+  return P <= 2 * kSlotLanes ? 2 : 5;
+}
+
+// Spread of a compact tile (compact_tile).  Offsets U[-3, 3] span about 700 voxels at 3x3x3 and 1090
+// at 3x5x5, U[-4, 4] 1250 and 1770.  16x34x60 (fp32: 9x33x47), gathering / by slots.  Forward: 24 x
+// 128 bf16, 3x3x3 U[-4, 4] 2.88 / 2.34 ms, 3x5x5 U[-3, 3] 7.32 / 4.64, U[-4, 4] 7.48 / 7.13; 16 x 64
+// bf16, 3x3x3 U[-3, 3] 1.02 / 1.05, U[-4, 4] 1.07 / 1.21; 6 x 64 fp32, 3x3x3 U[-4, 4] 0.30 / 0.37.
+// Backward, V pass + K pass: 24 x 128 bf16, 3x3x3 U[-3, 3] 4.68 / 4.50, U[-4, 4] 4.62 / 5.21, 3x5x5
+// U[-3, 3] 12.0 / 12.0, U[-4, 4] 12.0 / 13.0.
+template <int D, bool BF16>
+constexpr int forward_box() { return BF16 && D == 128 ? 1500 : 1000; }
+constexpr int kBackwardBox = 1000;
+
+// The backward sweeps the slots three times and counts the compact tiles on their own, so it needs
+// larger rows or more points.  V pass + K pass, gathering and by slots, N(0, 1) offsets: 128 bf16
+// channels, 16x34x60, 24 heads: 1x3x3 1.92 / 2.49 ms, 3x3x3 4.58 / 3.90, 3x5x5 11.9 / 8.5, 3x7x7
+// 22.9 / 18.0; 64 bf16 channels, 16 heads: 3x5x5 5.14 / 5.10, 3x7x7 10.2 / 11.1; 64 fp32
+// channels, 9x33x47, 6 heads: 3x3x3 0.84 / 0.84 (two batch items), 3x5x5 1.14 / 0.93, 3x7x7 2.28 /
+// 2.03.
+template <int D, bool BF16>
+inline int backward_rounds(int P) {
+  if (!slot_rows_ok<D, BF16>() || (BF16 && D == 64)) return 0;
+  if (P <= 2 * kSlotLanes) return BF16 && P >= kSlotLanes ? 2 : 0;
+  return 5;
+}
+
+// Pencil order of the query-owned kernels: cells of one token, or of four along x where tiles may
+// be taken by slots.  A tile is a workgroup's rows with a row on kLanes lanes.  Pencils are about
+// 12 x 12 tokens: at 64x68x120, 24 heads x 128, 3x5x5, offsets U[-8, 8], the forward took 159 /
+// 162 / 197 ms with pencils of about 12 x 12 / 16 x 16 / 24 x 24 tokens.
+// With slots, a grid whose tiles would leave compute units idle gets smaller ones, down to one
+// cell, of which a workgroup's other waves have nothing (4x8x8 tokens, 2 heads x 32, fp32: 17.6 ->
+// 10.6 us).
 constexpr int kFillTiles = 512;  // two workgroups per compute unit
 
 template <int D, bool BF16>
-inline PencilOrder query_order(const Geometry& g, bool fill = false) {
-  constexpr int Q = slot_rows_ok<D, BF16>() ? kSlotQueries : 1;
+inline PencilOrder query_order(const Geometry& g, bool slots, bool fill = false) {
+  if (!slots) return plan_pencils(g.B * g.heads, g.T, g.H, g.W, Layout<D, BF16>::kRowsPerBlock, 12, 12);
+  constexpr int Q = kSlotQueries;
   int run = Layout<D, BF16>::kRowsPerBlock / Q;
   const int64_t cells = (int64_t)g.B * g.heads * g.T * g.H * ((g.W + Q - 1) / Q);
-  while (fill && Q > 1 && run > 1 && cells < (int64_t)run * kFillTiles) run /= 2;
+  while (fill && run > 1 && cells < (int64_t)run * kFillTiles) run /= 2;
   return plan_pencils(g.B * g.heads, g.T, g.H, (g.W + Q - 1) / Q, run, 12, 12 / Q);
 }
 
-// Token e of a tile in that order; false if it is past the pencil or the grid.
-template <int D, bool BF16>
+// Token e of a tile in that order; false if it is past the tile, the pencil or the grid.
+template <bool SLOTS>
 __device__ inline __attribute__((always_inline)) bool query_token(const PencilOrder& po,
                                                                   const Geometry& g,
                                                                   const PencilTile& tl, int e,
                                                                   int& i, int& j) {
-  if constexpr (slot_rows_ok<D, BF16>())
-    return slot_token(po, g, tl, e, i, j) && e < po.run * kSlotQueries;
+  if constexpr (SLOTS) return slot_token(po, g, tl, e, i, j) && e < po.run * kSlotQueries;
   return pencil_cell(po, tl, e, i, j);
 }
 
