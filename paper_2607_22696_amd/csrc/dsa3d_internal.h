@@ -54,6 +54,7 @@ struct ConvGeometry {
   int kt, kh, kw, taps;      // odd filter size and its tap count
   int chunks;                // 128-channel chunks
   int strips, sg, hq;        // 8-token strips along x, strips per brick, 4-row quads along y
+  int segs, seg_frames;      // segments of the frames on the streaming path, frames of one
   int tiles_per_bc;          // tiles per (channel chunk, batch item), brick padding included
   int wg_blocks;             // weight-gradient blocks per (channel chunk, filter plane)
 };

@@ -265,30 +265,40 @@ __global__ __launch_bounds__(kBlockThreads) void dwconv_wgrad_kernel(
   }
 }
 
-// dw[c][tap] = sum over slots of part[slot][c][tap] (slots in order); db likewise.
-__global__ __launch_bounds__(kBlockThreads) void dwconv_wgrad_reduce_kernel(
+// dw[c][tap] = sum over slots of part[slot][c][tap]; db likewise.  A block takes 64 outputs: wave w
+// adds slots w, w + 16, ... (each load 256 consecutive bytes), then the 16 partial sums are added
+// in order, so the result is repeatable.  One thread per output walking every slot left the sums
+// to the latency of its loads: 338 MB took 402 us at 64x68x120x3072, 3x3x3, and take 102 us now.
+constexpr int kReduceWaves = 16;
+
+__global__ __launch_bounds__(64 * kReduceWaves) void dwconv_wgrad_reduce_kernel(
     const float* __restrict__ part, const float* __restrict__ part_b, int64_t per_slot,
     int64_t per_slot_b, int slots, float* __restrict__ dw, float* __restrict__ db) {
-  const int64_t n = per_slot + per_slot_b;
-  for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < n;
-       o += (int64_t)gridDim.x * blockDim.x) {
-    const bool is_b = o >= per_slot;
-    if (is_b ? db == nullptr : dw == nullptr) continue;
-    const float* src = is_b ? part_b + (o - per_slot) : part + o;
-    const int64_t stride = is_b ? per_slot_b : per_slot;
-    float s = 0.0f;
-    for (int k = 0; k < slots; ++k) s += src[k * stride];
-    if (is_b)
-      db[o - per_slot] = s;
-    else
-      dw[o] = s;
+  __shared__ float sums[kReduceWaves][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t o = (int64_t)blockIdx.x * 64 + lane;
+  const bool is_b = o >= per_slot, mine = o < per_slot + per_slot_b;
+  const float* src = is_b ? part_b + (o - per_slot) : part + o;
+  const int64_t stride = is_b ? per_slot_b : per_slot;
+  float s = 0.0f;
+  if (mine)
+    for (int k = wave; k < slots; k += kReduceWaves) s += src[k * stride];
+  sums[wave][lane] = s;
+  __syncthreads();
+  if (wave != 0 || !mine) return;
+  for (int w = 1; w < kReduceWaves; ++w) s += sums[w][lane];
+  if (is_b) {
+    if (db != nullptr) db[o - per_slot] = s;
+  } else if (dw != nullptr) {
+    dw[o] = s;
   }
 }
 
 // ---------------------------------------------------------------------------- time streaming
 
-// Fast path for bf16 data and filters of at most 3 along every axis.  A block owns a brick of
-// 4 grid rows x 8 tokens x 128 channels and walks all frames.  One input slice of the brick (its
+// Fast path for filters of at most 3 along every axis.  A block owns a brick of 4 grid rows x 8
+// tokens x 128 channels and walks its frames: all of them, or one of g.segs equal segments where
+// the grid has too few bricks to fill the chip (a segment reads the filter's halo of frames too).  One input slice of the brick (its
 // rows and columns plus the filter's halo, zero outside the grid) is staged per frame, in one of
 // two LDS buffers; while a slice is used, the next one is stored into the other buffer and the
 // one after that is in flight into registers, so every input element comes from HBM about once
@@ -303,9 +313,38 @@ struct SliceShape {
   static constexpr int TAPS = KT * KH * KW;
 };
 
-// The slice positions this wave loads: 32-bit byte offsets within a frame (UINT32_MAX, which the
+constexpr uint32_t kOutside = 0xfffffff0u;  // beyond a frame (below 2 GB), no wrap within a pair
+
+// A lane's two channels of one position as they are in memory.
+template <bool BF16>
+struct PairWord {
+  typedef uint32_t type;
+};
+template <>
+struct PairWord<false> {
+  typedef uint2 type;
+};
+template <bool BF16>
+using pair_t = typename PairWord<BF16>::type;
+
+template <bool BF16>
+__device__ inline __attribute__((always_inline)) pair_t<BF16> load_pair(__amdgpu_buffer_rsrc_t r,
+                                                                        uint32_t off) {
+  if constexpr (BF16)
+    return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
+  else
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
+}
+__device__ inline __attribute__((always_inline)) float2 widen(uint32_t u) {
+  return make_float2(__uint_as_float(u << 16), __uint_as_float(u & 0xffff0000u));
+}
+__device__ inline __attribute__((always_inline)) float2 widen(const uint2& u) {
+  return make_float2(__uint_as_float(u.x), __uint_as_float(u.y));
+}
+
+// The slice positions this wave loads: 32-bit byte offsets within a frame (kOutside, which the
 // buffer unit reads as zero, outside the grid or the channel range), computed once per brick.
-template <int KT, int KH, int KW>
+template <bool BF16, int KT, int KH, int KW>
 __device__ inline void slice_offsets(const ConvGeometry& g, int i0, int j0, int c, int wave,
                                      uint32_t (&off)[SliceShape<KT, KH, KW>::PER_WAVE]) {
   using RG = SliceShape<KT, KH, KW>;
@@ -317,7 +356,8 @@ __device__ inline void slice_offsets(const ConvGeometry& g, int i0, int j0, int 
     const int ii = i0 - rh + y, jj = j0 - rw + x;
     const bool in = pos < RG::POS && c < g.C && (unsigned)ii < (unsigned)g.H &&
                     (unsigned)jj < (unsigned)g.W;
-    off[k] = in ? (uint32_t)(((uint32_t)ii * g.W + jj) * (uint32_t)g.C + c) * 2u : 0xffffffffu;
+    off[k] = in ? (uint32_t)(((uint32_t)ii * g.W + jj) * (uint32_t)g.C + c) * (BF16 ? 2u : 4u)
+                : kOutside;
   }
 }
 
@@ -331,43 +371,56 @@ __device__ inline __attribute__((always_inline)) __amdgpu_buffer_rsrc_t frame_rs
       kBufferFlags);
 }
 
-template <int KT, int KH, int KW>
+template <bool BF16, int KT, int KH, int KW>
 __device__ inline __attribute__((always_inline)) void load_slice(
     const char* batch_base, int frame_bytes, int f, int T,
-    const uint32_t (&off)[SliceShape<KT, KH, KW>::PER_WAVE], uint32_t (&v)[SliceShape<KT, KH, KW>::PER_WAVE]) {
+    const uint32_t (&off)[SliceShape<KT, KH, KW>::PER_WAVE],
+    pair_t<BF16> (&v)[SliceShape<KT, KH, KW>::PER_WAVE]) {
   const __amdgpu_buffer_rsrc_t r = frame_rsrc(batch_base, frame_bytes, f, T);
 #pragma unroll
-  for (int k = 0; k < SliceShape<KT, KH, KW>::PER_WAVE; ++k)
-    v[k] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off[k], 0, 0);
+  for (int k = 0; k < SliceShape<KT, KH, KW>::PER_WAVE; ++k) v[k] = load_pair<BF16>(r, off[k]);
 }
 
-__device__ inline __attribute__((always_inline)) float2 bf16x2(uint32_t u) {
-  return make_float2(__uint_as_float(u << 16), __uint_as_float(u & 0xffff0000u));
+// Frames [t0, t1) of segment seg.
+__device__ inline __attribute__((always_inline)) void segment(const ConvGeometry& g, int seg,
+                                                              int& t0, int& t1) {
+  t0 = seg * g.seg_frames;
+  t1 = min(t0 + g.seg_frames, g.T);
 }
 
-// out = conv(in) [+ bias] [+ out] for bf16 `in`; bricks ordered chunk, batch, row quad, strip.
+// out = conv(in) [+ bias] [+ out]; bricks ordered chunk, batch, segment, row quad, strip.
 // The brick walks the input frames once: slice s (its rows and columns plus the filter halo)
 // sits in LDS buffer s & 1, each wave widens the KH rows it needs to fp32 once, and adds them
 // through filter plane a into output frame s + rt - a, for every a.  The KT output frames in
 // progress are held in registers and shift down by one slot per slice; frame t is stored once
 // slice t + rt has been added.
-template <bool OUT_BF16, bool FLIP, int KT, int KH, int KW>
+// SEG: the frames are cut into segments (walking all of them from frame 0 is kept apart, as the
+// bounds cost the loop 6-10%: 1.91 -> 2.10 ms at 64x68x120x3072).
+template <bool BF16, bool OUT_BF16, bool FLIP, bool SEG, int KT, int KH, int KW>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2))) void dwconv_stream_kernel(
     ConvGeometry g, const void* __restrict__ in, const float* __restrict__ w,
     const float* __restrict__ bias, void* __restrict__ out, int accumulate, int bricks) {
   using RG = SliceShape<KT, KH, KW>;
   static_assert(KT == 1 || KT == 3, "time extent 1 or 3");
-  __shared__ uint32_t slices[2][RG::POS * 64];
+  typedef pair_t<BF16> Pair;
+  __shared__ Pair slices[2][RG::POS * 64];
   constexpr int OS = OUT_BF16 ? 2 : 4;
   constexpr int rt = (KT - 1) / 2;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int frame_bytes = g.H * g.W * g.C * 2;  // below 2^31 on this path
+  const int frame_bytes = g.H * g.W * g.C * (BF16 ? 2 : 4);  // below 2^31 on this path
   for (int brick = xcd_tile(blockIdx.x, gridDim.x); brick < bricks; brick += gridDim.x) {
     const int strip = brick % g.strips;
     int r = brick / g.strips;
     const int iq = r % g.hq;
     r /= g.hq;
+    int t0 = 0, t1 = g.T;
+    if constexpr (SEG) {
+      segment(g, r % g.segs, t0, t1);
+      r /= g.segs;
+    }
     const int b = r % g.B, cc = r / g.B;
+    // slices [s0, s1): the segment's frames and the filter's halo inside the grid
+    const int s0 = SEG ? max(t0 - rt, 0) : 0, s1 = SEG ? min(t1 + rt, g.T) : g.T;
     const int c = cc * kChunk + 2 * lane;
     const bool active = c < g.C;
     const int i0 = iq * kRows, j0 = strip * kTok, i = i0 + wave;
@@ -381,7 +434,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
     float2 b2 = make_float2(0.0f, 0.0f);
     if (bias != nullptr && active) b2 = make_float2(bias[c], bias[c + 1]);
     uint32_t off[RG::PER_WAVE];
-    slice_offsets<KT, KH, KW>(g, i0, j0, c, wave, off);
+    slice_offsets<BF16, KT, KH, KW>(g, i0, j0, c, wave, off);
     const char* base = static_cast<const char*>(in) + (int64_t)b * g.T * frame_bytes;
     char* obase = static_cast<char*>(out) + (int64_t)b * g.T * g.H * g.W * g.C * OS;
 
@@ -392,7 +445,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
     for (int sl = 0; sl < KT; ++sl)
 #pragma unroll
       for (int k = 0; k < kTok; ++k) acc[sl][k] = b2;
-    auto put = [&](int buf, const uint32_t (&v)[RG::PER_WAVE]) {
+    auto put = [&](int buf, const Pair (&v)[RG::PER_WAVE]) {
 #pragma unroll
       for (int k = 0; k < RG::PER_WAVE; ++k) {
         const int pos = wave + kWavesPerBlock * k;
@@ -419,28 +472,28 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
           *reinterpret_cast<float2*>(o) = v;
       }
     };
-    uint32_t nxt[RG::PER_WAVE];
-    load_slice<KT, KH, KW>(base, frame_bytes, 0, g.T, off, nxt);
-    put(0, nxt);  // the previous brick ended on a barrier after its last read
-    if (g.T > 1) load_slice<KT, KH, KW>(base, frame_bytes, 1, g.T, off, nxt);
+    Pair nxt[RG::PER_WAVE];
+    load_slice<BF16, KT, KH, KW>(base, frame_bytes, s0, g.T, off, nxt);
+    put(s0 & 1, nxt);  // the previous brick ended on a barrier after its last read
+    if (s0 + 1 < s1) load_slice<BF16, KT, KH, KW>(base, frame_bytes, s0 + 1, g.T, off, nxt);
     __syncthreads();
 #pragma unroll 1
-    for (int s = 0; s < g.T; ++s) {
+    for (int s = s0; s < s1; ++s) {
       // store slice s + 1, request slice s + 2, add slice s
-      if (s + 1 < g.T) {
+      if (s + 1 < s1) {
         put((s + 1) & 1, nxt);
-        if (s + 2 < g.T) load_slice<KT, KH, KW>(base, frame_bytes, s + 2, g.T, off, nxt);
+        if (s + 2 < s1) load_slice<BF16, KT, KH, KW>(base, frame_bytes, s + 2, g.T, off, nxt);
       }
-      const uint32_t* cur = slices[s & 1];
+      const Pair* cur = slices[s & 1];
 #pragma unroll
       for (int e = 0; e < KH; ++e) {
-        const uint32_t* src = cur + (wave + e) * RG::RX * 64 + lane;
+        const Pair* src = cur + (wave + e) * RG::RX * 64 + lane;
         float2 xv[RG::RX];
 #pragma unroll
-        for (int x = 0; x < RG::RX; ++x) xv[x] = bf16x2(src[x * 64]);
+        for (int x = 0; x < RG::RX; ++x) xv[x] = widen(src[x * 64]);
 #pragma unroll
         for (int a = 0; a < KT; ++a) {
-          if (s + rt - a >= g.T) continue;  // that output frame is past the end
+          if (s + rt - a >= t1) continue;  // that output frame is past the end
 #pragma unroll
           for (int f = 0; f < KW; ++f) {
             const float2 wv = wt[(a * KH + e) * KW + f];
@@ -453,7 +506,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         }
         asm volatile("" ::: "memory");  // one row's reads in flight at a time (registers)
       }
-      if (s - rt >= 0) emit(s - rt);
+      if (s - rt >= t0) emit(s - rt);
 #pragma unroll
       for (int sl = 0; sl + 1 < KT; ++sl)
 #pragma unroll
@@ -462,53 +515,60 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
       for (int k = 0; k < kTok; ++k) acc[KT - 1][k] = b2;
       __syncthreads();  // slice s is read; its buffer takes slice s + 2 next
     }
-    // frames T - rt .. T - 1 are complete after the last slice (slots 0 .. rt - 1)
-    if constexpr (rt == 1) emit(g.T - 1);
+    // the grid's last frame has no slice after it (slot 0 after the shift)
+    if constexpr (rt == 1)
+      if (!SEG || t1 == g.T) emit(g.T - 1);
   }
 }
 
 // Weight and bias gradient partial sums on the streaming path: one brick per block; wave w of
-// brick (cc, b, iq, strip) writes slot ((b * hq + iq) * strips + strip) * 4 + w, its sums
-// over all frames of its row of the brick.  As in the forward, the x slices are walked once
+// brick (cc, b, seg, iq, strip) writes slot (((b * segs + seg) * hq + iq) * strips + strip) * 4 + w,
+// its sums over the frames of its segment and its row of the brick.  As in the forward, the x slices are walked once
 // (LDS buffer s & 1, each row widened once per wave): slice s meets dy frame s + rt - a through
 // filter plane a, and the KT dy frames in use are held in registers (slot j: frame s - rt + j),
 // shifting down by one per slice.
-template <int KT, int KH, int KW>
+template <bool BF16, int KT, int KH, int KW>
 __global__ __launch_bounds__(kBlockThreads) void dwconv_stream_wgrad_kernel(
     ConvGeometry g, const void* __restrict__ x, const void* __restrict__ dy,
     float* __restrict__ part, float* __restrict__ part_b) {
   using RG = SliceShape<KT, KH, KW>;
   static_assert(KT == 1 || KT == 3, "time extent 1 or 3");
-  __shared__ uint32_t slices[2][RG::POS * 64];
+  typedef pair_t<BF16> Pair;
+  __shared__ Pair slices[2][RG::POS * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   constexpr int rt = (KT - 1) / 2;
-  const int frame_bytes = g.H * g.W * g.C * 2;  // below 2^31 on this path
+  const int frame_bytes = g.H * g.W * g.C * (BF16 ? 2 : 4);  // below 2^31 on this path
   const int brick = xcd_tile(blockIdx.x, gridDim.x);
   const int strip = brick % g.strips;
   int r = brick / g.strips;
   const int iq = r % g.hq;
   r /= g.hq;
+  const int seg = r % g.segs;
+  int t0, t1;
+  segment(g, seg, t0, t1);
+  r /= g.segs;
   const int b = r % g.B, cc = r / g.B;
+  const int s0 = max(t0 - rt, 0), s1 = min(t1 + rt, g.T);  // x slices
   const int c = cc * kChunk + 2 * lane;
   const bool active = c < g.C;
   const int i0 = iq * kRows, j0 = strip * kTok, i = i0 + wave;
   uint32_t off[RG::PER_WAVE];
-  slice_offsets<KT, KH, KW>(g, i0, j0, c, wave, off);
-  // this wave's dy row: 8 tokens at byte offsets within a frame (UINT32_MAX outside)
+  slice_offsets<BF16, KT, KH, KW>(g, i0, j0, c, wave, off);
+  // this wave's dy row: 8 tokens at byte offsets within a frame (kOutside outside)
   uint32_t doff[kTok];
 #pragma unroll
   for (int k = 0; k < kTok; ++k)
     doff[k] = (active && i < g.H && j0 + k < g.W)
-                  ? (uint32_t)(((uint32_t)i * g.W + j0 + k) * (uint32_t)g.C + c) * 2u
-                  : 0xffffffffu;
+                  ? (uint32_t)(((uint32_t)i * g.W + j0 + k) * (uint32_t)g.C + c) * (BF16 ? 2u : 4u)
+                  : kOutside;
   const char* xbase = static_cast<const char*>(x) + (int64_t)b * g.T * frame_bytes;
   const char* dbase = static_cast<const char*>(dy) + (int64_t)b * g.T * frame_bytes;
-  auto load_dy = [&](int f, uint32_t (&v)[kTok]) {  // zeros outside [0, T)
-    const __amdgpu_buffer_rsrc_t rs = frame_rsrc(dbase, frame_bytes, f, g.T);
+  auto load_dy = [&](int f, Pair (&v)[kTok]) {  // zeros outside the segment
+    const __amdgpu_buffer_rsrc_t rs = frame_rsrc(dbase, frame_bytes, f < t0 || f >= t1 ? -1 : f, g.T);
 #pragma unroll
-    for (int k = 0; k < kTok; ++k) v[k] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)doff[k], 0, 0);
+    for (int k = 0; k < kTok; ++k) v[k] = load_pair<BF16>(rs, doff[k]);
   };
-  auto put = [&](int buf, const uint32_t (&v)[RG::PER_WAVE]) {
+  auto put = [&](int buf, const Pair (&v)[RG::PER_WAVE]) {
 #pragma unroll
     for (int k = 0; k < RG::PER_WAVE; ++k) {
       const int pos = wave + kWavesPerBlock * k;
@@ -519,48 +579,46 @@ __global__ __launch_bounds__(kBlockThreads) void dwconv_stream_wgrad_kernel(
 #pragma unroll
   for (int tap = 0; tap < RG::TAPS; ++tap) acc[tap] = make_float2(0.0f, 0.0f);
   float2 db = make_float2(0.0f, 0.0f);
-  // dy window: slot j = frame s - rt + j (frames below 0 are zero)
+  // dy window: slot j = frame s - rt + j (frames outside the segment are zero)
   float2 d[KT][kTok];
 #pragma unroll
   for (int j = 0; j < KT; ++j) {
-    uint32_t v[kTok];
-    load_dy(j - rt, v);
+    Pair v[kTok];
+    load_dy(s0 + j - rt, v);
 #pragma unroll
     for (int k = 0; k < kTok; ++k) {
-      d[j][k] = bf16x2(v[k]);
-      if (j >= rt) {  // frames 0 .. rt enter the bias sum here, later ones as they arrive
-        db.x += d[j][k].x;
-        db.y += d[j][k].y;
-      }
+      d[j][k] = widen(v[k]);  // these frames enter the bias sum here, later ones as they arrive
+      db.x += d[j][k].x;
+      db.y += d[j][k].y;
     }
   }
-  uint32_t dnxt[kTok];
-  load_dy(rt + 1, dnxt);
-  uint32_t nxt[RG::PER_WAVE];
-  load_slice<KT, KH, KW>(xbase, frame_bytes, 0, g.T, off, nxt);
-  put(0, nxt);
-  if (g.T > 1) load_slice<KT, KH, KW>(xbase, frame_bytes, 1, g.T, off, nxt);
+  Pair dnxt[kTok];
+  load_dy(s0 + rt + 1, dnxt);
+  Pair nxt[RG::PER_WAVE];
+  load_slice<BF16, KT, KH, KW>(xbase, frame_bytes, s0, g.T, off, nxt);
+  put(s0 & 1, nxt);
+  if (s0 + 1 < s1) load_slice<BF16, KT, KH, KW>(xbase, frame_bytes, s0 + 1, g.T, off, nxt);
   __syncthreads();
 #pragma unroll 1
-  for (int s = 0; s < g.T; ++s) {
-    if (s + 1 < g.T) {
+  for (int s = s0; s < s1; ++s) {
+    if (s + 1 < s1) {
       put((s + 1) & 1, nxt);
-      if (s + 2 < g.T) load_slice<KT, KH, KW>(xbase, frame_bytes, s + 2, g.T, off, nxt);
+      if (s + 2 < s1) load_slice<BF16, KT, KH, KW>(xbase, frame_bytes, s + 2, g.T, off, nxt);
     }
-    const uint32_t* cur = slices[s & 1];
+    const Pair* cur = slices[s & 1];
 #pragma unroll
     for (int e = 0; e < KH; ++e) {
-      const uint32_t* src = cur + (wave + e) * RG::RX * 64 + lane;
+      const Pair* src = cur + (wave + e) * RG::RX * 64 + lane;
       float2 xv[RG::RX];
 #pragma unroll
-      for (int q = 0; q < RG::RX; ++q) xv[q] = bf16x2(src[q * 64]);
+      for (int q = 0; q < RG::RX; ++q) xv[q] = widen(src[q * 64]);
 #pragma unroll
       for (int a = 0; a < KT; ++a) {
 #pragma unroll
         for (int f = 0; f < KW; ++f)
 #pragma unroll
           for (int k = 0; k < kTok; ++k) {
-            const float2 dv = d[KT - 1 - a][k];  // dy frame s + rt - a (zero outside the grid)
+            const float2 dv = d[KT - 1 - a][k];  // dy frame s + rt - a (zero outside the segment)
             acc[(a * KH + e) * KW + f].x = fmaf(dv.x, xv[k + f].x, acc[(a * KH + e) * KW + f].x);
             acc[(a * KH + e) * KW + f].y = fmaf(dv.y, xv[k + f].y, acc[(a * KH + e) * KW + f].y);
           }
@@ -574,7 +632,7 @@ __global__ __launch_bounds__(kBlockThreads) void dwconv_stream_wgrad_kernel(
       for (int k = 0; k < kTok; ++k) d[j][k] = d[j + 1][k];
 #pragma unroll
     for (int k = 0; k < kTok; ++k) {
-      d[KT - 1][k] = bf16x2(dnxt[k]);
+      d[KT - 1][k] = widen(dnxt[k]);
       db.x += d[KT - 1][k].x;
       db.y += d[KT - 1][k].y;
     }
@@ -582,7 +640,8 @@ __global__ __launch_bounds__(kBlockThreads) void dwconv_stream_wgrad_kernel(
     __syncthreads();  // slice s is read; its buffer takes slice s + 2 next
   }
   if (!active) return;
-  const int64_t slot = (((int64_t)b * g.hq + iq) * g.strips + strip) * kWavesPerBlock + wave;
+  const int64_t slot =
+      ((((int64_t)b * g.segs + seg) * g.hq + iq) * g.strips + strip) * kWavesPerBlock + wave;
   float* pc0 = part + (slot * g.C + c) * RG::TAPS;
   float* pc1 = pc0 + RG::TAPS;
 #pragma unroll
@@ -666,25 +725,29 @@ hipError_t wgrad_kh(const ConvGeometry& g, const void* x, const void* dy, float*
   }
 }
 
-int stream_bricks(const ConvGeometry& g) { return g.chunks * g.B * g.hq * g.strips; }
+int stream_bricks(const ConvGeometry& g) { return g.chunks * g.B * g.segs * g.hq * g.strips; }
 
-template <bool OUT_BF16, bool FLIP, int KT, int KH, int KW>
+template <bool BF16, bool OUT_BF16, bool FLIP, int KT, int KH, int KW>
 hipError_t launch_stream(const ConvGeometry& g, const void* in, const float* w, const float* bias,
                          void* out, int accumulate, hipStream_t s) {
   const int bricks = stream_bricks(g);
   const int blocks = bricks < kMaxBlocks ? bricks : kMaxBlocks;
   void* a[] = {(void*)&g, (void*)&in, (void*)&w, (void*)&bias, (void*)&out, (void*)&accumulate,
                (void*)&bricks};
-  return hipLaunchKernel(
-      reinterpret_cast<const void*>(&dwconv_stream_kernel<OUT_BF16, FLIP, KT, KH, KW>),
-      dim3(blocks), dim3(kBlockThreads), a, 0, s);
+  const void* kern =
+      g.segs > 1
+          ? reinterpret_cast<const void*>(
+                &dwconv_stream_kernel<BF16, OUT_BF16, FLIP, true, KT, KH, KW>)
+          : reinterpret_cast<const void*>(
+                &dwconv_stream_kernel<BF16, OUT_BF16, FLIP, false, KT, KH, KW>);
+  return hipLaunchKernel(kern, dim3(blocks), dim3(kBlockThreads), a, 0, s);
 }
 
-template <int KT, int KH, int KW>
+template <bool BF16, int KT, int KH, int KW>
 hipError_t launch_stream_wgrad(const ConvGeometry& g, const void* x, const void* dy, float* part,
                                float* part_b, hipStream_t s) {
   void* a[] = {(void*)&g, (void*)&x, (void*)&dy, (void*)&part, (void*)&part_b};
-  return hipLaunchKernel(reinterpret_cast<const void*>(&dwconv_stream_wgrad_kernel<KT, KH, KW>),
+  return hipLaunchKernel(reinterpret_cast<const void*>(&dwconv_stream_wgrad_kernel<BF16, KT, KH, KW>),
                          dim3(stream_bricks(g)), dim3(kBlockThreads), a, 0, s);
 }
 
@@ -692,22 +755,23 @@ hipError_t launch_stream_wgrad(const ConvGeometry& g, const void* x, const void*
 #define DSA3D_STREAM_SHAPES(X) \
   X(1, 1, 1) X(1, 1, 3) X(1, 3, 1) X(1, 3, 3) X(3, 1, 1) X(3, 1, 3) X(3, 3, 1) X(3, 3, 3)
 
-template <bool OUT_BF16, bool FLIP>
+template <bool BF16, bool OUT_BF16, bool FLIP>
 hipError_t stream_conv(const ConvGeometry& g, const void* in, const float* w, const float* bias,
                        void* out, int accumulate, hipStream_t s) {
 #define DSA3D_CASE(KT, KH, KW)                    \
   if (g.kt == KT && g.kh == KH && g.kw == KW)     \
-    return launch_stream<OUT_BF16, FLIP, KT, KH, KW>(g, in, w, bias, out, accumulate, s);
+    return launch_stream<BF16, OUT_BF16, FLIP, KT, KH, KW>(g, in, w, bias, out, accumulate, s);
   DSA3D_STREAM_SHAPES(DSA3D_CASE)
 #undef DSA3D_CASE
   return hipErrorInvalidValue;
 }
 
+template <bool BF16>
 hipError_t stream_wgrad(const ConvGeometry& g, const void* x, const void* dy, float* part,
                         float* part_b, hipStream_t s) {
 #define DSA3D_CASE(KT, KH, KW)                \
   if (g.kt == KT && g.kh == KH && g.kw == KW) \
-    return launch_stream_wgrad<KT, KH, KW>(g, x, dy, part, part_b, s);
+    return launch_stream_wgrad<BF16, KT, KH, KW>(g, x, dy, part, part_b, s);
   DSA3D_STREAM_SHAPES(DSA3D_CASE)
 #undef DSA3D_CASE
   return hipErrorInvalidValue;
@@ -720,16 +784,33 @@ hipError_t stream_wgrad(const ConvGeometry& g, const void* x, const void* dy, fl
 // blocks of one (chunk, plane) move through the grid together; at most one per tile.
 constexpr int kWgradBlocksTarget = 768;
 
+// The streaming path's blocks, below which the frames are cut: four per compute unit, about what
+// stays resident.
+constexpr int kStreamBlocks = 1024;
+constexpr int kSegFrames = 4;
+constexpr int kF32Bricks = 4096;
+
 void conv_plan(ConvGeometry& g) {
   g.taps = g.kt * g.kh * g.kw;
-  // the streaming path: bf16 data, every filter extent 1 or 3, frames below 2 GB (a raw buffer
-  // of one frame)
-  g.stream = g.bf16 && g.kt <= 3 && g.kh <= 3 && g.kw <= 3 &&
-             (uint64_t)g.H * g.W * g.C * 2 < 0x7fffffffull;
   g.chunks = (g.C + kChunk - 1) / kChunk;
   g.strips = (g.W + kTok - 1) / kTok;
   g.sg = g.strips < 5 ? g.strips : 5;
   g.hq = (g.H + kRows - 1) / kRows;
+  // Segments of the frames: enough for kStreamBlocks blocks, of at least kSegFrames frames each
+  // (a 3-frame filter reads two more per segment).
+  const int64_t whole = (int64_t)g.chunks * g.B * g.hq * g.strips;
+  const int64_t want_segs = (kStreamBlocks + whole - 1) / whole;
+  const int most = g.T / kSegFrames > 1 ? g.T / kSegFrames : 1;
+  g.segs = (int)(want_segs < most ? want_segs : most);
+  g.seg_frames = (g.T + g.segs - 1) / g.segs;
+  g.segs = (g.T + g.seg_frames - 1) / g.seg_frames;
+  // The streaming path: every filter extent 1 or 3, frames below 2 GB (a raw buffer of one frame).
+  // fp32 grids of very many bricks per chunk stay with the general kernel, whose weight gradient
+  // needs partial sums per resident wave and not per brick.  fp32 at 16x34x60x1024, 3x3x3, general
+  // and streaming: forward 179 -> 96 us, dx 192 -> 96, weight gradient 148 -> 101.
+  g.stream = g.kt <= 3 && g.kh <= 3 && g.kw <= 3 &&
+             (uint64_t)g.H * g.W * g.C * (g.bf16 ? 2 : 4) < 0x7fffffffull &&
+             (g.bf16 || (int64_t)g.B * g.segs * g.hq * g.strips <= kF32Bricks);
   const int bricks = (g.strips + g.sg - 1) / g.sg;
   g.tiles_per_bc = bricks * g.T * g.hq * g.sg;
   const int want = kWgradBlocksTarget / (g.chunks * g.kt);
@@ -740,7 +821,7 @@ void conv_plan(ConvGeometry& g) {
 // Partial-sum slots of the weight-gradient sweep: one per wave of a brick on the streaming path,
 // one per wave of a sweep block otherwise.
 size_t conv_slots(const ConvGeometry& g) {
-  return g.stream ? (size_t)g.B * g.hq * g.strips * kWavesPerBlock
+  return g.stream ? (size_t)g.B * g.segs * g.hq * g.strips * kWavesPerBlock
                   : (size_t)g.wg_blocks * kWavesPerBlock;
 }
 
@@ -753,7 +834,9 @@ size_t conv_workspace_bytes(const ConvGeometry& g) {
 
 hipError_t launch_conv_forward(const ConvGeometry& g, bool bf16, const void* x, const float* w,
                                const float* bias, void* y, int accumulate, hipStream_t s) {
-  if (g.stream) return stream_conv<true, false>(g, x, w, bias, y, accumulate, s);
+  if (g.stream)
+    return bf16 ? stream_conv<true, true, false>(g, x, w, bias, y, accumulate, s)
+                : stream_conv<false, false, false>(g, x, w, bias, y, accumulate, s);
   return bf16 ? conv_kw<true, true, false>(g, x, w, bias, y, accumulate, s)
               : conv_kw<false, false, false>(g, x, w, bias, y, accumulate, s);
 }
@@ -764,7 +847,8 @@ hipError_t launch_conv_backward(const ConvGeometry& g, bool bf16, const void* x,
   hipError_t e = hipSuccess;
   if (dx != nullptr) {
     if (g.stream)
-      e = stream_conv<false, true>(g, dy, w, nullptr, dx, accumulate_dx, s);
+      e = bf16 ? stream_conv<true, false, true>(g, dy, w, nullptr, dx, accumulate_dx, s)
+               : stream_conv<false, false, true>(g, dy, w, nullptr, dx, accumulate_dx, s);
     else
       e = bf16 ? conv_kw<true, false, true>(g, dy, w, nullptr, dx, accumulate_dx, s)
                : conv_kw<false, false, true>(g, dy, w, nullptr, dx, accumulate_dx, s);
@@ -777,18 +861,19 @@ hipError_t launch_conv_backward(const ConvGeometry& g, bool bf16, const void* x,
   float* part_b = reinterpret_cast<float*>(static_cast<char*>(workspace) +
                                            ((part_bytes + 255) & ~size_t(255)));
   if (g.stream)
-    e = stream_wgrad(g, x, dy, part, part_b, s);
+    e = bf16 ? stream_wgrad<true>(g, x, dy, part, part_b, s)
+             : stream_wgrad<false>(g, x, dy, part, part_b, s);
   else
     e = bf16 ? wgrad_kh<true>(g, x, dy, part, part_b, s) : wgrad_kh<false>(g, x, dy, part, part_b, s);
   if (e != hipSuccess) return e;
   const int64_t per_slot = (int64_t)g.C * g.taps, per_slot_b = g.C;
   const int nslots = (int)slots;
   const int64_t n = per_slot + per_slot_b;
-  const int blocks = (int)((n + kBlockThreads - 1) / kBlockThreads);
+  const int blocks = (int)((n + 63) / 64);
   void* a[] = {(void*)&part, (void*)&part_b, (void*)&per_slot, (void*)&per_slot_b,
                (void*)&nslots, (void*)&dw, (void*)&db};
   return hipLaunchKernel(reinterpret_cast<const void*>(&dwconv_wgrad_reduce_kernel), dim3(blocks),
-                         dim3(kBlockThreads), a, 0, s);
+                         dim3(64 * kReduceWaves), a, 0, s);
 }
 
 }  // namespace dsa3d
