@@ -62,9 +62,8 @@ dsa3d_status dsa3d_dwconv3d_forward(const dsa3d_dwconv_desc* desc, const void* x
 
 /* Bytes of device workspace dsa3d_dwconv3d_backward needs for the weight and bias gradients
  * (partial sums of the grid sweep: 4 bytes per channel and tap, and per channel, for each wave
- * slot: with every filter extent 1 or 3 four slots per 4 x 8-token column of the grid, frames
- * together, up to 4096 columns in fp32; else about 3072 / (ceil(C/128) kt) slots); 0 for a
- * descriptor the backward would reject. */
+ * slot: in bf16 with every filter extent 1 or 3 four slots per 4 x 8-token column of the grid;
+ * else about 3072 / (ceil(C/128) kt) slots); 0 for a descriptor the backward would reject. */
 size_t dsa3d_dwconv3d_backward_workspace_size(const dsa3d_dwconv_desc* desc);
 
 /* Backward of dsa3d_dwconv3d_forward for upstream gradient dy:

@@ -33,9 +33,8 @@
 // four neighbouring queries once per sweep (bwd_slots_tile, dsa3d_slots.h): dots of the V rows with
 // dout, of the K rows with q, and the sum of K rows for dq with Delta known.  V and K pass at
 // 16x34x60, 24 heads x 128, 3x7x7, offsets N(0, 1): 23.0 -> 17.5 ms.
-// The predicted-weights variant reads no K: one sweep (phase 1 with the given logits, the
-// bin counts' ranks not kept) and a finalize of one thread per point that claims its slot
-// from a fill cursor take phases 1 and 3.
+// The predicted-weights variant reads no K: one sweep (phase 1 with the given logits) and a finalize
+// of one thread per point take phases 1 and 3.
 #include "dsa3d_slots.h"
 
 namespace dsa3d {
@@ -94,14 +93,16 @@ __device__ inline bool cell_inside(const Geometry& g, int x, int y, int z) {
 // forms point chunk + sub (position, corners, weights, cell), counts it into its bin, and
 // the row's lanes pick the corner indices, fractions and cell up with ds_bpermute; the
 // weights are rebuilt from the fractions with the same products.  Lane `sub` also keeps
-// that point's record (alpha_p and A_p = 0; da_p and B_p), and the row stores the chunk's
-// records as one contiguous block.
+// that point's record (da_p and B_p) and rank, and the row stores the chunk's as contiguous
+// blocks; alpha_p is formed again from the logit by the finalize pass, which then reads 20 bytes
+// per point instead of 32 and claims no slot (with 16-byte alpha records and slots from a cursor:
+// sweep 3.46, finalize 2.16 ms at 64x34x60, 16 heads x 64, 3x3x3).
 template <int D, bool BF16>
 __global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_sweep_kernel(
     Geometry g, const void* __restrict__ v, const float* __restrict__ logits,
     const float* __restrict__ offsets, const float* __restrict__ lse,
-    const void* __restrict__ dout, RecK* __restrict__ reck, RecV* __restrict__ recv,
-    float* __restrict__ delta_out, uint32_t* __restrict__ counts, PencilOrder po) {
+    const void* __restrict__ dout, RecV* __restrict__ recv, float* __restrict__ delta_out,
+    uint32_t* __restrict__ counts, uint32_t* __restrict__ ranks, PencilOrder po, int64_t vt0) {
   using LY = Layout<D, BF16>;
   constexpr int L = LY::kLanes;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -113,97 +114,93 @@ __global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_sweep_k
   const int rt = (g.kt - 1) / 2, rh = (g.kh - 1) / 2, rw = (g.kw - 1) / 2;
   const int khw = g.kh * g.kw;
 
-  for (int64_t vt = blockIdx.x; vt < po.vtiles; vt += gridDim.x) {
-    PencilTile tl;
-    if (!pencil_tile(po, vt, tl)) continue;  // the whole block: no pencil left on this XCD
-    const int bh = tl.group;
-    const int b = bh / g.heads, m = bh % g.heads;
-    const int t = tl.frame;
-    const RowWindow win = make_window<LY::kRowBytes>(g, v, v, b, m, t);  // V rows only
-    int i, j;
-    // All lanes of a group share the token: a whole group is idle or active, so neither the
-    // group reductions nor the point sharing ever mix an idle group into an active one.
-    if (!query_token<false>(po, g, tl, wave * LY::kGroups + grp, i, j)) continue;
-    const int n = t * HW + i * g.W + j;
-    const int64_t row = ((int64_t)b * g.N + n) * g.heads + m;
+  PencilTile tl;
+  if (!pencil_tile(po, vt0 + blockIdx.x, tl)) return;  // the whole block: no pencil left on this XCD
+  const int bh = tl.group;
+  const int b = bh / g.by_heads, m = bh - b * g.heads;
+  const int t = tl.frame;
+  const RowWindow win = make_window<LY::kRowBytes>(g, v, v, b, m, t);  // V rows only
+  int i, j;
+  // All lanes of a group share the token: a whole group is idle or active, so neither the
+  // group reductions nor the point sharing ever mix an idle group into an active one.
+  if (!query_token<false>(po, g, tl, wave * LY::kGroups + grp, i, j)) return;
+  const int n = t * HW + i * g.W + j;
+  const int64_t row = ((int64_t)b * g.N + n) * g.heads + m;
 
-    const uint4 gr = load16(gb, row * LY::kRowBytes + lane_off);
-    const float lse2 = lse[row] * kLog2e;
-    const float* off = offsets + row * g.P * 3;
-    float delta = 0.0f;
+  const uint4 gr = load16(gb, row * LY::kRowBytes + lane_off);
+  const float lse2 = lse[row] * kLog2e;
+  const float* off = offsets + row * g.P * 3;
+  float delta = 0.0f;
 
-    int pm = min(sub, g.P - 1);  // this lane's point of the chunk (clamped in the last one)
-    float ox = off[3 * pm], oy = off[3 * pm + 1], oz = off[3 * pm + 2];
-    for (int p0 = 0; p0 < g.P; p0 += L) {
-      const int it = pm / khw, ih = (pm - it * khw) / g.kw, iw = pm - it * khw - ih * g.kw;
-      Point mine;
-      make_point(g, win, t, i, j, it - rt, ih - rh, iw - rw, ox, oy, oz, mine);
-      const float mylog2 = logits[row * g.P + pm] * kLog2e;  // this lane's point's logit, base 2
-      const bool own = p0 + sub < g.P;
-      if (own && cell_inside(g, mine.cx, mine.cy, mine.cz))  // result unused: no wait
-        __hip_atomic_fetch_add(counts + cell_index(g, bh, mine.cx, mine.cy, mine.cz), 1u,
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      pm = min(p0 + L + sub, g.P - 1);  // next chunk's offsets, in flight during this one
-      ox = off[3 * pm];
-      oy = off[3 * pm + 1];
-      oz = off[3 * pm + 2];
-      const int nk = min(L, g.P - p0);
-      float4 rec0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), rec1 = rec0;
-      for (int kk = 0; kk < nk; ++kk) {
-        const int src = (grp * L + kk) << 2;
-        Point pt;
+  int pm = min(sub, g.P - 1);  // this lane's point of the chunk (clamped in the last one)
+  float ox = off[3 * pm], oy = off[3 * pm + 1], oz = off[3 * pm + 2];
+  for (int p0 = 0; p0 < g.P; p0 += L) {
+    const int it = pm / g.by_khw, rp = pm - it * khw, ih = rp / g.by_kw, iw = rp - ih * g.kw;
+    Point mine;
+    make_point(g, win, t, i, j, it - rt, ih - rh, iw - rw, ox, oy, oz, mine);
+    const float mylog2 = logits[row * g.P + pm] * kLog2e;  // this lane's point's logit, base 2
+    const bool own = p0 + sub < g.P;
+    uint32_t rank = 0u;  // the point's rank in its bin, as in the V pass
+    if (own && cell_inside(g, mine.cx, mine.cy, mine.cz))
+      rank = __hip_atomic_fetch_add(counts + cell_index(g, bh, mine.cx, mine.cy, mine.cz), 1u,
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    pm = min(p0 + L + sub, g.P - 1);  // next chunk's offsets, in flight during this one
+    ox = off[3 * pm];
+    oy = off[3 * pm + 1];
+    oz = off[3 * pm + 2];
+    const int nk = min(L, g.P - p0);
+    float4 rec = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int kk = 0; kk < nk; ++kk) {
+      const int src = (grp * L + kk) << 2;
+      Point pt;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) pt.vidx[c] = __builtin_amdgcn_ds_bpermute(src, mine.vidx[c]);
-        const float tx = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(mine.ax[1])));
-        const float ty = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(mine.ay[1])));
-        const float tz = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(mine.az[1])));
-        pt.ax[0] = 1.0f - tx;
-        pt.ax[1] = tx;
-        pt.ay[0] = 1.0f - ty;
-        pt.ay[1] = ty;
-        pt.az[0] = 1.0f - tz;
-        pt.az[1] = tz;
-        {
-          const float wyz[4] = {pt.ay[0] * pt.az[0], pt.ay[1] * pt.az[0], pt.ay[0] * pt.az[1],
-                                pt.ay[1] * pt.az[1]};
+      for (int c = 0; c < 8; ++c) pt.vidx[c] = __builtin_amdgcn_ds_bpermute(src, mine.vidx[c]);
+      const float tx = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(mine.ax[1])));
+      const float ty = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(mine.ay[1])));
+      const float tz = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(mine.az[1])));
+      pt.ax[0] = 1.0f - tx;
+      pt.ax[1] = tx;
+      pt.ay[0] = 1.0f - ty;
+      pt.ay[1] = ty;
+      pt.az[0] = 1.0f - tz;
+      pt.az[1] = tz;
+      {
+        const float wyz[4] = {pt.ay[0] * pt.az[0], pt.ay[1] * pt.az[0], pt.ay[0] * pt.az[1],
+                              pt.ay[1] * pt.az[1]};
 #pragma unroll
-          for (int c = 0; c < 8; ++c) pt.w[c] = pt.ax[c & 1] * wyz[c >> 1];
-        }
-        uint4 vr[8];
-        load_shared_corners<LY::kRowBytes, false>(g, win, vb, vb, b, m, lane_off, mine, src,
-                                                  pt.vidx, nullptr, vr);
-        float dap = 0.0f, b3[3] = {0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          const int cx = c & 1, cy = (c >> 1) & 1, cz = c >> 2;
-          const float dvv = chunk_dot<BF16>(gr, vr[c]);
-          dap = fmaf(pt.w[c], dvv, dap);
-          // d w_c / d pos along each axis (corners outside the grid have zero rows, so zero dots)
-          const float wx = cx ? pt.ay[cy] * pt.az[cz] : -(pt.ay[cy] * pt.az[cz]);
-          const float wy = cy ? pt.ax[cx] * pt.az[cz] : -(pt.ax[cx] * pt.az[cz]);
-          const float wz = cz ? pt.ax[cx] * pt.ay[cy] : -(pt.ax[cx] * pt.ay[cy]);
-          b3[0] = fmaf(wx, dvv, b3[0]);
-          b3[1] = fmaf(wy, dvv, b3[1]);
-          b3[2] = fmaf(wz, dvv, b3[2]);
-        }
-        const float alpha =
-            exp2f(__int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(mylog2))) - lse2);
-        const float da = group_sum<L>(dap);
-        delta = fmaf(alpha, da, delta);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) b3[a] = group_sum<L>(b3[a]);
-        if (sub == kk) {
-          rec0 = make_float4(alpha, 0.0f, 0.0f, 0.0f);
-          rec1 = make_float4(da, b3[0], b3[1], b3[2]);
-        }
+        for (int c = 0; c < 8; ++c) pt.w[c] = pt.ax[c & 1] * wyz[c >> 1];
       }
-      if (own) {
-        *reinterpret_cast<float4*>(reck + row * g.P + p0 + sub) = rec0;
-        *reinterpret_cast<float4*>(recv + row * g.P + p0 + sub) = rec1;
+      uint4 vr[8];
+      load_shared_corners<LY::kRowBytes, false>(g, win, vb, vb, b, m, lane_off, mine, src,
+                                                pt.vidx, nullptr, vr);
+      float dap = 0.0f, b3[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const int cx = c & 1, cy = (c >> 1) & 1, cz = c >> 2;
+        const float dvv = chunk_dot<BF16>(gr, vr[c]);
+        dap = fmaf(pt.w[c], dvv, dap);
+        // d w_c / d pos along each axis (corners outside the grid have zero rows, so zero dots)
+        const float wx = cx ? pt.ay[cy] * pt.az[cz] : -(pt.ay[cy] * pt.az[cz]);
+        const float wy = cy ? pt.ax[cx] * pt.az[cz] : -(pt.ax[cx] * pt.az[cz]);
+        const float wz = cz ? pt.ax[cx] * pt.ay[cy] : -(pt.ax[cx] * pt.ay[cy]);
+        b3[0] = fmaf(wx, dvv, b3[0]);
+        b3[1] = fmaf(wy, dvv, b3[1]);
+        b3[2] = fmaf(wz, dvv, b3[2]);
       }
+      const float alpha =
+          exp2f(__int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(mylog2))) - lse2);
+      const float da = group_sum<L>(dap);
+      delta = fmaf(alpha, da, delta);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) b3[a] = group_sum<L>(b3[a]);
+      if (sub == kk) rec = make_float4(da, b3[0], b3[1], b3[2]);
     }
-    if (sub == 0) delta_out[row] = delta;
+    if (own) {
+      *reinterpret_cast<float4*>(recv + row * g.P + p0 + sub) = rec;
+      ranks[row * g.P + p0 + sub] = rank;
+    }
   }
+  if (sub == 0) delta_out[row] = delta;
 }
 
 // ---------------------------------------------------------------------------- 1b. split sweep
@@ -1034,11 +1031,10 @@ __global__ __launch_bounds__(kScanThreads) void scan_sums_kernel(uint32_t* __res
   if (threadIdx.x == 0) *grand = carry;
 }
 
-// starts[x] = cursor[x] = offset of block + exclusive scan inside the block.
+// starts[x] = offset of block + exclusive scan inside the block.
 __global__ __launch_bounds__(kScanThreads) void scan_apply_kernel(const uint32_t* __restrict__ in,
                                                                    const uint32_t* __restrict__ sums,
                                                                    uint32_t* __restrict__ out,
-                                                                   uint32_t* __restrict__ cursor,
                                                                    int64_t n) {
   __shared__ uint32_t lds[kScanThreads / 64];
   const int64_t base = (int64_t)blockIdx.x * kScanBlockItems + (int64_t)threadIdx.x * kScanItems;
@@ -1054,62 +1050,52 @@ __global__ __launch_bounds__(kScanThreads) void scan_apply_kernel(const uint32_t
   uint32_t run = sums[blockIdx.x] + excl;
 #pragma unroll
   for (int e = 0; e < kScanItems; ++e) {
-    if (base + e < n) {
-      out[base + e] = run;
-      cursor[base + e] = run;
-    }
+    if (base + e < n) out[base + e] = run;
     run += vals[e];
   }
 }
 
 // ---------------------------------------------------------------------------- 3. finalize
 
-// dlogits (the predicted-weights variant, else null) receives alpha_p (da_p - Delta).
+// The predicted-weights variant's points, one thread each: d_offsets, dlogits = alpha_p (da_p -
+// Delta) and the entry at its bin's start + its rank.
+struct FinalizeDivs {
+  FastDiv P, N, HW, W;
+};
+
 __global__ __launch_bounds__(kBlockThreads) void bwd_finalize_kernel(
-    Geometry g, const float* __restrict__ offsets, const RecK* __restrict__ reck,
-    const RecV* __restrict__ recv,
-    const float* __restrict__ delta, uint32_t* __restrict__ cursor, float* __restrict__ doff,
-    float* __restrict__ dlogits, Entry* __restrict__ entries, int npoints) {
+    Geometry g, FinalizeDivs by, const float* __restrict__ offsets,
+    const float* __restrict__ logits, const float* __restrict__ lse,
+    const RecV* __restrict__ recv, const float* __restrict__ delta,
+    const uint32_t* __restrict__ starts, const uint32_t* __restrict__ ranks,
+    float* __restrict__ doff, float* __restrict__ dlogits, Entry* __restrict__ entries,
+    int npoints) {
   const int rt = (g.kt - 1) / 2, rh = (g.kh - 1) / 2, rw = (g.kw - 1) / 2;
-  const unsigned P = g.P, heads = g.heads, N = g.N, W = g.W, HW = g.H * g.W;
-  for (unsigned idx = blockIdx.x * blockDim.x + threadIdx.x; idx < (unsigned)npoints;
-       idx += gridDim.x * blockDim.x) {
-    const unsigned row = idx / P;
-    const unsigned p = idx - row * P;
-    const RecK rk = reck[idx];
+  const int HW = g.H * g.W;
+  for (int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; at < npoints;
+       at += (int64_t)gridDim.x * blockDim.x) {
+    const int idx = (int)at, row = idx / by.P, p = idx - row * g.P;
     const RecV rv = recv[idx];
+    const float alpha = exp2f(logits[idx] * kLog2e - lse[row] * kLog2e);
     const float dd = rv.dalpha - delta[row];
-    float* d = doff + (size_t)idx * 3;
-    const float sa = g.scale * dd;
-    d[0] = rk.alpha * fmaf(sa, rk.ax, rv.bx);
-    d[1] = rk.alpha * fmaf(sa, rk.ay, rv.by);
-    d[2] = rk.alpha * fmaf(sa, rk.az, rv.bz);
-    if (dlogits != nullptr) dlogits[idx] = rk.alpha * dd;
-    const unsigned tok = row / heads;
-    const unsigned m = row - tok * heads;
-    const unsigned b = tok / N;
-    const unsigned n = tok - b * N;
-    const unsigned t = n / HW;
-    const unsigned rem = n - t * HW;
-    const unsigned i = rem / W;
-    const unsigned j = rem - i * W;
-    const unsigned iw = p % g.kw, ih = (p / g.kw) % g.kh, it = p / (g.kw * g.kh);
-    const float* o = offsets + (size_t)idx * 3;
+    float* d = doff + at * 3;
+    d[0] = alpha * rv.bx;
+    d[1] = alpha * rv.by;
+    d[2] = alpha * rv.bz;
+    dlogits[idx] = alpha * dd;
+    const int tok = row / g.by_heads, m = row - tok * g.heads;
+    const int b = tok / by.N, n = tok - b * g.N;
+    const int t = n / by.HW, rem = n - t * HW, i = rem / by.W, j = rem - i * g.W;
+    const int it = p / g.by_khw, rp = p - it * (g.kh * g.kw), ih = rp / g.by_kw, iw = rp - ih * g.kw;
+    const float* o = offsets + at * 3;
     int x, y, z;
     float fx, fy, fz;
-    axis((float)((int)j + (int)iw - rw), o[0], g.W, x, fx);
-    axis((float)((int)i + (int)ih - rh), o[1], g.H, y, fy);
-    axis((float)((int)t + (int)it - rt), o[2], g.T, z, fz);
+    axis((float)(j + iw - rw), o[0], g.W, x, fx);
+    axis((float)(i + ih - rh), o[1], g.H, y, fy);
+    axis((float)(t + it - rt), o[2], g.T, z, fz);
     if (!cell_inside(g, x, y, z)) continue;
-    const uint32_t slot = atomicAdd(cursor + cell_index(g, b * heads + m, x, y, z), 1u);
-    Entry e;
-    e.n = (int32_t)n;
-    e.alpha = rk.alpha;
-    e.sds = g.scale * rk.alpha * dd;
-    e.fx = fx;
-    e.fy = fy;
-    e.fz = fz;
-    entries[slot] = e;
+    const uint32_t slot = starts[cell_index(g, b * g.heads + m, x, y, z)] + ranks[idx];
+    entries[slot] = Entry{n, alpha, alpha * dd, fx, fy, fz};
   }
 }
 
@@ -1606,7 +1592,7 @@ void bwd_gather_mfma_kernel(Geometry g, const void* __restrict__ q, const void* 
 struct Workspace {
   uint32_t* counts;   // [cells]
   uint32_t* starts;   // [cells + 1]
-  uint32_t* cursor;   // [cells]
+  uint32_t* spare;    // [cells]: unused, part of the documented size
   uint32_t* sums;     // [ceil(cells / kScanBlockItems)]
   RecK* reck;         // [rows * P]
   RecV* recv;         // [rows * P]
@@ -1633,7 +1619,7 @@ Workspace carve(const Geometry& g, void* base) {
   };
   w.counts = reinterpret_cast<uint32_t*>(take(cells * 4));
   w.starts = reinterpret_cast<uint32_t*>(take((cells + 1) * 4));
-  w.cursor = reinterpret_cast<uint32_t*>(take(cells * 4));
+  w.spare = reinterpret_cast<uint32_t*>(take(cells * 4));
   w.sums = reinterpret_cast<uint32_t*>(take(nsums * 4));
   w.reck = reinterpret_cast<RecK*>(take(points * sizeof(RecK)));
   w.recv = reinterpret_cast<RecV*>(take(points * sizeof(RecV)));
@@ -1673,7 +1659,6 @@ hipError_t bwd_dispatch(const Geometry& g, const void* q, const void* k, const v
   }
   const int rounds = pw ? 0 : backward_rounds<D, BF16>(g.P);
   const PencilOrder po = query_order<D, BF16>(g, rounds > 0);
-  const int blocks = grid_blocks(po.vtiles);
   // The main operator sweeps the points twice (V pass, then K pass with the finish of each
   // row's points); the predicted-weights variant, which reads no K, sweeps them once and
   // finishes them in the finalize pass.
@@ -1690,11 +1675,13 @@ hipError_t bwd_dispatch(const Geometry& g, const void* q, const void* k, const v
     });
     if (e != hipSuccess) return e;
   } else {
-    void* a[] = {(void*)&g,      (void*)&v,      (void*)&logits,  (void*)&off,
-                 (void*)&lse,    (void*)&dout,   (void*)&w.reck,  (void*)&w.recv,
-                 (void*)&w.delta, (void*)&w.counts, (void*)&po};
-    e = hipLaunchKernel(reinterpret_cast<const void*>(&bwd_sweep_kernel<D, BF16>), dim3(blocks),
-                        dim3(kBlockThreads), a, 0, s);
+    e = launch_tiles(po.vtiles, [&](int64_t vt0, int blocks) {
+      void* a[] = {(void*)&g,      (void*)&v,       (void*)&logits,   (void*)&off,
+                   (void*)&lse,    (void*)&dout,    (void*)&w.recv,   (void*)&w.delta,
+                   (void*)&w.counts, (void*)&w.ranks, (void*)&po,     (void*)&vt0};
+      return hipLaunchKernel(reinterpret_cast<const void*>(&bwd_sweep_kernel<D, BF16>),
+                             dim3(blocks), dim3(kBlockThreads), a, 0, s);
+    });
     if (e != hipSuccess) return e;
   }
   if ((e = mark(1)) != hipSuccess) return e;
@@ -1708,8 +1695,7 @@ hipError_t bwd_dispatch(const Geometry& g, const void* q, const void* k, const v
     e = hipLaunchKernel(reinterpret_cast<const void*>(&scan_sums_kernel), dim3(1),
                         dim3(kScanThreads), b2, 0, s);
     if (e != hipSuccess) return e;
-    void* c3[] = {(void*)&w.counts, (void*)&w.sums, (void*)&w.starts, (void*)&w.cursor,
-                  (void*)&cells};
+    void* c3[] = {(void*)&w.counts, (void*)&w.sums, (void*)&w.starts, (void*)&cells};
     e = hipLaunchKernel(reinterpret_cast<const void*>(&scan_apply_kernel), dim3((unsigned)nsums),
                         dim3(kScanThreads), c3, 0, s);
     if (e != hipSuccess) return e;
@@ -1741,9 +1727,10 @@ hipError_t bwd_dispatch(const Geometry& g, const void* q, const void* k, const v
     if (e != hipSuccess) return e;
   } else {
     const int npoints = (int)points;
-    void* a[] = {(void*)&g,      (void*)&off,     (void*)&w.reck,  (void*)&w.recv,  (void*)&w.delta,
-                 (void*)&w.cursor, (void*)&doff, (void*)&dlogits, (void*)&w.entries,
-                 (void*)&npoints};
+    const FinalizeDivs by = {fast_div(g.P), fast_div(g.N), fast_div(g.H * g.W), fast_div(g.W)};
+    void* a[] = {(void*)&g,        (void*)&by,    (void*)&off,      (void*)&logits, (void*)&lse,
+                 (void*)&w.recv,   (void*)&w.delta, (void*)&w.starts, (void*)&w.ranks,
+                 (void*)&doff,     (void*)&dlogits, (void*)&w.entries, (void*)&npoints};
     e = hipLaunchKernel(reinterpret_cast<const void*>(&bwd_finalize_kernel), dim3(grid_for(points)),
                         dim3(kBlockThreads), a, 0, s);
     if (e != hipSuccess) return e;

@@ -722,12 +722,12 @@ constexpr bool slot_rows_ok() {
 }
 
 // Rounds that a kernel instance numbers together (0: every tile gathers) for rows of P points.
-// Numbering costs a wave the same for 9 points as for 16, which rows of 128 bytes do not earn
-// back: forward at 16x34x60, 24 heads, 1x3x3, 64 bf16 channels: 0.63 ms gathering, 0.90 by slots;
-// 128 channels: 1.14 and 1.06.
+// Numbering costs a wave the same for 9 points as for 16, which a 1x3x3 kernel does not earn
+// back: forward, 24 heads, gathering / by slots: 64 bf16 channels, 16x34x60 0.63 / 0.90 ms; 128
+// channels, 16x34x60 1.14 / 1.06, 3x21x96 (2 heads) 19 / 24 us.
 template <int D, bool BF16>
 inline int forward_rounds(int P) {
-  if (!slot_rows_ok<D, BF16>() || (P < kSlotLanes && !(BF16 && D == 128))) return 0;
+  if (!slot_rows_ok<D, BF16>() || P < kSlotLanes) return 0;
   return P <= 2 * kSlotLanes ? 2 : 5;
 }
 

@@ -521,16 +521,35 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
   }
 }
 
-// Weight and bias gradient partial sums on the streaming path: one brick per block; wave w of
-// brick (cc, b, seg, iq, strip) writes slot (((b * segs + seg) * hq + iq) * strips + strip) * 4 + w,
-// its sums over the frames of its segment and its row of the brick.  As in the forward, the x slices are walked once
-// (LDS buffer s & 1, each row widened once per wave): slice s meets dy frame s + rt - a through
-// filter plane a, and the KT dy frames in use are held in registers (slot j: frame s - rt + j),
-// shifting down by one per slice.
+// A wave's sums over its channels (2 per lane) into slot `slot`.
+template <int TAPS>
+__device__ inline __attribute__((always_inline)) void write_sums(float* __restrict__ part,
+                                                                 float* __restrict__ part_b,
+                                                                 int64_t slot, int C, int c,
+                                                                 const float2 (&acc)[TAPS],
+                                                                 float2 db) {
+  float* pc0 = part + (slot * C + c) * TAPS;
+  float* pc1 = pc0 + TAPS;
+#pragma unroll
+  for (int tap = 0; tap < TAPS; ++tap) {
+    pc0[tap] = acc[tap].x;
+    pc1[tap] = acc[tap].y;
+  }
+  part_b[slot * C + c] = db.x;
+  part_b[slot * C + c + 1] = db.y;
+}
+
+// Weight and bias gradient partial sums on the streaming path.  As in the forward, the x slices are
+// walked once (LDS buffer s & 1, each row widened once per wave): slice s meets dy frame s + rt - a
+// through filter plane a, and the KT dy frames in use are held in registers (slot j: frame s - rt +
+// j), shifting down by one per slice.  A wave sums its row of a unit (b, seg, iq, strip) over the
+// segment's frames.  bf16: one unit per block, and wave w of unit u writes slot 4 u + w.  fp32: the
+// workspace has the general kernel's few slots, so block p of a chunk's `blocks` takes units p,
+// p + blocks, ..., adds its four waves' sums in LDS and writes slot p.
 template <bool BF16, int KT, int KH, int KW>
 __global__ __launch_bounds__(kBlockThreads) void dwconv_stream_wgrad_kernel(
     ConvGeometry g, const void* __restrict__ x, const void* __restrict__ dy,
-    float* __restrict__ part, float* __restrict__ part_b) {
+    float* __restrict__ part, float* __restrict__ part_b, int blocks) {
   using RG = SliceShape<KT, KH, KW>;
   static_assert(KT == 1 || KT == 3, "time extent 1 or 3");
   typedef pair_t<BF16> Pair;
@@ -538,119 +557,138 @@ __global__ __launch_bounds__(kBlockThreads) void dwconv_stream_wgrad_kernel(
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   constexpr int rt = (KT - 1) / 2;
   const int frame_bytes = g.H * g.W * g.C * (BF16 ? 2 : 4);  // below 2^31 on this path
-  const int brick = xcd_tile(blockIdx.x, gridDim.x);
-  const int strip = brick % g.strips;
-  int r = brick / g.strips;
-  const int iq = r % g.hq;
-  r /= g.hq;
-  const int seg = r % g.segs;
-  int t0, t1;
-  segment(g, seg, t0, t1);
-  r /= g.segs;
-  const int b = r % g.B, cc = r / g.B;
-  const int s0 = max(t0 - rt, 0), s1 = min(t1 + rt, g.T);  // x slices
+  const int blk = xcd_tile(blockIdx.x, gridDim.x);
+  const int cc = blk / blocks, p = blk - cc * blocks;
   const int c = cc * kChunk + 2 * lane;
   const bool active = c < g.C;
-  const int i0 = iq * kRows, j0 = strip * kTok, i = i0 + wave;
-  uint32_t off[RG::PER_WAVE];
-  slice_offsets<BF16, KT, KH, KW>(g, i0, j0, c, wave, off);
-  // this wave's dy row: 8 tokens at byte offsets within a frame (kOutside outside)
-  uint32_t doff[kTok];
-#pragma unroll
-  for (int k = 0; k < kTok; ++k)
-    doff[k] = (active && i < g.H && j0 + k < g.W)
-                  ? (uint32_t)(((uint32_t)i * g.W + j0 + k) * (uint32_t)g.C + c) * (BF16 ? 2u : 4u)
-                  : kOutside;
-  const char* xbase = static_cast<const char*>(x) + (int64_t)b * g.T * frame_bytes;
-  const char* dbase = static_cast<const char*>(dy) + (int64_t)b * g.T * frame_bytes;
-  auto load_dy = [&](int f, Pair (&v)[kTok]) {  // zeros outside the segment
-    const __amdgpu_buffer_rsrc_t rs = frame_rsrc(dbase, frame_bytes, f < t0 || f >= t1 ? -1 : f, g.T);
-#pragma unroll
-    for (int k = 0; k < kTok; ++k) v[k] = load_pair<BF16>(rs, doff[k]);
-  };
-  auto put = [&](int buf, const Pair (&v)[RG::PER_WAVE]) {
-#pragma unroll
-    for (int k = 0; k < RG::PER_WAVE; ++k) {
-      const int pos = wave + kWavesPerBlock * k;
-      if (pos < RG::POS) slices[buf][pos * 64 + lane] = v[k];
-    }
-  };
   float2 acc[RG::TAPS];
 #pragma unroll
   for (int tap = 0; tap < RG::TAPS; ++tap) acc[tap] = make_float2(0.0f, 0.0f);
   float2 db = make_float2(0.0f, 0.0f);
-  // dy window: slot j = frame s - rt + j (frames outside the segment are zero)
-  float2 d[KT][kTok];
-#pragma unroll
-  for (int j = 0; j < KT; ++j) {
-    Pair v[kTok];
-    load_dy(s0 + j - rt, v);
-#pragma unroll
-    for (int k = 0; k < kTok; ++k) {
-      d[j][k] = widen(v[k]);  // these frames enter the bias sum here, later ones as they arrive
-      db.x += d[j][k].x;
-      db.y += d[j][k].y;
-    }
-  }
-  Pair dnxt[kTok];
-  load_dy(s0 + rt + 1, dnxt);
-  Pair nxt[RG::PER_WAVE];
-  load_slice<BF16, KT, KH, KW>(xbase, frame_bytes, s0, g.T, off, nxt);
-  put(s0 & 1, nxt);
-  if (s0 + 1 < s1) load_slice<BF16, KT, KH, KW>(xbase, frame_bytes, s0 + 1, g.T, off, nxt);
-  __syncthreads();
+  const int units = g.B * g.segs * g.hq * g.strips;
 #pragma unroll 1
-  for (int s = s0; s < s1; ++s) {
-    if (s + 1 < s1) {
-      put((s + 1) & 1, nxt);
-      if (s + 2 < s1) load_slice<BF16, KT, KH, KW>(xbase, frame_bytes, s + 2, g.T, off, nxt);
-    }
-    const Pair* cur = slices[s & 1];
+  for (int u = p; u < units; u += blocks) {
+    const int strip = u % g.strips;
+    int r = u / g.strips;
+    const int iq = r % g.hq;
+    r /= g.hq;
+    int t0, t1;
+    segment(g, r % g.segs, t0, t1);
+    const int b = r / g.segs;
+    const int s0 = max(t0 - rt, 0), s1 = min(t1 + rt, g.T);  // x slices
+    const int i0 = iq * kRows, j0 = strip * kTok, i = i0 + wave;
+    uint32_t off[RG::PER_WAVE];
+    slice_offsets<BF16, KT, KH, KW>(g, i0, j0, c, wave, off);
+    // this wave's dy row: 8 tokens at byte offsets within a frame (kOutside outside)
+    uint32_t doff[kTok];
 #pragma unroll
-    for (int e = 0; e < KH; ++e) {
-      const Pair* src = cur + (wave + e) * RG::RX * 64 + lane;
-      float2 xv[RG::RX];
+    for (int k = 0; k < kTok; ++k)
+      doff[k] = (active && i < g.H && j0 + k < g.W)
+                    ? (uint32_t)(((uint32_t)i * g.W + j0 + k) * (uint32_t)g.C + c) * (BF16 ? 2u : 4u)
+                    : kOutside;
+    const char* xbase = static_cast<const char*>(x) + (int64_t)b * g.T * frame_bytes;
+    const char* dbase = static_cast<const char*>(dy) + (int64_t)b * g.T * frame_bytes;
+    auto load_dy = [&](int f, Pair (&v)[kTok]) {  // zeros outside the segment
+      const __amdgpu_buffer_rsrc_t rs = frame_rsrc(dbase, frame_bytes, f < t0 || f >= t1 ? -1 : f, g.T);
 #pragma unroll
-      for (int q = 0; q < RG::RX; ++q) xv[q] = widen(src[q * 64]);
+      for (int k = 0; k < kTok; ++k) v[k] = load_pair<BF16>(rs, doff[k]);
+    };
+    auto put = [&](int buf, const Pair (&v)[RG::PER_WAVE]) {
 #pragma unroll
-      for (int a = 0; a < KT; ++a) {
-#pragma unroll
-        for (int f = 0; f < KW; ++f)
-#pragma unroll
-          for (int k = 0; k < kTok; ++k) {
-            const float2 dv = d[KT - 1 - a][k];  // dy frame s + rt - a (zero outside the segment)
-            acc[(a * KH + e) * KW + f].x = fmaf(dv.x, xv[k + f].x, acc[(a * KH + e) * KW + f].x);
-            acc[(a * KH + e) * KW + f].y = fmaf(dv.y, xv[k + f].y, acc[(a * KH + e) * KW + f].y);
-          }
+      for (int k = 0; k < RG::PER_WAVE; ++k) {
+        const int pos = wave + kWavesPerBlock * k;
+        if (pos < RG::POS) slices[buf][pos * 64 + lane] = v[k];
       }
-      asm volatile("" ::: "memory");  // one row's reads in flight at a time (registers)
+    };
+    // dy window: slot j = frame s - rt + j (frames outside the segment are zero)
+    float2 d[KT][kTok];
+#pragma unroll
+    for (int j = 0; j < KT; ++j) {
+      Pair v[kTok];
+      load_dy(s0 + j - rt, v);
+#pragma unroll
+      for (int k = 0; k < kTok; ++k) {
+        d[j][k] = widen(v[k]);  // these frames enter the bias sum here, later ones as they arrive
+        db.x += d[j][k].x;
+        db.y += d[j][k].y;
+      }
     }
-    // shift the dy window; frame s + rt + 1 enters (and the bias sum)
+    Pair dnxt[kTok];
+    load_dy(s0 + rt + 1, dnxt);
+    Pair nxt[RG::PER_WAVE];
+    load_slice<BF16, KT, KH, KW>(xbase, frame_bytes, s0, g.T, off, nxt);
+    put(s0 & 1, nxt);
+    if (s0 + 1 < s1) load_slice<BF16, KT, KH, KW>(xbase, frame_bytes, s0 + 1, g.T, off, nxt);
+    __syncthreads();
+#pragma unroll 1
+    for (int s = s0; s < s1; ++s) {
+      if (s + 1 < s1) {
+        put((s + 1) & 1, nxt);
+        if (s + 2 < s1) load_slice<BF16, KT, KH, KW>(xbase, frame_bytes, s + 2, g.T, off, nxt);
+      }
+      const Pair* cur = slices[s & 1];
 #pragma unroll
-    for (int j = 0; j + 1 < KT; ++j)
+      for (int e = 0; e < KH; ++e) {
+        const Pair* src = cur + (wave + e) * RG::RX * 64 + lane;
+        float2 xv[RG::RX];
 #pragma unroll
-      for (int k = 0; k < kTok; ++k) d[j][k] = d[j + 1][k];
+        for (int q = 0; q < RG::RX; ++q) xv[q] = widen(src[q * 64]);
 #pragma unroll
-    for (int k = 0; k < kTok; ++k) {
-      d[KT - 1][k] = widen(dnxt[k]);
-      db.x += d[KT - 1][k].x;
-      db.y += d[KT - 1][k].y;
+        for (int a = 0; a < KT; ++a) {
+#pragma unroll
+          for (int f = 0; f < KW; ++f)
+#pragma unroll
+            for (int k = 0; k < kTok; ++k) {
+              const float2 dv = d[KT - 1 - a][k];  // dy frame s + rt - a (zero outside the segment)
+              acc[(a * KH + e) * KW + f].x = fmaf(dv.x, xv[k + f].x, acc[(a * KH + e) * KW + f].x);
+              acc[(a * KH + e) * KW + f].y = fmaf(dv.y, xv[k + f].y, acc[(a * KH + e) * KW + f].y);
+            }
+        }
+        asm volatile("" ::: "memory");  // one row's reads in flight at a time (registers)
+      }
+      // shift the dy window; frame s + rt + 1 enters (and the bias sum)
+#pragma unroll
+      for (int j = 0; j + 1 < KT; ++j)
+#pragma unroll
+        for (int k = 0; k < kTok; ++k) d[j][k] = d[j + 1][k];
+#pragma unroll
+      for (int k = 0; k < kTok; ++k) {
+        d[KT - 1][k] = widen(dnxt[k]);
+        db.x += d[KT - 1][k].x;
+        db.y += d[KT - 1][k].y;
+      }
+      load_dy(s + rt + 2, dnxt);
+      __syncthreads();  // slice s is read; its buffer takes slice s + 2 next
     }
-    load_dy(s + rt + 2, dnxt);
-    __syncthreads();  // slice s is read; its buffer takes slice s + 2 next
   }
-  if (!active) return;
-  const int64_t slot =
-      ((((int64_t)b * g.segs + seg) * g.hq + iq) * g.strips + strip) * kWavesPerBlock + wave;
-  float* pc0 = part + (slot * g.C + c) * RG::TAPS;
-  float* pc1 = pc0 + RG::TAPS;
+  if constexpr (BF16) {
+    if (!active) return;
+    write_sums<RG::TAPS>(part, part_b, (int64_t)p * kWavesPerBlock + wave, g.C, c, acc, db);
+  } else {
+    // the last barrier of the walk ended every read of the slices
+    float* sums = reinterpret_cast<float*>(slices);
+    constexpr int N = RG::TAPS + 1;  // taps and bias
+    static_assert(N * 128 * sizeof(float) <= sizeof(slices), "the sums of a wave fit the slices");
+    for (int w = 1; w < kWavesPerBlock; ++w) {
+      if (wave == w) {
 #pragma unroll
-  for (int tap = 0; tap < RG::TAPS; ++tap) {
-    pc0[tap] = acc[tap].x;
-    pc1[tap] = acc[tap].y;
+        for (int n = 0; n < N; ++n)
+          *reinterpret_cast<float2*>(sums + (n * 64 + lane) * 2) = n < RG::TAPS ? acc[n] : db;
+      }
+      __syncthreads();
+      if (wave == 0) {
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+          const float2 o = *reinterpret_cast<const float2*>(sums + (n * 64 + lane) * 2);
+          float2& a = n < RG::TAPS ? acc[n] : db;
+          a.x += o.x;
+          a.y += o.y;
+        }
+      }
+      __syncthreads();
+    }
+    if (wave == 0 && active) write_sums<RG::TAPS>(part, part_b, p, g.C, c, acc, db);
   }
-  part_b[slot * g.C + c] = db.x;
-  part_b[slot * g.C + c + 1] = db.y;
 }
 
 // ---------------------------------------------------------------------------- launch
@@ -727,6 +765,12 @@ hipError_t wgrad_kh(const ConvGeometry& g, const void* x, const void* dy, float*
 
 int stream_bricks(const ConvGeometry& g) { return g.chunks * g.B * g.segs * g.hq * g.strips; }
 
+// Blocks per chunk of the streaming weight gradient: one per unit, in fp32 at most one per slot.
+int stream_wgrad_blocks(const ConvGeometry& g) {
+  const int units = g.B * g.segs * g.hq * g.strips, slots = g.wg_blocks * kWavesPerBlock;
+  return g.bf16 || units < slots ? units : slots;
+}
+
 template <bool BF16, bool OUT_BF16, bool FLIP, int KT, int KH, int KW>
 hipError_t launch_stream(const ConvGeometry& g, const void* in, const float* w, const float* bias,
                          void* out, int accumulate, hipStream_t s) {
@@ -746,9 +790,10 @@ hipError_t launch_stream(const ConvGeometry& g, const void* in, const float* w, 
 template <bool BF16, int KT, int KH, int KW>
 hipError_t launch_stream_wgrad(const ConvGeometry& g, const void* x, const void* dy, float* part,
                                float* part_b, hipStream_t s) {
-  void* a[] = {(void*)&g, (void*)&x, (void*)&dy, (void*)&part, (void*)&part_b};
+  const int blocks = stream_wgrad_blocks(g);
+  void* a[] = {(void*)&g, (void*)&x, (void*)&dy, (void*)&part, (void*)&part_b, (void*)&blocks};
   return hipLaunchKernel(reinterpret_cast<const void*>(&dwconv_stream_wgrad_kernel<BF16, KT, KH, KW>),
-                         dim3(stream_bricks(g)), dim3(kBlockThreads), a, 0, s);
+                         dim3(g.chunks * blocks), dim3(kBlockThreads), a, 0, s);
 }
 
 // The filter shapes the streaming path covers: every extent 1 or 3.
@@ -788,7 +833,6 @@ constexpr int kWgradBlocksTarget = 768;
 // stays resident.
 constexpr int kStreamBlocks = 1024;
 constexpr int kSegFrames = 4;
-constexpr int kF32Bricks = 4096;
 
 void conv_plan(ConvGeometry& g) {
   g.taps = g.kt * g.kh * g.kw;
@@ -805,12 +849,10 @@ void conv_plan(ConvGeometry& g) {
   g.seg_frames = (g.T + g.segs - 1) / g.segs;
   g.segs = (g.T + g.seg_frames - 1) / g.seg_frames;
   // The streaming path: every filter extent 1 or 3, frames below 2 GB (a raw buffer of one frame).
-  // fp32 grids of very many bricks per chunk stay with the general kernel, whose weight gradient
-  // needs partial sums per resident wave and not per brick.  fp32 at 16x34x60x1024, 3x3x3, general
+  // fp32 at 16x34x60x1024, 3x3x3, general
   // and streaming: forward 179 -> 96 us, dx 192 -> 96, weight gradient 148 -> 101.
   g.stream = g.kt <= 3 && g.kh <= 3 && g.kw <= 3 &&
-             (uint64_t)g.H * g.W * g.C * (g.bf16 ? 2 : 4) < 0x7fffffffull &&
-             (g.bf16 || (int64_t)g.B * g.segs * g.hq * g.strips <= kF32Bricks);
+             (uint64_t)g.H * g.W * g.C * (g.bf16 ? 2 : 4) < 0x7fffffffull;
   const int bricks = (g.strips + g.sg - 1) / g.sg;
   g.tiles_per_bc = bricks * g.T * g.hq * g.sg;
   const int want = kWgradBlocksTarget / (g.chunks * g.kt);
@@ -818,11 +860,12 @@ void conv_plan(ConvGeometry& g) {
   g.wg_blocks = (int)(want < 1 ? 1 : (want > per_pair ? per_pair : want));
 }
 
-// Partial-sum slots of the weight-gradient sweep: one per wave of a brick on the streaming path,
-// one per wave of a sweep block otherwise.
+// Partial-sum slots of the weight-gradient sweep: one per wave of a unit on the bf16 streaming path,
+// one per wave of a general sweep block otherwise (the fp32 streaming path uses as many as it has
+// blocks).
 size_t conv_slots(const ConvGeometry& g) {
-  return g.stream ? (size_t)g.B * g.segs * g.hq * g.strips * kWavesPerBlock
-                  : (size_t)g.wg_blocks * kWavesPerBlock;
+  return g.stream && g.bf16 ? (size_t)g.B * g.segs * g.hq * g.strips * kWavesPerBlock
+                            : (size_t)g.wg_blocks * kWavesPerBlock;
 }
 
 size_t conv_workspace_bytes(const ConvGeometry& g) {
@@ -867,7 +910,7 @@ hipError_t launch_conv_backward(const ConvGeometry& g, bool bf16, const void* x,
     e = bf16 ? wgrad_kh<true>(g, x, dy, part, part_b, s) : wgrad_kh<false>(g, x, dy, part, part_b, s);
   if (e != hipSuccess) return e;
   const int64_t per_slot = (int64_t)g.C * g.taps, per_slot_b = g.C;
-  const int nslots = (int)slots;
+  const int nslots = g.stream && !g.bf16 ? stream_wgrad_blocks(g) : (int)slots;
   const int64_t n = per_slot + per_slot_b;
   const int blocks = (int)((n + 63) / 64);
   void* a[] = {(void*)&part, (void*)&part_b, (void*)&per_slot, (void*)&per_slot_b,
