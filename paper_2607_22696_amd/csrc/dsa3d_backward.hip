@@ -496,7 +496,7 @@ __device__ inline __attribute__((always_inline)) void count_tile(
     uint32_t* __restrict__ ranks) {
   const int bh = tl.group, b = bh / g.by_heads, m = bh - b * g.heads;
   const int lp = threadIdx.x % kSlotLanes;
-  for (int e = threadIdx.x / kSlotLanes; e < po.run * kSlotQueries;
+  for (int e = threadIdx.x / kSlotLanes; e < tile_tokens(po);
        e += kBlockThreads / kSlotLanes) {
     int i, j;
     if (!slot_token(po, g, tl, e, i, j)) continue;
@@ -762,12 +762,13 @@ __device__ inline __attribute__((always_inline)) void bwd_slots_tile(
   const int bh = tl.group, b = bh / g.by_heads, m = bh - b * g.heads, t = tl.frame;
   const SlotWindow win = slot_window<LY::kRowBytes>(g, b, m, t);
 
-  for (int e0 = kSlotQueries * wave; e0 < po.run * kSlotQueries;
+  for (int e0 = kSlotQueries * wave; e0 < tile_tokens(po);
        e0 += kWavesPerBlock * kSlotQueries) {
     int i, j;
     const bool active = slot_token(po, g, tl, e0 + qi, i, j);
     if (__builtin_amdgcn_ballot_w64(active) == 0) continue;
-    j = min(j, g.W - 1);  // an idle query computes on a valid token and stores nothing
+    i = min(i, g.H - 1);  // an idle query computes on a valid token and stores nothing
+    j = min(j, g.W - 1);
     const int n = t * HW + i * g.W + j;
     const int64_t row = ((int64_t)b * g.N + n) * g.heads + m;
     const float* off = offsets + row * g.P * 3;

@@ -174,12 +174,13 @@ __device__ inline __attribute__((always_inline)) void slots_tile(
   float* const val = lds.val[qi];
   const int HW = g.H * g.W;
 
-  for (int e0 = kSlotQueries * wave; e0 < po.run * kSlotQueries;
+  for (int e0 = kSlotQueries * wave; e0 < tile_tokens(po);
        e0 += kWavesPerBlock * kSlotQueries) {
     int i, j;
     const bool active = slot_token(po, g, tl, e0 + qi, i, j);
     if (__builtin_amdgcn_ballot_w64(active) == 0) continue;
-    j = min(j, g.W - 1);  // an idle query computes on a valid token and stores nothing
+    i = min(i, g.H - 1);  // an idle query computes on a valid token and stores nothing
+    j = min(j, g.W - 1);
     const int b = tl.group / g.by_heads, m = tl.group - b * g.heads;
     const int t = tl.frame;
     const SlotWindow win = slot_window<LY::kRowBytes>(g, b, m, t);

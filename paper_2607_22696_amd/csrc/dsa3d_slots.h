@@ -128,12 +128,13 @@ __device__ inline __attribute__((always_inline)) uint32_t lane_scan(uint32_t v) 
 
 // ---------------------------------------------------------------------------- tiles
 
-// Where tiles may be taken by slots, a cell of the pencil order is four tokens along x.  Token e of
-// a tile: false if it is past the pencil or the grid.
+// Token e of a tile (four neighbours to a wave of the slots): of a cell of four tokens along x, or
+// in raster order of the pencil's rectangle.  False if it is past the pencil or the grid.
 __device__ inline __attribute__((always_inline)) bool slot_token(const PencilOrder& po,
                                                                  const Geometry& g,
                                                                  const PencilTile& tl, int e,
                                                                  int& i, int& j) {
+  if (po.cell == 1) return pencil_cell(po, tl, e, i, j);
   int cell;
   const bool in = pencil_cell(po, tl, e / kSlotQueries, i, cell);
   j = cell * kSlotQueries + e % kSlotQueries;
@@ -754,24 +755,33 @@ inline int backward_rounds(int P) {
   return 5;
 }
 
-// Pencil order of the query-owned kernels: cells of one token, or of four along x where tiles may
-// be taken by slots.  A tile is a workgroup's rows with a row on kLanes lanes.  Pencils are about
-// 12 x 12 tokens: at 64x68x120, 24 heads x 128, 3x5x5, offsets U[-8, 8], the forward took 159 /
-// 162 / 197 ms with pencils of about 12 x 12 / 16 x 16 / 24 x 24 tokens.
-// With slots, a grid whose tiles would leave compute units idle gets smaller ones, down to one
-// cell, of which a workgroup's other waves have nothing (4x8x8 tokens, 2 heads x 32, fp32: 17.6 ->
-// 10.6 us).
+// Pencil order of the query-owned kernels.  A tile is a workgroup's rows with a row on kLanes lanes;
+// pencils are about 12 x 12 tokens: at 64x68x120, 24 heads x 128, 3x5x5, offsets U[-8, 8], the
+// forward took 159 / 162 / 197 ms with pencils of about 12 x 12 / 16 x 16 / 24 x 24 tokens.
+// Where tiles may be taken by slots, cells are four tokens along x, which keeps a wave's queries
+// in one grid row, unless the grid's width would leave more than 1 in 32 of them empty (43x16x18:
+// 10% of the gathering kernels' lanes).
+// With slots, a grid whose tiles would leave compute units idle gets smaller ones, down to four
+// tokens, of which a workgroup's other waves have nothing (4x8x8 tokens, 2 heads x 32, fp32: 17.6
+// -> 10.6 us).
 constexpr int kFillTiles = 512;  // two workgroups per compute unit
 
 template <int D, bool BF16>
 inline PencilOrder query_order(const Geometry& g, bool slots, bool fill = false) {
-  if (!slots) return plan_pencils(g.B * g.heads, g.T, g.H, g.W, Layout<D, BF16>::kRowsPerBlock, 12, 12);
   constexpr int Q = kSlotQueries;
-  int run = Layout<D, BF16>::kRowsPerBlock / Q;
-  const int64_t cells = (int64_t)g.B * g.heads * g.T * g.H * ((g.W + Q - 1) / Q);
-  while (fill && run > 1 && cells < (int64_t)run * kFillTiles) run /= 2;
-  return plan_pencils(g.B * g.heads, g.T, g.H, (g.W + Q - 1) / Q, run, 12, 12 / Q);
+  int run = Layout<D, BF16>::kRowsPerBlock;
+  if (!slots) return plan_pencils(g.B * g.heads, g.T, g.H, g.W, run, 12, 12);
+  const int64_t tokens = (int64_t)g.B * g.heads * g.N;
+  while (fill && run > Q && tokens < (int64_t)run * kFillTiles) run /= 2;
+  const int cols = (g.W + Q - 1) / Q;
+  if (32 * (cols * Q - g.W) > g.W) return plan_pencils(g.B * g.heads, g.T, g.H, g.W, run, 12, 12);
+  PencilOrder o = plan_pencils(g.B * g.heads, g.T, g.H, cols, run / Q, 12, 12 / Q);
+  o.cell = Q;
+  return o;
 }
+
+// Tokens of a tile.
+DSA3D_TILE_FN int tile_tokens(const PencilOrder& o) { return o.run * o.cell; }
 
 // Token e of a tile in that order; false if it is past the tile, the pencil or the grid.
 template <bool SLOTS>
@@ -779,7 +789,7 @@ __device__ inline __attribute__((always_inline)) bool query_token(const PencilOr
                                                                   const Geometry& g,
                                                                   const PencilTile& tl, int e,
                                                                   int& i, int& j) {
-  if constexpr (SLOTS) return slot_token(po, g, tl, e, i, j) && e < po.run * kSlotQueries;
+  if constexpr (SLOTS) return slot_token(po, g, tl, e, i, j) && e < tile_tokens(po);
   return pencil_cell(po, tl, e, i, j);
 }
 

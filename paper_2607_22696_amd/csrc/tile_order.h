@@ -53,6 +53,7 @@ struct PencilOrder {
   int frames, rows, cols;  // cell grid of one (batch, head) group
   int ph, pw;              // pencil size in cells
   int run;                 // cells per tile
+  int cell;                // tokens of a cell along x (set by the planner's caller where not 1)
   int np_r, np_c;          // pencils along rows and columns
   int runs;                // tiles per pencil frame, ceil(ph * pw / run)
   int64_t pencil_tiles;    // tiles per pencil, frames * runs
@@ -68,6 +69,7 @@ DSA3D_TILE_FN PencilOrder pencils_of(int groups, int frames, int rows, int cols,
   o.rows = rows;
   o.cols = cols;
   o.run = run;
+  o.cell = 1;
   o.ph = (rows + nr - 1) / nr;
   o.pw = (cols + nc - 1) / nc;
   o.np_r = (rows + o.ph - 1) / o.ph;
