@@ -1119,20 +1119,22 @@ struct BlockAcc {
 // voxel x0 is the upper corner of cell x0 - 1 and the lower of cell x0, the voxel x0 + 1 the
 // upper of x0 and the lower of x0 + 1: [s0, m1), [m1, m2), [m2, end).  `zlow` says whether
 // the voxels are the lower z corner of this plane's cells.  Entries are read one batch
-// ahead, so a batch waits for its rows only.
+// ahead, so a batch waits for its rows only.  The caller is one of `parts` groups that share the
+// run batch by batch.
 template <int D, bool BF16, bool PW, int YR>
 __device__ inline __attribute__((always_inline)) void gather_run(
     const char* __restrict__ qh, const char* __restrict__ gh, uint32_t tok_bytes,
     const Entry* __restrict__ entries, uint32_t s0, uint32_t m1, uint32_t m2, uint32_t end,
-    bool zlow, BlockAcc<Layout<D, BF16>::kVec>& acc) {
+    bool zlow, uint32_t part, uint32_t parts, BlockAcc<Layout<D, BF16>::kVec>& acc) {
   using LY = Layout<D, BF16>;
   constexpr int VEC = LY::kVec;
   constexpr int U = kGatherUnroll;
+  s0 += part * U;
   if (s0 >= end) return;
   Entry en[U];
 #pragma unroll
   for (int k = 0; k < U; ++k) en[k] = entries[min(s0 + k, end - 1)];
-  for (uint32_t u = s0; u < end; u += U) {
+  for (uint32_t u = s0; u < end; u += U * parts) {
     uint4 qr[U], gr[U];
 #pragma unroll
     for (int k = 0; k < U; ++k) {
@@ -1142,7 +1144,7 @@ __device__ inline __attribute__((always_inline)) void gather_run(
     }
     Entry nx[U];
 #pragma unroll
-    for (int k = 0; k < U; ++k) nx[k] = entries[min(u + U + k, end - 1)];
+    for (int k = 0; k < U; ++k) nx[k] = entries[min(u + U * parts + k, end - 1)];
 #pragma unroll
     for (int k = 0; k < U; ++k) {
       const uint32_t uk = u + k;
@@ -1181,7 +1183,10 @@ __device__ inline __attribute__((always_inline)) void gather_run(
 // the planes z - 1 and z: six runs of three adjacent bins, and each entry's q and dout rows
 // are loaded once per run for all the voxels it feeds.
 // PW (the predicted-weights variant): dV only (there is no K).
-template <int D, bool BF16, bool PW>
+// WAVE: all groups of a wave share one block, batch by batch, and add their sums at the end: for
+// grids whose blocks would leave the chip idle, where the chain of a block's batches is the time
+// (4x8x8 tokens, 2 heads x 32, 3x3x3: 65 -> 15 us).
+template <int D, bool BF16, bool PW, bool WAVE>
 __global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_gather_kernel(
     Geometry g, const void* __restrict__ q, const void* __restrict__ dout,
     const uint32_t* __restrict__ starts, const Entry* __restrict__ entries, float* __restrict__ dk,
@@ -1198,7 +1203,8 @@ __global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_gather_
   const int bh = tl.group;
   const int b = bh / g.by_heads, m = bh - b * g.heads;
   int by, bx;  // the group's 2 x 2 block (cell of the pencil grid)
-  if (!pencil_cell(po, tl, wave * LY::kGroups + grp, by, bx)) return;
+  if (!pencil_cell(po, tl, WAVE ? wave : wave * LY::kGroups + grp, by, bx)) return;
+  const uint32_t part = WAVE ? grp : 0, parts = WAVE ? LY::kGroups : 1;
   const int64_t head_off = ((int64_t)b * g.N * g.heads + m) * LY::kRowBytes + sub * 16;
   const char* qh = static_cast<const char*>(q) + head_off;
   const char* gh = static_cast<const char*>(dout) + head_off;
@@ -1229,9 +1235,21 @@ __global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_gather_
       r[yr][3] = hasx1 ? starts[ci + 3] : r[yr][2];
     }
     const bool zlow = cz == 1;
-    gather_run<D, BF16, PW, 0>(qh, gh, tok_bytes, entries, r[0][0], r[0][1], r[0][2], r[0][3], zlow, acc);
-    gather_run<D, BF16, PW, 1>(qh, gh, tok_bytes, entries, r[1][0], r[1][1], r[1][2], r[1][3], zlow, acc);
-    gather_run<D, BF16, PW, 2>(qh, gh, tok_bytes, entries, r[2][0], r[2][1], r[2][2], r[2][3], zlow, acc);
+    gather_run<D, BF16, PW, 0>(qh, gh, tok_bytes, entries, r[0][0], r[0][1], r[0][2], r[0][3], zlow, part, parts, acc);
+    gather_run<D, BF16, PW, 1>(qh, gh, tok_bytes, entries, r[1][0], r[1][1], r[1][2], r[1][3], zlow, part, parts, acc);
+    gather_run<D, BF16, PW, 2>(qh, gh, tok_bytes, entries, r[2][0], r[2][1], r[2][2], r[2][3], zlow, part, parts, acc);
+  }
+  if constexpr (WAVE) {
+#pragma unroll
+    for (int d = L; d < 64; d *= 2)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          if constexpr (!PW) acc.k[c][e] += __shfl_xor(acc.k[c][e], d);
+          acc.v[c][e] += __shfl_xor(acc.v[c][e], d);
+        }
+    if (grp != 0) return;
   }
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
@@ -1658,7 +1676,7 @@ hipError_t bwd_dispatch(const Geometry& g, const void* q, const void* k, const v
                         dim3(kBlockThreads), a, 0, s);
     if (e != hipSuccess) return e;
   }
-  const int rounds = pw ? 0 : backward_rounds<D, BF16>(g.P);
+  const int rounds = pw ? 0 : backward_rounds<D, BF16>(g);
   const PencilOrder po = query_order<D, BF16>(g, rounds > 0);
   // The main operator sweeps the points twice (V pass, then K pass with the finish of each
   // row's points); the predicted-weights variant, which reads no K, sweeps them once and
@@ -1757,11 +1775,16 @@ hipError_t bwd_dispatch(const Geometry& g, const void* q, const void* k, const v
     if (e != hipSuccess) return e;
   } else {
     using LY = Layout<D, BF16>;
-    // cells: 2 x 2 voxel blocks of a frame; pencils of about 32 x 32 voxels
+    // cells: 2 x 2 voxel blocks of a frame; pencils of about 32 x 32 voxels.  Fewer than four waves
+    // per compute unit: a wave per block.
+    const int64_t vblocks = (int64_t)g.B * g.heads * g.T * ((g.H + 1) / 2) * ((g.W + 1) / 2);
+    const bool wave = vblocks < 1024 * LY::kGroups;
     const PencilOrder go = plan_pencils(g.B * g.heads, g.T, (g.H + 1) / 2, (g.W + 1) / 2,
-                                        LY::kRowsPerBlock, 16, 16);
-    const void* kern = pw ? reinterpret_cast<const void*>(&bwd_gather_kernel<D, BF16, true>)
-                          : reinterpret_cast<const void*>(&bwd_gather_kernel<D, BF16, false>);
+                                        wave ? kWavesPerBlock : LY::kRowsPerBlock, 16, 16);
+#define DSA3D_GATHER(PW, WAVE) reinterpret_cast<const void*>(&bwd_gather_kernel<D, BF16, PW, WAVE>)
+    const void* kern = pw ? (wave ? DSA3D_GATHER(true, true) : DSA3D_GATHER(true, false))
+                          : (wave ? DSA3D_GATHER(false, true) : DSA3D_GATHER(false, false));
+#undef DSA3D_GATHER
     e = launch_tiles(go.vtiles, [&](int64_t vt0, int gblocks) {
       void* a[] = {(void*)&g,  (void*)&q,  (void*)&dout, (void*)&w.starts, (void*)&w.entries,
                    (void*)&dk, (void*)&dv, (void*)&go,   (void*)&vt0};
