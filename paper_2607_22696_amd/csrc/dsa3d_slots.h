@@ -780,6 +780,9 @@ inline int backward_rounds(const Geometry& g) {
 // tokens, of which a workgroup's other waves have nothing (4x8x8 tokens, 2 heads x 32, fp32: 17.6
 // -> 10.6 us).
 constexpr int kFillTiles = 512;  // two workgroups per compute unit
+// Pencils taken in raster order stay narrow: a wave at the turn of a row spans their width, and with
+// the points' reach it has to fit the 32 bits of a word.
+constexpr int kRasterCols = 13;
 
 template <int D, bool BF16>
 inline PencilOrder query_order(const Geometry& g, bool slots, bool fill = false) {
@@ -789,7 +792,8 @@ inline PencilOrder query_order(const Geometry& g, bool slots, bool fill = false)
   const int64_t tokens = (int64_t)g.B * g.heads * g.N;
   while (fill && run > Q && tokens < (int64_t)run * kFillTiles) run /= 2;
   const int cols = (g.W + Q - 1) / Q;
-  if (32 * (cols * Q - g.W) > g.W) return plan_pencils(g.B * g.heads, g.T, g.H, g.W, run, 12, 12);
+  if (32 * (cols * Q - g.W) > g.W)
+    return plan_pencils(g.B * g.heads, g.T, g.H, g.W, run, 12, 12, kRasterCols);
   PencilOrder o = plan_pencils(g.B * g.heads, g.T, g.H, cols, run / Q, 12, 12 / Q);
   o.cell = Q;
   return o;

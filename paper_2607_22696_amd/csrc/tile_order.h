@@ -92,9 +92,10 @@ DSA3D_TILE_FN PencilOrder pencils_of(int groups, int frames, int rows, int cols,
 // of those nine splits the one that leaves the fewest idle cells (cells of a frame's tiles
 // past the grid or past a pencil's rectangle) wins, then the one nearest the target.  On the
 // 68 x 120 grid with 16-cell tiles and a 12 x 12 target that gives 10 x 11 pencils, and on
-// 34 x 60 with 32-cell tiles 17 x 15 (255 cells in 8 tiles of 32).
+// 34 x 60 with 32-cell tiles 17 x 15 (255 cells in 8 tiles of 32).  Pencils wider than max_c cells
+// are not taken where a narrower one is among the nine.
 DSA3D_TILE_FN PencilOrder plan_pencils(int groups, int frames, int rows, int cols, int run,
-                                       int target_r, int target_c) {
+                                       int target_r, int target_c, int max_c = 1 << 30) {
   const int nr0 = (2 * rows + target_r) / (2 * target_r);  // round(rows / target_r)
   const int nc0 = (2 * cols + target_c) / (2 * target_c);
   PencilOrder best = pencils_of(groups, frames, rows, cols, run, nr0 < 1 ? 1 : nr0,
@@ -105,6 +106,7 @@ DSA3D_TILE_FN PencilOrder plan_pencils(int groups, int frames, int rows, int col
       const int nr = nr0 + dr, nc = nc0 + dc;
       if (nr < 1 || nc < 1 || nr > rows || nc > cols) continue;
       const PencilOrder o = pencils_of(groups, frames, rows, cols, run, nr, nc);
+      if (o.pw > max_c) continue;
       const int64_t idle = (int64_t)o.np_r * o.np_c * o.runs * run - (int64_t)rows * cols;
       const int64_t dist = (int64_t)(o.ph - target_r) * (o.ph - target_r) +
                            (int64_t)(o.pw - target_c) * (o.pw - target_c);
