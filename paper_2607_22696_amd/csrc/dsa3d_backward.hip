@@ -1676,7 +1676,7 @@ hipError_t bwd_dispatch(const Geometry& g, const void* q, const void* k, const v
                         dim3(kBlockThreads), a, 0, s);
     if (e != hipSuccess) return e;
   }
-  const int rounds = pw ? 0 : backward_rounds<D, BF16>(g);
+  const int rounds = pw ? 0 : backward_rounds(D, BF16, rows, g.P);
   const PencilOrder po = query_order<D, BF16>(g, rounds > 0);
   // The main operator sweeps the points twice (V pass, then K pass with the finish of each
   // row's points); the predicted-weights variant, which reads no K, sweeps them once and
@@ -1685,7 +1685,7 @@ hipError_t bwd_dispatch(const Geometry& g, const void* q, const void* k, const v
   if ((e = mark(0)) != hipSuccess) return e;
   if (split) {
     const void* vkern = reinterpret_cast<const void*>(&bwd_vpass_kernel<D, BF16, false>);
-    if constexpr (slot_rows_ok<D, BF16>())
+    if constexpr (slot_rows_ok(D, BF16))
       if (rounds > 0) vkern = reinterpret_cast<const void*>(&bwd_vpass_kernel<D, BF16, true>);
     e = launch_tiles(po.vtiles, [&](int64_t vt0, int blocks) {
       void* a[] = {(void*)&g,        (void*)&v,       (void*)&off, (void*)&dout, (void*)&w.recv,
@@ -1727,7 +1727,7 @@ hipError_t bwd_dispatch(const Geometry& g, const void* q, const void* k, const v
   reinterpret_cast<const void*>(&bwd_kpass_kernel<D, BF16, HOLD, R, WHOLE>)
     const bool whole = g.win_frames == g.T;
     const void* kern = hold ? DSA3D_KPASS(kHoldChunks, 0, false) : DSA3D_KPASS(0, 0, false);
-    if constexpr (slot_rows_ok<D, BF16>() && !(BF16 && D == 64)) {
+    if constexpr (slot_rows_ok(D, BF16) && !(BF16 && D == 64)) {
       if constexpr (BF16)  // up to 32 points are always held
         if (rounds == 2)
           kern = whole ? DSA3D_KPASS(kHoldChunks, 2, true) : DSA3D_KPASS(kHoldChunks, 2, false);

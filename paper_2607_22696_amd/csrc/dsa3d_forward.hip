@@ -297,7 +297,7 @@ fwd_kernel(Geometry g, const void* __restrict__ q, const void* __restrict__ k,
   PencilTile tl;
   if (!pencil_tile(po, vt0 + blockIdx.x, tl)) return;  // no pencil left on this XCD
   if constexpr (R > 0) {
-    if (compact_tile(g, po, tl, offsets, forward_box<D, BF16, R>())) {  // the same in every wave
+    if (compact_tile(g, po, tl, offsets, forward_box(D, BF16, R))) {  // the same in every wave
       slots_tile<D, BF16, PW, R, WHOLE>(
           g, po, tl, q, k, v, logits, offsets, out, lse,
           reinterpret_cast<SlotLds*>(lds)[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)]);
@@ -318,11 +318,11 @@ hipError_t fwd_dispatch(const Geometry& g, const void* q, const void* k, const v
 #define DSA3D_FWD(R, WHOLE)                                                    \
   (pw ? reinterpret_cast<const void*>(&fwd_kernel<D, BF16, true, R, WHOLE>)   \
       : reinterpret_cast<const void*>(&fwd_kernel<D, BF16, false, R, WHOLE>))
-  const int rounds = forward_rounds<D, BF16>(g, pw);
+  const int rounds = forward_rounds(D, BF16, (int64_t)g.B * g.N * g.heads, g.P, pw);
   const PencilOrder po = query_order<D, BF16>(g, rounds > 0, true);
   const bool whole = g.win_frames == g.T;
   const void* kern = DSA3D_FWD(0, false);
-  if constexpr (slot_rows_ok<D, BF16>()) {
+  if constexpr (slot_rows_ok(D, BF16)) {
     if (rounds == 2) kern = whole ? DSA3D_FWD(2, true) : DSA3D_FWD(2, false);
     if (rounds == 5) kern = whole ? DSA3D_FWD(5, true) : DSA3D_FWD(5, false);
   }

@@ -37,6 +37,7 @@
 #pragma once
 
 #include "dsa3d_device.h"
+#include "slot_rules.h"
 
 namespace dsa3d {
 namespace dev {
@@ -44,8 +45,6 @@ namespace dev {
 typedef __bf16 slot_bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float slot_f32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kSlotQueries = 4;  // per wave, neighbours along x
-constexpr int kSlotLanes = 16;   // lanes (points of a round) per query
 constexpr int kSlotBoxX = 32, kSlotBoxY = 16, kSlotBoxZ = 16;
 constexpr int kSlotWords = kSlotBoxY * kSlotBoxZ;  // four per lane
 static_assert(kSlotWords == 256, "four words per lane");
@@ -715,61 +714,6 @@ __device__ inline __attribute__((always_inline)) void row_sums(
 }
 
 // ---------------------------------------------------------------------------- launch shape
-
-// Whether the slots are built for this row size.
-template <int D, bool BF16>
-constexpr bool slot_rows_ok() {
-  return SlotSum<D, BF16>::kLanes == 8 || SlotSum<D, BF16>::kLanes == 16;
-}
-
-// Rounds that a kernel instance numbers together (0: every tile gathers) for rows of P points.
-// Numbering costs a wave the same for 9 points as for 16, which a 1x3x3 kernel does not earn
-// back: forward, 24 heads, gathering / by slots: 64 bf16 channels, 16x34x60 0.63 / 0.90 ms; 128
-// channels, 16x34x60 1.14 / 1.06, 3x21x96 (2 heads) 19 / 24 us.  A grid of few rows waits for one
-// wave's sweeps, which are a longer chain than the points' (4x14x21, 2 heads, forward: 64 fp32
-// channels 3x3x3 57 / 82 us, 3x5x5 119 / 144; 64 bf16 3x3x3 39 / 64, 3x7x7 122 / 194) except for
-// rows of 32 fp32 channels, eight to a load (4x8x8, 3x3x3 17 / 11), and many points of 128 bf16
-// channels (4x14x21, 3x7x7 238 / 207).
-constexpr int64_t kSlotRows = 16384;
-
-template <int D, bool BF16>
-inline bool few_rows(const Geometry& g) {
-  return D > 32 && !(BF16 && D == 128 && g.P > 2 * kSlotLanes) &&
-         (int64_t)g.B * g.N * g.heads < kSlotRows;
-}
-
-// The predicted-weights variant reads V only, half of what sharing saves: 64 bf16 channels, 64x34x60,
-// 16 heads, 3x3x3: 2.40 ms gathering, 2.45 by slots.
-template <int D, bool BF16>
-inline int forward_rounds(const Geometry& g, bool pw) {
-  if (!slot_rows_ok<D, BF16>() || g.P < kSlotLanes || few_rows<D, BF16>(g)) return 0;
-  if (pw && BF16 && D == 64 && g.P <= 2 * kSlotLanes) return 0;
-  return g.P <= 2 * kSlotLanes ? 2 : 5;
-}
-
-// Spread of a compact tile (compact_tile).  Offsets U[-3, 3] span about 700 voxels at 3x3x3 and 1090
-// at 3x5x5, U[-4, 4] 1250 and 1770.  16x34x60 (fp32: 9x33x47), gathering / by slots.  Forward: 24 x
-// 128 bf16, 3x3x3 U[-4, 4] 2.88 / 2.34 ms, 3x5x5 U[-3, 3] 7.32 / 4.64, U[-4, 4] 7.48 / 7.13; 16 x 64
-// bf16, 3x3x3 U[-3, 3] 1.02 / 1.05, U[-4, 4] 1.07 / 1.21; 6 x 64 fp32, 3x3x3 U[-4, 4] 0.30 / 0.37.
-// Backward, V pass + K pass: 24 x 128 bf16, 3x3x3 U[-3, 3] 4.68 / 4.50, U[-4, 4] 4.62 / 5.21, 3x5x5
-// U[-3, 3] 12.0 / 12.0, U[-4, 4] 12.0 / 13.0.
-// 16 x 64 bf16, 3x7x7 N(0, 1) by slots: 3.68 ms with 1000, 3.36 with 1500.
-template <int D, bool BF16, int R>
-constexpr int forward_box() { return (BF16 && D == 128) || R > 2 ? 1500 : 1000; }
-constexpr int kBackwardBox = 1000;
-
-// The backward sweeps the slots three times and counts the compact tiles on their own, so it needs
-// larger rows or more points.  V pass + K pass, gathering and by slots, N(0, 1) offsets: 128 bf16
-// channels, 16x34x60, 24 heads: 1x3x3 1.92 / 2.49 ms, 3x3x3 4.58 / 3.90, 3x5x5 11.9 / 8.5, 3x7x7
-// 22.9 / 18.0; 64 bf16 channels, 16 heads: 3x5x5 5.14 / 5.10, 3x7x7 10.2 / 11.1; 64 fp32
-// channels, 9x33x47, 6 heads: 3x3x3 0.84 / 0.84 (two batch items), 3x5x5 1.14 / 0.93, 3x7x7 2.28 /
-// 2.03.
-template <int D, bool BF16>
-inline int backward_rounds(const Geometry& g) {
-  if (!slot_rows_ok<D, BF16>() || (BF16 && D == 64) || few_rows<D, BF16>(g)) return 0;
-  if (g.P <= 2 * kSlotLanes) return BF16 && g.P >= kSlotLanes ? 2 : 0;
-  return 5;
-}
 
 // Pencil order of the query-owned kernels.  A tile is a workgroup's rows with a row on kLanes lanes;
 // pencils are about 12 x 12 tokens: at 64x68x120, 24 heads x 128, 3x5x5, offsets U[-8, 8], the

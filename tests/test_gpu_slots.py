@@ -10,7 +10,7 @@ import pytest
 
 import oracle
 import testgen
-from tests.util import max_abs, rel_err, say, shape9, to_device, to_host
+from tests.util import max_abs, rel_err, reorder_bound, say, shape9, to_device, to_host
 
 torch = pytest.importorskip("torch")
 
@@ -62,32 +62,44 @@ def compare(w, host):
 
 
 N05 = testgen.Dist(testgen.NORMAL, 0.0, 0.5)
+
+# (case, rounds that the forward and the backward number together, 0: every tile gathers).  The
+# rounds are asserted without a GPU by test_slot_rules.py, so that a change of the dispatch cannot
+# turn these into tests of the gathering code.
 CASES = [
-    # points per query: one under, at and over a round (16), two rounds (32) and five (80)
-    case("k335_f32_d32", T=3, H=5, W=9, heads=2, head_dim=32, kt=3, kh=3, kw=5, seed=70),
-    case("k1115_f32_d64", T=2, H=3, W=21, heads=1, head_dim=64, kt=1, kh=1, kw=15, seed=71),
-    case("k1117_bf16_d64", T=2, H=3, W=21, heads=2, head_dim=64, kt=1, kh=1, kw=17, dtype="bf16",
-         seed=72),
-    case("k1311_bf16_d128", T=2, H=5, W=18, heads=1, head_dim=128, kt=1, kh=3, kw=11,
-         dtype="bf16", seed=73),
-    case("k1127_bf16_d128", T=1, H=2, W=30, heads=2, head_dim=128, kt=1, kh=1, kw=27,
-         dtype="bf16", seed=74),
-    case("k399_bf16_d64", T=3, H=9, W=10, heads=1, head_dim=64, kt=1, kh=9, kw=9, dtype="bf16",
-         seed=75, offsets=N05),
-    case("k399_f32_d64", T=2, H=8, W=7, heads=1, head_dim=64, kt=1, kh=9, kw=9, seed=76),
+    # points per query: under, at and over a round (16), two rounds (32) and five (80)
+    (case("k335_f32_d32", T=3, H=5, W=9, heads=2, head_dim=32, kt=3, kh=3, kw=5, seed=70), 5, 5),
+    (case("k1115_f32_d64", T=2, H=3, W=21, heads=1, head_dim=64, kt=1, kh=1, kw=15, seed=71), 0, 0),
+    (case("k1117_bf16_d64", T=2, H=21, W=21, heads=20, head_dim=64, kt=1, kh=1, kw=17,
+          dtype="bf16", seed=72), 2, 0),
+    (case("k1311_bf16_d128", T=2, H=5, W=18, heads=1, head_dim=128, kt=1, kh=3, kw=11,
+          dtype="bf16", seed=73), 5, 5),
+    (case("k1127_bf16_d128", T=2, H=21, W=30, heads=14, head_dim=128, kt=1, kh=1, kw=27,
+          dtype="bf16", seed=74), 2, 2),
+    (case("k399_bf16_d64", T=3, H=9, W=10, heads=61, head_dim=64, kt=1, kh=9, kw=9, dtype="bf16",
+          seed=75, offsets=N05), 5, 0),
+    (case("k399_f32_d64", T=3, H=8, W=7, heads=98, head_dim=64, kt=1, kh=9, kw=9, seed=76), 5, 5),
+    (case("k377_bf16_d128", T=3, H=8, W=11, heads=2, head_dim=128, kt=3, kh=7, kw=7, dtype="bf16",
+          seed=85), 5, 5),
+    (case("k377_f32_d32", T=3, H=8, W=11, heads=2, head_dim=32, kt=3, kh=7, kw=7, seed=86), 5, 5),
+    # an ordinary training step's kernel
+    (case("k333_bf16_d128", T=8, H=12, W=24, heads=8, head_dim=128, dtype="bf16", seed=87), 2, 2),
+    (case("k355_f32_d64", T=6, H=12, W=24, heads=10, head_dim=64, kt=3, kh=5, kw=5, seed=88), 5, 5),
+    (case("k333_f32_d64", T=8, H=12, W=24, heads=8, head_dim=64, seed=89), 2, 0),
     # the last four-token cell of a row holds 1, 2 and 3 tokens; two batch items
-    case("w5_bf16_d128", B=2, T=2, H=3, W=5, heads=1, head_dim=128, dtype="bf16", seed=77),
-    case("w6_bf16_d64", T=2, H=13, W=6, heads=3, head_dim=64, dtype="bf16", seed=78),
-    case("w7_f32_d32", T=2, H=3, W=7, heads=2, head_dim=32, seed=79),
+    (case("w5_bf16_d128", B=2, T=10, H=9, W=5, heads=20, head_dim=128, dtype="bf16", seed=77), 2, 2),
+    (case("w6_bf16_d64", T=7, H=13, W=6, heads=31, head_dim=64, dtype="bf16", seed=78), 2, 0),
+    (case("w7_f32_d32", T=2, H=3, W=7, heads=2, head_dim=32, seed=79), 2, 0),
     # a grid beyond one tile per pencil frame, so that tiles keep their full size
-    case("tiles_bf16_d64", T=8, H=16, W=24, heads=8, head_dim=64, dtype="bf16", seed=80),
+    (case("tiles_bf16_d64", T=8, H=16, W=24, heads=8, head_dim=64, dtype="bf16", seed=80), 2, 0),
     # 65 heads x 256-byte rows: no buffer window, every row by a global load
-    case("no_window_bf16_d128", T=2, H=3, W=5, heads=65, head_dim=128, dtype="bf16", seed=81),
-    case("no_window_f32_d64", T=2, H=3, W=5, heads=65, head_dim=64, seed=82),
+    (case("no_window_bf16_d128", T=4, H=9, W=8, heads=65, head_dim=128, dtype="bf16", seed=81), 2, 2),
+    (case("no_window_f32_d64", T=4, H=9, W=8, heads=65, head_dim=64, kt=3, kh=3, kw=5, seed=82),
+     5, 5),
 ]
 
 
-@pytest.mark.parametrize("w", CASES, ids=lambda w: w.name)
+@pytest.mark.parametrize("w", [c[0] for c in CASES], ids=lambda w: w.name)
 def test_parity(w):
     host = list(testgen.gen_inputs(w))
     if host[4] is None:
@@ -95,19 +107,93 @@ def test_parity(w):
     compare(w, host)
 
 
-@pytest.mark.parametrize("dtype,dim,kernel", [("bf16", 128, (3, 3, 3)), ("bf16", 64, (3, 5, 5)),
-                                              ("f32", 64, (3, 3, 3)), ("f32", 32, (3, 7, 7))])
-def test_points_that_leave_the_box(dtype, dim, kernel):
-    """A tile is judged by its first token; here other tokens of compact tiles reach across the
-    whole grid (rounds without shared slots) and a few points lie far outside it."""
-    w = case("box", T=20, H=20, W=36, heads=1, head_dim=dim, kt=kernel[0], kh=kernel[1],
-             kw=kernel[2], dtype=dtype, seed=83)
+def pw_case(name, **kw):
+    return testgen.PW_WORKLOADS["pw_64x34x60"].with_grid(name=name, offsets=N05, **kw)
+
+
+# (case of the predicted-weights variant, its forward's rounds)
+PW_CASES = [
+    (pw_case("pw_k333_bf16_d128", T=8, H=12, W=24, heads=8, head_dim=128, seed=90), 2),
+    (pw_case("pw_k377_bf16_d128", T=3, H=8, W=11, heads=2, head_dim=128, kh=7, kw=7, seed=91), 5),
+    (pw_case("pw_k355_bf16_d64", T=6, H=12, W=24, heads=10, kh=5, kw=5, seed=92), 5),
+    (pw_case("pw_k333_f32_d32", T=3, H=7, W=10, heads=2, head_dim=32, dtype="f32", seed=93), 2),
+    (pw_case("pw_k335_f32_d64", T=6, H=12, W=24, heads=10, kw=5, dtype="f32", seed=94), 5),
+]
+
+
+@pytest.mark.parametrize("w", [c[0] for c in PW_CASES], ids=lambda w: w.name)
+def test_predicted_weights_parity(w):
+    """Some logits are -inf (weight 0), up to a row's first 20 points."""
+    import paper_2607_22696_amd as dsa
+    bf = w.dtype == "bf16"
+    logits, v, off, dout = testgen.gen_pw_inputs(w)
+    lead = np.arange(logits[..., 0].size).reshape(logits.shape[:-1]) % 21
+    for p in range(20):
+        logits[..., p][lead > p] = -np.inf
+    ld, od = to_device(logits, False), to_device(off, False)
+    vd, gd = to_device(v, bf), to_device(dout, bf)
+    kern = (w.kt, w.kh, w.kw)
+    out, lse = dsa.pw_forward(ld, vd, od, kernel=kern)
+    grads = dsa.pw_backward(ld, vd, od, lse, gd, kernel=kern)
+    torch.cuda.synchronize()
+    ref = oracle.pw_forward(shape9(w), w.dtype, logits, v, off)
+    check("out", to_host(out).reshape(ref[0].shape), ref[0], bf)
+    check("lse", to_host(lse).reshape(-1), ref[1], bf)
+    rdl, rdv, rdo = oracle.pw_backward(shape9(w), w.dtype, logits, v, off, dout)
+    for name, g, r in zip(("dlogits", "dv", "doff"), grads, (rdl, rdv, rdo)):
+        check(name, to_host(g), r, bf)
+
+
+def box_case(dtype, dim, kernel):
+    return case("box", T=20, H=20, W=36, heads=2, head_dim=dim, kt=kernel[0], kh=kernel[1],
+                kw=kernel[2], dtype=dtype, seed=83)
+
+
+BOX_CASES = [(box_case("bf16", 128, (3, 3, 3)), 2, 2), (box_case("bf16", 64, (3, 5, 5)), 5, 0),
+             (box_case("f32", 64, (3, 3, 3)), 2, 0), (box_case("f32", 64, (3, 5, 5)), 5, 5),
+             (box_case("f32", 32, (3, 7, 7)), 5, 5)]
+
+
+@pytest.mark.parametrize("w", [c[0] for c in BOX_CASES],
+                         ids=lambda w: f"{w.dtype}-{w.head_dim}-{w.kt}x{w.kh}x{w.kw}")
+def test_points_that_leave_the_box(w):
+    """Queries whose points lie close together each, but apart from their neighbours': further than
+    a wave's box reaches (rounds without shared slots), and within it but with more voxels than
+    there are slots (fewer rounds at a time).  A few points lie far outside the grid."""
     host = list(testgen.gen_inputs(w))
     host[4] = testgen.gen_tensor(w, testgen.TID_DOUT, w.qkv_shape(), w.dout, True)
     off = host[3]
-    off[:, :, :, 2::5] = np.sign(off[:, :, :, 2::5]) * (np.abs(off[:, :, :, 2::5]) * 40)
+    off[:, :, :10, 2::5, :, :, 0] += np.where(np.arange(2, w.W, 5) < 18, 25.0, -25.0)[:, None, None]
+    off[:, :, 10:, 1::2, :, :, 1] -= 8.0
     off[:, :, 1::7, 1::6, :, 3] = 1e4
     compare(w, host)
+
+
+def test_window_of_one_frame():
+    """Frames of 2.5 GB: the buffer window holds one of the two frames, and every row of the other
+    one is a global load.  The same heads on their own (a window of both frames) take the same sums
+    in the same order."""
+    import paper_2607_22696_amd as dsa
+    T, H, W, heads, few, D, kernel = 2, 400, 400, 60, 2, 128, (3, 1, 7)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+
+    def randn(*shape, dtype=torch.bfloat16):
+        return torch.randn(shape, generator=gen, device="cuda", dtype=dtype)
+
+    q, k, v, dout = (randn(1, T, H, W, heads, D) for _ in range(4))
+    off = randn(1, T, H, W, heads, 21, 3, dtype=torch.float32).mul_(0.5)
+    out, lse = dsa.forward(q, k, v, off, kernel=kernel)
+    dq, dk, dv, doff = dsa.backward(q, k, v, off, lse, dout, kernel=kernel)
+    part = [x[:, :, :, :, :few].contiguous() for x in (q, k, v, off, dout)]
+    out2, lse2 = dsa.forward(*part[:4], kernel=kernel)
+    dq2, dk2, dv2, doff2 = dsa.backward(*part[:4], lse2, part[4], kernel=kernel)
+    for name, a, b in (("out", out, out2), ("lse", lse, lse2), ("dq", dq, dq2),
+                       ("doff", doff, doff2)):
+        assert torch.equal(a[:, :, :, :, :few], b), name
+    for name, a, b in (("dk", dk, dk2), ("dv", dv, dv2)):  # the order of a voxel's entries differs
+        d = (a[:, :, :, :, :few] - b).abs().max().item()
+        say(f"  {name}: {d:.3e}")
+        assert d <= reorder_bound(21, b.abs().max().item()), name
 
 
 @pytest.mark.parametrize("dim", [64, 128])

@@ -27,6 +27,17 @@ def max_abs(got, ref):
     return float(np.max(np.abs(got - ref))) if ref.size else 0.0
 
 
+def reorder_bound(points: int, ref) -> float:
+    """Largest difference of two fp32 sums of the same dK / dV entries in different orders.
+
+    A voxel is a corner of about 8 x points entries.  Each addition rounds by at most 2^-23 of the
+    running sum (one unit in the last place: the matrix cores do not round to nearest), which is
+    taken to stay below the tensor's largest element; the two sums may err in opposite directions.
+    That is 5e-5 of the largest element at 27 points, where one entry that is lost or misplaced
+    changes an element by about its rms / sqrt(8 points), 7e-2."""
+    return 2 * 8 * points * 2.0 ** -23 * float(np.max(np.abs(np.asarray(ref, dtype=np.float64))))
+
+
 def to_device(a: np.ndarray, io_bf16: bool):
     import torch
     if a.dtype == np.uint16:
