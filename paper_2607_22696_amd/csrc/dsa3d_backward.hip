@@ -807,9 +807,7 @@ __device__ inline __attribute__((always_inline)) void bwd_slots_tile(
       constexpr bool kKeep = R <= 2;
       float4 rk[kKeep ? R : 1], rv[kKeep ? R : 1];
       if (!again) {
-        SlotVecs<D, BF16> vec;
-        vec.load(static_cast<const char*>(dout), qrow);
-        row_dots<D, BF16>(slot_rows<LY::kRowBytes>(g, v, win, b, m, global), lds, vec, ns);
+        row_dots<D, BF16>(slot_rows<LY::kRowBytes>(g, v, win, b, m, global), lds, dout, qrow, ns);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           if (r * L >= npts) break;
@@ -820,8 +818,7 @@ __device__ inline __attribute__((always_inline)) void bwd_slots_tile(
           if ((!kKeep || !single) && active && r * L + lp < npts) vrow[c0 + r * L + lp] = y;
         }
         wave_sync();
-        vec.load(static_cast<const char*>(q), qrow);
-        row_dots<D, BF16>(slot_rows<LY::kRowBytes>(g, k, win, b, m, global), lds, vec, ns);
+        row_dots<D, BF16>(slot_rows<LY::kRowBytes>(g, k, win, b, m, global), lds, q, qrow, ns);
         float part = 0.0f;
 #pragma unroll
         for (int r = 0; r < R; ++r) {

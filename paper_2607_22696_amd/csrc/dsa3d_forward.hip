@@ -214,11 +214,8 @@ __device__ inline __attribute__((always_inline)) void slots_tile(
       bool global;
       int n;
       npts = number_slots<R, WHOLE>(g, win, (uint32_t)g.heads * LY::kRowBytes, lds, pt, npts, n, global);
-      if constexpr (!PW) {
-        SlotVecs<D, BF16> vec;
-        vec.load(static_cast<const char*>(q), qrow);
-        row_dots<D, BF16>(slot_rows<LY::kRowBytes>(g, k, win, b, m, global), lds, vec, n);
-      }
+      if constexpr (!PW)
+        row_dots<D, BF16>(slot_rows<LY::kRowBytes>(g, k, win, b, m, global), lds, q, qrow, n);
       float mc = mx;
 #pragma unroll
       for (int r = 0; r < R; ++r) {

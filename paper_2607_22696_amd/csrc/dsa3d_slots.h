@@ -23,6 +23,8 @@
 //    as long).  As the A of v_mfma_f32_16x16x32_bf16 that lane is row l % 16 = 4 (slot % 4) +
 //    chunk and K group slot / 4; column n = 4 a + c of B holds the vector's chunk c in K group a
 //    and zeros elsewhere, so result (4 s + c, 4 a + c) is what chunk c of slot 4 a + s adds.
+//    An infinity or a NaN meets the zeros of the other groups, so a wave that sees a NaN takes
+//    its products again on the vector ALU, row by row.
 //  * row_sums: the slots are the products' K.  A row is read whole by D / 8 lanes; after eight
 //    loads a lane holds 8 channels of 8 slots, and byte permutes pair them into the B operand of
 //    one product per channel.  A holds the slots' coefficients byte by byte (a byte is exact in
@@ -419,77 +421,111 @@ struct SlotVecs {
   }
 };
 
-// val[w][s] = <vector of query w, row of slot s> for n slots.
-template <int D, bool BF16, bool GLOBAL>
-__device__ inline __attribute__((always_inline)) void row_dots_of(const SlotRows& rows,
-                                                                  SlotLds& lds,
-                                                                  const SlotVecs<D, BF16>& vec,
-                                                                  int n) {
-  const int lane = lane_id();
-  if constexpr (BF16) {
-    constexpr int KS = D / 32;
-    const uint32_t off = 16u * (lane & 3);
-    float* const out = &lds.val[lane & 3][(lane & 12) + (lane >> 4)];
-    for (int base = 0; base < n; base += 32) {
-      uint4 a[2][KS];
+// val[w][s] = <vector of query w, row of slot s> for n slots on the vector ALU, U loads in flight:
+// a row's lanes hold 16 bytes of it each, vec[w] the same 16 bytes of query w's vector.
+template <int D, bool BF16, bool GLOBAL, int U>
+__device__ inline __attribute__((always_inline)) void row_dots_valu(
+    const SlotRows& rows, SlotLds& lds, const uint4 (&vec)[kSlotQueries], int n) {
+  constexpr int L = D * (BF16 ? 2 : 4) / 16, SPL = 64 / L;
+  const int lane = lane_id(), sub = lane % L, grp = lane / L;
+  for (int base = 0; base < n; base += U * SPL) {
+    uint4 a[U];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const uint32_t e = lds.list[base + 16 * h + (lane >> 2)];  // past the end: no voxel
+    for (int i = 0; i < U; ++i)
+      a[i] = slot_load<GLOBAL>(rows, lds.list[base + i * SPL + grp], 16u * sub);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) a[h][ks] = slot_load<GLOBAL>(rows, e, off + 64u * ks);
+    for (int w = 0; w < kSlotQueries; ++w) {
+      float keep = 0.0f;
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        const float s = group_sum<L>(chunk_dot<BF16>(vec[w], a[i]));
+        keep = sub == i ? s : keep;
       }
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        float s[kSlotQueries];
-#pragma unroll
-        for (int w = 0; w < kSlotQueries; ++w) {
-          slot_f32x4_t c = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks)
-            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(slot_bf16x8_t, a[h][ks]),
-                __builtin_bit_cast(slot_bf16x8_t, vec.f[w][ks]), c, 0, 0, 0);
-          // lane l: results (4 (l / 16) + i, l % 16); chunk l % 4 of slot 4 ((l / 4) % 4) + l / 16
-          const float lo = lane & 1 ? c[1] : c[0], hi = lane & 1 ? c[3] : c[2];
-          s[w] = lane & 2 ? hi : lo;
-        }
-        // the sum over the four lanes of a slot, query l % 4's in lane l
-        const float u0 = (lane & 1 ? s[1] : s[0]) + dpp_mov<0xB1>(lane & 1 ? s[0] : s[1]);
-        const float u1 = (lane & 1 ? s[3] : s[2]) + dpp_mov<0xB1>(lane & 1 ? s[2] : s[3]);
-        out[base + 16 * h] = (lane & 2 ? u1 : u0) + dpp_mov<0x4E>(lane & 2 ? u0 : u1);
-      }
-    }
-  } else {
-    constexpr int L = D / 4, SPL = 64 / L;
-    const int sub = lane % L, grp = lane / L;
-    for (int base = 0; base < n; base += 8 * SPL) {
-      uint4 a[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        a[i] = slot_load<GLOBAL>(rows, lds.list[base + i * SPL + grp], 16u * sub);
-#pragma unroll
-      for (int w = 0; w < kSlotQueries; ++w) {
-        float keep = 0.0f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float s = group_sum<L>(chunk_dot<false>(vec.f[w][0], a[i]));
-          keep = sub == i ? s : keep;
-        }
-        if (sub < 8) lds.val[w][base + sub * SPL + grp] = keep;
-      }
+      if (sub < U) lds.val[w][base + sub * SPL + grp] = keep;
     }
   }
 }
 
+// The same on the matrix cores (bf16 rows).  Returns whether this lane saw a NaN: a row with an
+// infinity or a NaN meets the zeros of B and makes the products of three other slots NaN.
+template <int D, bool GLOBAL>
+__device__ inline __attribute__((always_inline)) bool row_dots_mfma(const SlotRows& rows,
+                                                                    SlotLds& lds,
+                                                                    const SlotVecs<D, true>& vec,
+                                                                    int n) {
+  const int lane = lane_id();
+  constexpr int KS = D / 32;
+  const uint32_t off = 16u * (lane & 3);
+  float* const out = &lds.val[lane & 3][(lane & 12) + (lane >> 4)];
+  bool nan = false;
+  for (int base = 0; base < n; base += 32) {
+    uint4 a[2][KS];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t e = lds.list[base + 16 * h + (lane >> 2)];  // past the end: no voxel
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) a[h][ks] = slot_load<GLOBAL>(rows, e, off + 64u * ks);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      float s[kSlotQueries];
+#pragma unroll
+      for (int w = 0; w < kSlotQueries; ++w) {
+        slot_f32x4_t c = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              __builtin_bit_cast(slot_bf16x8_t, a[h][ks]),
+              __builtin_bit_cast(slot_bf16x8_t, vec.f[w][ks]), c, 0, 0, 0);
+        // lane l: results (4 (l / 16) + i, l % 16); chunk l % 4 of slot 4 ((l / 4) % 4) + l / 16
+        const float lo = lane & 1 ? c[1] : c[0], hi = lane & 1 ? c[3] : c[2];
+        s[w] = lane & 2 ? hi : lo;
+      }
+      // the sum over the four lanes of a slot, query l % 4's in lane l
+      const float u0 = (lane & 1 ? s[1] : s[0]) + dpp_mov<0xB1>(lane & 1 ? s[0] : s[1]);
+      const float u1 = (lane & 1 ? s[3] : s[2]) + dpp_mov<0xB1>(lane & 1 ? s[2] : s[3]);
+      const float d = (lane & 2 ? u1 : u0) + dpp_mov<0x4E>(lane & 2 ? u0 : u1);
+      out[base + 16 * h] = d;
+      nan = nan || d != d;
+    }
+  }
+  return nan;
+}
+
+// val[w][s] = <row qrow[w] of x, row of slot s> for n slots.  A wave that sees a NaN forms its
+// products again row by row, so that a row with an infinity or a NaN reaches its own slot only.
+template <int D, bool BF16, bool GLOBAL>
+__device__ inline __attribute__((always_inline)) void row_dots_of(
+    const SlotRows& rows, SlotLds& lds, const char* x, const int64_t (&qrow)[kSlotQueries], int n) {
+  SlotVecs<D, BF16> vec;
+  vec.load(x, qrow);
+  if constexpr (BF16) {
+    const bool nan = row_dots_mfma<D, GLOBAL>(rows, lds, vec, n);
+    if (__builtin_amdgcn_ballot_w64(nan) != 0) {
+      uint4 own[kSlotQueries];
+#pragma unroll
+      for (int w = 0; w < kSlotQueries; ++w)
+        own[w] = *reinterpret_cast<const uint4*>(x + qrow[w] * (2 * D) + 16 * (lane_id() % (D / 8)));
+      wave_sync();
+      row_dots_valu<D, true, GLOBAL, 2>(rows, lds, own, n);
+    }
+  } else {
+    uint4 own[kSlotQueries];
+#pragma unroll
+    for (int w = 0; w < kSlotQueries; ++w) own[w] = vec.f[w][0];
+    row_dots_valu<D, false, GLOBAL, 8>(rows, lds, own, n);
+  }
+}
+
 template <int D, bool BF16>
-__device__ inline __attribute__((always_inline)) void row_dots(const SlotRows& rows,
-                                                               SlotLds& lds,
-                                                               const SlotVecs<D, BF16>& vec,
+__device__ inline __attribute__((always_inline)) void row_dots(const SlotRows& rows, SlotLds& lds,
+                                                               const void* x,
+                                                               const int64_t (&qrow)[kSlotQueries],
                                                                int n) {
   if (!rows.global)
-    row_dots_of<D, BF16, false>(rows, lds, vec, n);
+    row_dots_of<D, BF16, false>(rows, lds, static_cast<const char*>(x), qrow, n);
   else
-    row_dots_of<D, BF16, true>(rows, lds, vec, n);
+    row_dots_of<D, BF16, true>(rows, lds, static_cast<const char*>(x), qrow, n);
   wave_sync();
 }
 

@@ -196,21 +196,85 @@ def test_window_of_one_frame():
         assert d <= reorder_bound(21, b.abs().max().item()), name
 
 
-@pytest.mark.parametrize("dim", [64, 128])
-def test_infinite_values_stay_where_they_are(dim):
-    """An infinite channel of a V row makes that channel of the queries that sample it infinite
-    (or NaN where signs meet), as a plain sum does, and touches no other channel or query."""
-    import paper_2607_22696_amd as dsa
-    w = case("inf", T=3, H=6, W=10, heads=1, head_dim=dim, dtype="bf16", seed=84)
+# Rows with an infinity: a bf16 grid of 16,384 rows (FINITE_CASES, asserted to take the slots), every
+# offset +0.25, so that voxel (t, i, j) is a corner of the points of the queries (t-2 .. t+1, ...).
+def finite_case(dim, kernel, dtype="bf16"):
+    return case("finite", T=4, H=16, W=32, heads=8, head_dim=dim, kt=kernel[0], kh=kernel[1],
+                kw=kernel[2], dtype=dtype, seed=84)
+
+
+FINITE_CASES = [(finite_case(128, (3, 3, 3)), 2, 2), (finite_case(128, (3, 5, 5)), 5, 5),
+                (finite_case(64, (3, 3, 3)), 2, 0), (finite_case(64, (3, 5, 5)), 5, 0),
+                (finite_case(32, (3, 5, 5), "f32"), 5, 5)]
+VOXEL = (1, 8, 13)
+
+
+def finite_id(w):
+    return f"{w.dtype}-{w.head_dim}-{w.kt}x{w.kh}x{w.kw}"
+
+
+def finite_inputs(w, offset=0.25):
+    bf = w.dtype == "bf16"
     q, k, v, off, _ = testgen.gen_inputs(w)
-    off = np.full_like(off, 0.25)
-    qd, kd, vd = (to_device(a, True) for a in (q, k, v))
-    od = to_device(off, False)
-    clean = to_host(dsa.forward(qd, kd, vd, od)[0])
-    vd[0, 1, 2, 3, 0, 5] = float("inf")
-    got = to_host(dsa.forward(qd, kd, vd, od)[0])
-    hit = np.zeros(clean.shape, bool)
-    # the queries whose 3x3x3 points at +0.25 have voxel (1, 2, 3) among their corners
-    hit[0, 0:3, 0:4, 1:5, 0, 5] = True
-    assert np.array_equal(got[~hit], clean[~hit])
-    assert np.all(np.isposinf(got[hit]))
+    dout = testgen.gen_tensor(w, testgen.TID_DOUT, w.qkv_shape(), w.dout, True)
+    off = np.full_like(off, offset)
+    return tuple(to_device(a, bf) for a in (q, k, v)) + (to_device(off, False), to_device(dout, bf))
+
+
+def samplers(w):
+    """Queries (head 0) that have VOXEL among the corners of their points at +0.25."""
+    hit = np.zeros((w.B, w.T, w.H, w.W, w.heads), bool)
+    at = [slice(max(c - r - 1, 0), c + r + 1) for c, r in
+          zip(VOXEL, ((w.kt - 1) // 2, (w.kh - 1) // 2, (w.kw - 1) // 2))]
+    hit[0, at[0], at[1], at[2], 0] = True
+    return hit
+
+
+def close(w, got, want):
+    """Sums taken again in another order: the tolerances of the file."""
+    check("elsewhere", got, want, w.dtype == "bf16")
+
+
+@pytest.mark.parametrize("w", [c[0] for c in FINITE_CASES], ids=finite_id)
+def test_an_infinite_key_reaches_its_own_queries_only(w):
+    import paper_2607_22696_amd as dsa
+    q, k, v, off, dout = finite_inputs(w)
+    kern = (w.kt, w.kh, w.kw)
+    hit = samplers(w)
+    out0, lse0 = (to_host(x) for x in dsa.forward(q, k, v, off, kernel=kern))
+    good = dsa.forward(q, k, v, off, kernel=kern)[1]
+    dq0, _, _, do0 = dsa.backward(q, k, v, off, good, dout, kernel=kern)
+    k[(0,) + VOXEL + (0, 5)] = float("inf")
+    out, lse = dsa.forward(q, k, v, off, kernel=kern)
+    dq, _, _, do = dsa.backward(q, k, v, off, lse, dout, kernel=kern)
+    out, lse = to_host(out), to_host(lse)
+    for name, got, want in (("out", out, out0), ("lse", lse, lse0), ("dq", to_host(dq), to_host(dq0)),
+                            ("doff", to_host(do), to_host(do0))):
+        assert np.isfinite(got[~hit]).all(), name
+        close(w, got[~hit], want[~hit])
+
+
+@pytest.mark.parametrize("w", [c[0] for c in FINITE_CASES], ids=finite_id)
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_an_infinite_value_reaches_its_own_queries_only(w, value):
+    """An infinite channel of a V row makes that channel of the queries that sample it infinite, as
+    a plain sum does, and touches no other channel or query; in the backward every gradient of
+    those queries is lost, and no other."""
+    import paper_2607_22696_amd as dsa
+    q, k, v, off, dout = finite_inputs(w)
+    kern = (w.kt, w.kh, w.kw)
+    hit = samplers(w)
+    out0, lse = dsa.forward(q, k, v, off, kernel=kern)
+    dq0, _, _, do0 = dsa.backward(q, k, v, off, lse, dout, kernel=kern)
+    v[(0,) + VOXEL + (0, 5)] = value
+    out = to_host(dsa.forward(q, k, v, off, kernel=kern)[0])
+    dq, _, _, do = (to_host(x) for x in dsa.backward(q, k, v, off, lse, dout, kernel=kern))
+    channel = np.zeros(out.shape, bool)
+    channel[..., 5] = hit
+    assert np.array_equal(out[channel], np.full(channel.sum(), value, np.float32), equal_nan=True)
+    assert np.isfinite(out[~channel]).all()
+    close(w, out[~channel], to_host(out0)[~channel])
+    assert not np.isfinite(dq[hit]).any()
+    for name, got, want in (("dq", dq, to_host(dq0)), ("doff", do, to_host(do0))):
+        assert np.isfinite(got[~hit]).all(), name
+        close(w, got[~hit], want[~hit])

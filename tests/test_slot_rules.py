@@ -42,7 +42,7 @@ def rounds(tmp_path_factory):
 
 
 def test_the_slot_tests_reach_their_kernels(rounds):
-    for w, fwd, bwd in slots.CASES + slots.BOX_CASES:
+    for w, fwd, bwd in slots.CASES + slots.BOX_CASES + slots.FINITE_CASES:
         assert rounds(w)[:2] == (fwd, bwd), w.name
     for w, fwd in slots.PW_CASES:
         assert rounds(w)[2] == fwd, w.name
