@@ -807,38 +807,58 @@ __device__ inline __attribute__((always_inline)) void bwd_slots_tile(
       constexpr bool kKeep = R <= 2;
       float4 rk[kKeep ? R : 1], rv[kKeep ? R : 1];
       if (!again) {
-        row_dots<D, BF16>(slot_rows<LY::kRowBytes>(g, v, win, b, m, global), lds, dout, qrow, ns);
+        const SlotRows vrows = slot_rows<LY::kRowBytes>(g, v, win, b, m, global);
+        auto combine_v = [&] {
+          bool nan = false;
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          if (r * L >= npts) break;
-          float d[8];
-          pt[r].read(val, d);
-          const float4 y = corner_sums(pt[r], d);
-          if constexpr (kKeep) rv[r] = y;
-          if ((!kKeep || !single) && active && r * L + lp < npts) vrow[c0 + r * L + lp] = y;
-        }
-        wave_sync();
-        row_dots<D, BF16>(slot_rows<LY::kRowBytes>(g, k, win, b, m, global), lds, q, qrow, ns);
-        float part = 0.0f;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          if (r * L >= npts) break;
-          float d[8];
-          pt[r].read(val, d);
-          float4 y = corner_sums(pt[r], d);
-          y.x = exp2f(y.x * g.scale_log2 - lse2);
-          if constexpr (kKeep) rk[r] = y;
-          if (r * L + lp < npts) {
-            const int p = c0 + r * L + lp;
-            part = fmaf(y.x, kKeep ? rv[r].x : active ? vrow[p].x : 0.0f, part);
-            if ((!kKeep || !single) && active) krow[p] = y;
+          for (int r = 0; r < R; ++r) {
+            if (r * L >= npts) break;
+            float d[8];
+            pt[r].read(val, d);
+            const float4 y = corner_sums(pt[r], d);
+            nan = nan || y.x != y.x;
+            if constexpr (kKeep) rv[r] = y;
+            if ((!kKeep || !single) && active && r * L + lp < npts) vrow[c0 + r * L + lp] = y;
           }
+          return nan;
+        };
+        row_dots<D, BF16>(vrows, lds, dout, qrow, ns);
+        if (dots_again<BF16>(combine_v())) {
+          row_dots<D, BF16, true>(vrows, lds, dout, qrow, ns);
+          combine_v();
+        }
+        const SlotRows krows = slot_rows<LY::kRowBytes>(g, k, win, b, m, global);
+        float part;
+        auto combine_k = [&] {
+          bool nan = false;
+          part = 0.0f;
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            if (r * L >= npts) break;
+            float d[8];
+            pt[r].read(val, d);
+            float4 y = corner_sums(pt[r], d);
+            nan = nan || y.x != y.x;
+            y.x = exp2f(y.x * g.scale_log2 - lse2);
+            if constexpr (kKeep) rk[r] = y;
+            if (r * L + lp < npts) {
+              const int p = c0 + r * L + lp;
+              part = fmaf(y.x, kKeep ? rv[r].x : active ? vrow[p].x : 0.0f, part);
+              if ((!kKeep || !single) && active) krow[p] = y;
+            }
+          }
+          return nan;
+        };
+        row_dots<D, BF16>(krows, lds, q, qrow, ns);
+        if (dots_again<BF16>(combine_k())) {
+          row_dots<D, BF16, true>(krows, lds, q, qrow, ns);
+          combine_k();
         }
         delta += group_sum<L>(part);
       }
       if (again || single) {
-        // ds_p of the chunk's points, and their magnitudes' sum for the fixed point
-        float ds[R], mag = 0.0f;
+        // ds_p of the chunk's points; one that is not finite makes every channel of dq NaN
+        float ds[R], bad = 0.0f;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           ds[r] = 0.0f;
@@ -854,17 +874,11 @@ __device__ inline __attribute__((always_inline)) void bwd_slots_tile(
               da = rv[kKeep ? r : 0].x;
             }
             ds[r] = alpha * (da - delta);
-            mag += fabsf(ds[r]);
+            bad = fmaf(0.0f, ds[r], bad);
           }
         }
-        mag = group_sum<L>(mag);
-        const float fix = slot_scale(mag);
-        clear_coefs(lds, ns);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          if (r * L >= npts) break;
-          if (r * L + lp < npts) add_coefs(pt[r], val, ds[r] * fix);
-        }
+        bad = group_sum<L>(bad);
+        sum_coefs<R>(lds, pt, ds, npts, ns);
         if constexpr (kKeep) {
           if (single) {  // the points are done with before the sums need the registers
             uint32_t slot[R];
@@ -888,7 +902,7 @@ __device__ inline __attribute__((always_inline)) void bwd_slots_tile(
         float part[U::kVec];
         row_sums<D, BF16>(slot_rows<LY::kRowBytes>(g, k, win, b, m, global), lds, ns, part);
 #pragma unroll
-        for (int x = 0; x < U::kVec; ++x) sum[x] = fmaf(part[x], mag / kSlotOne, sum[x]);
+        for (int x = 0; x < U::kVec; ++x) sum[x] += part[x] + bad;
       }
       if (single) break;
       c0 += npts;

@@ -214,28 +214,40 @@ __device__ inline __attribute__((always_inline)) void slots_tile(
       bool global;
       int n;
       npts = number_slots<R, WHOLE>(g, win, (uint32_t)g.heads * LY::kRowBytes, lds, pt, npts, n, global);
-      if constexpr (!PW)
-        row_dots<D, BF16>(slot_rows<LY::kRowBytes>(g, k, win, b, m, global), lds, q, qrow, n);
+      if constexpr (!PW) {
+        const SlotRows rows = slot_rows<LY::kRowBytes>(g, k, win, b, m, global);
+        auto combine = [&] {
+          bool nan = false;
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            if (r * L >= npts) break;
+            float w[8], d[8];
+            pt[r].weights(w);
+            pt[r].read(val, d);
+            s[r] = 0.0f;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) s[r] = fmaf(w[c], d[c], s[r]);
+            nan = nan || s[r] != s[r];
+            s[r] *= g.scale_log2;
+          }
+          return nan;
+        };
+        row_dots<D, BF16>(rows, lds, q, qrow, n);
+        if (dots_again<BF16>(combine())) {
+          row_dots<D, BF16, true>(rows, lds, q, qrow, n);
+          combine();
+        }
+      }
       float mc = mx;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if (r * L >= npts) break;
-        if constexpr (!PW) {
-          float w[8], d[8];
-          pt[r].weights(w);
-          pt[r].read(val, d);
-          s[r] = 0.0f;
-#pragma unroll
-          for (int c = 0; c < 8; ++c) s[r] = fmaf(w[c], d[c], s[r]);
-          s[r] *= g.scale_log2;
-        }
         if (r * L + lp >= npts) s[r] = -INFINITY;
         mc = fmaxf(mc, s[r]);
       }
       mc = lane_maxf<L>(mc);
       const float corr = mx == mc ? 1.0f : exp2f(mx - mc);  // the first chunk: 0 (or of zeros)
       mx = mc;
-      clear_coefs(lds, n);
       float lc = 0.0f;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
@@ -248,16 +260,11 @@ __device__ inline __attribute__((always_inline)) void slots_tile(
       }
       lc = group_sum<L>(lc);
       l = fmaf(l, corr, lc);
-      const float fix = slot_scale(lc);
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if (r * L >= npts) break;
-        if (r * L + lp < npts) add_coefs(pt[r], val, s[r] * fix);
-      }
+      sum_coefs<R>(lds, pt, s, npts, n);
       float sum[U::kVec];
       row_sums<D, BF16>(slot_rows<LY::kRowBytes>(g, v, win, b, m, global), lds, n, sum);
 #pragma unroll
-      for (int x = 0; x < U::kVec; ++x) o[x] = fmaf(o[x], corr, sum[x] * (lc / kSlotOne));
+      for (int x = 0; x < U::kVec; ++x) o[x] = fmaf(o[x], corr, sum[x]);
       c0 += npts;
     }
     if (!active) continue;

@@ -27,15 +27,19 @@
 //    its products again on the vector ALU, row by row.
 //  * row_sums: the slots are the products' K.  A row is read whole by D / 8 lanes; after eight
 //    loads a lane holds 8 channels of 8 slots, and byte permutes pair them into the B operand of
-//    one product per channel.  A holds the slots' coefficients byte by byte (a byte is exact in
-//    bf16), one byte of one query per row, so that one product takes them all.
+//    one product per channel.  A holds the slots' fp32 coefficients as three bf16 parts (8 bits
+//    each, exact), one part of one query per row, so that one product takes them all.
 // fp32 rows take the vector ALU: products and sums in fp32.
 //
-// Coefficients are summed per slot in LDS as 32-bit fixed-point numbers, 2^30 standing for the sum
-// of the magnitudes of the query's coefficients: each corner adds at most 2^-31 of that sum as
-// rounding, less than the rounding of an fp32 sum of the row.  (An LDS float add takes 194
-// cycles of a compute unit per instruction and an integer add 11, with addresses as they come
-// here.)
+// Coefficients are summed per slot and query in LDS as 32-bit integers with a block exponent: a
+// first round of integer maxima finds the largest magnitude that a corner adds to the slot, and
+// the corners are then added at 2^-25 (up to 32 points; 2^-23 up to 80) of its power of two.  The
+// sum cannot overflow, since a point adds to a slot once, and what is rounded off a corner is at
+// most the rounding of an fp32 sum of that slot, however small the slot's coefficients are beside
+// the query's others.  (An LDS float add takes 194 cycles of a compute unit per instruction and
+// an integer add 11, with addresses as they come here.  One scale per query, without the maxima,
+// takes 23.2 instead of 24.6 ms at 64x68x120, 24 heads x 128, 3x3x3, and 199 instead of 230 us at
+// 16x32x32, 8 x 64, but a coefficient then keeps only the bits above 2^-31 of the query's sum.)
 #pragma once
 
 #include "dsa3d_device.h"
@@ -80,6 +84,7 @@ __device__ inline __attribute__((always_inline)) void wave_sync() {
 __device__ inline __attribute__((always_inline)) int lane_id() {
   int l = threadIdx.x & 63;
   asm volatile("" : "+v"(l));
+  __builtin_assume(l >= 0 && l < 64);
   return l;
 }
 
@@ -252,9 +257,10 @@ struct SlotPoint {
     const uint32_t s = e < 2 ? s01 : s23;
     return (int)(e & 1 ? s >> 16 : s & 0xffffu);
   }
-  // weights of the corners c = 4 cz + 2 cy + cx
-  __device__ inline __attribute__((always_inline)) void weights(float (&w)[8]) const {
-    const float ax[2] = {1.0f - fx, fx}, ay[2] = {1.0f - fy, fy}, az[2] = {1.0f - fz, fz};
+  // weights of the corners c = 4 cz + 2 cy + cx, times f
+  __device__ inline __attribute__((always_inline)) void weights(float (&w)[8],
+                                                                float f = 1.0f) const {
+    const float ax[2] = {f * (1.0f - fx), f * fx}, ay[2] = {1.0f - fy, fy}, az[2] = {1.0f - fz, fz};
 #pragma unroll
     for (int c = 0; c < 8; ++c) w[c] = ax[c & 1] * (ay[(c >> 1) & 1] * az[c >> 2]);
   }
@@ -398,25 +404,22 @@ __device__ inline __attribute__((always_inline)) int number_slots(const Geometry
 
 // ---------------------------------------------------------------------------- dot products
 
-// The four queries' vectors as row_dots takes them: bf16, the B operand of each 32-channel block;
-// fp32, the lane's 16 bytes of the row.
-template <int D, bool BF16>
+// The four queries' bf16 vectors as the B operand of each 32-channel block.
+template <int D>
 struct SlotVecs {
-  static constexpr int kParts = BF16 ? D / 32 : 1;
+  static constexpr int kParts = D / 32;
   uint4 f[kSlotQueries][kParts];
   __device__ inline __attribute__((always_inline)) void load(const char* x,
                                                              const int64_t (&row)[kSlotQueries]) {
-    constexpr int64_t kRowBytes = D * (BF16 ? 2 : 4);
     const int lane = lane_id();
-    const bool mine = !BF16 || (lane >> 4) == ((lane >> 2) & 3);
+    const bool mine = (lane >> 4) == ((lane >> 2) & 3);
 #pragma unroll
     for (int w = 0; w < kSlotQueries; ++w)
 #pragma unroll
       for (int k = 0; k < kParts; ++k) {
         f[w][k] = make_uint4(0u, 0u, 0u, 0u);
         if (mine)
-          f[w][k] = *reinterpret_cast<const uint4*>(
-              x + row[w] * kRowBytes + (BF16 ? 64 * k + 16 * (lane & 3) : 16 * (lane % (D / 4))));
+          f[w][k] = *reinterpret_cast<const uint4*>(x + row[w] * (2 * D) + 64 * k + 16 * (lane & 3));
       }
   }
 };
@@ -446,18 +449,17 @@ __device__ inline __attribute__((always_inline)) void row_dots_valu(
   }
 }
 
-// The same on the matrix cores (bf16 rows).  Returns whether this lane saw a NaN: a row with an
-// infinity or a NaN meets the zeros of B and makes the products of three other slots NaN.
+// The same on the matrix cores (bf16 rows).  A row with an infinity or a NaN meets the zeros of B
+// and makes the products of three other slots NaN.
 template <int D, bool GLOBAL>
-__device__ inline __attribute__((always_inline)) bool row_dots_mfma(const SlotRows& rows,
+__device__ inline __attribute__((always_inline)) void row_dots_mfma(const SlotRows& rows,
                                                                     SlotLds& lds,
-                                                                    const SlotVecs<D, true>& vec,
+                                                                    const SlotVecs<D>& vec,
                                                                     int n) {
   const int lane = lane_id();
   constexpr int KS = D / 32;
   const uint32_t off = 16u * (lane & 3);
   float* const out = &lds.val[lane & 3][(lane & 12) + (lane >> 4)];
-  bool nan = false;
   for (int base = 0; base < n; base += 32) {
     uint4 a[2][KS];
 #pragma unroll
@@ -484,49 +486,49 @@ __device__ inline __attribute__((always_inline)) bool row_dots_mfma(const SlotRo
       // the sum over the four lanes of a slot, query l % 4's in lane l
       const float u0 = (lane & 1 ? s[1] : s[0]) + dpp_mov<0xB1>(lane & 1 ? s[0] : s[1]);
       const float u1 = (lane & 1 ? s[3] : s[2]) + dpp_mov<0xB1>(lane & 1 ? s[2] : s[3]);
-      const float d = (lane & 2 ? u1 : u0) + dpp_mov<0x4E>(lane & 2 ? u0 : u1);
-      out[base + 16 * h] = d;
-      nan = nan || d != d;
+      out[base + 16 * h] = (lane & 2 ? u1 : u0) + dpp_mov<0x4E>(lane & 2 ? u0 : u1);
     }
   }
-  return nan;
 }
 
-// val[w][s] = <row qrow[w] of x, row of slot s> for n slots.  A wave that sees a NaN forms its
-// products again row by row, so that a row with an infinity or a NaN reaches its own slot only.
-template <int D, bool BF16, bool GLOBAL>
+// val[w][s] = <row qrow[w] of x, row of slot s> for n slots.  APART: row by row, so that a row with an
+// infinity or a NaN reaches its own slot only; for a wave whose points saw a NaN (dots_again).
+template <int D, bool BF16, bool GLOBAL, bool APART>
 __device__ inline __attribute__((always_inline)) void row_dots_of(
     const SlotRows& rows, SlotLds& lds, const char* x, const int64_t (&qrow)[kSlotQueries], int n) {
-  SlotVecs<D, BF16> vec;
-  vec.load(x, qrow);
-  if constexpr (BF16) {
-    const bool nan = row_dots_mfma<D, GLOBAL>(rows, lds, vec, n);
-    if (__builtin_amdgcn_ballot_w64(nan) != 0) {
-      uint4 own[kSlotQueries];
-#pragma unroll
-      for (int w = 0; w < kSlotQueries; ++w)
-        own[w] = *reinterpret_cast<const uint4*>(x + qrow[w] * (2 * D) + 16 * (lane_id() % (D / 8)));
-      wave_sync();
-      row_dots_valu<D, true, GLOBAL, 2>(rows, lds, own, n);
-    }
+  if constexpr (BF16 && !APART) {
+    SlotVecs<D> vec;
+    vec.load(x, qrow);
+    row_dots_mfma<D, GLOBAL>(rows, lds, vec, n);
   } else {
+    constexpr int kRowBytes = D * (BF16 ? 2 : 4);
     uint4 own[kSlotQueries];
 #pragma unroll
-    for (int w = 0; w < kSlotQueries; ++w) own[w] = vec.f[w][0];
-    row_dots_valu<D, false, GLOBAL, 8>(rows, lds, own, n);
+    for (int w = 0; w < kSlotQueries; ++w)
+      own[w] = *reinterpret_cast<const uint4*>(x + qrow[w] * kRowBytes +
+                                               16 * (lane_id() % (kRowBytes / 16)));
+    row_dots_valu<D, BF16, GLOBAL, BF16 ? 2 : 8>(rows, lds, own, n);
   }
 }
 
-template <int D, bool BF16>
+template <int D, bool BF16, bool APART = false>
 __device__ inline __attribute__((always_inline)) void row_dots(const SlotRows& rows, SlotLds& lds,
                                                                const void* x,
                                                                const int64_t (&qrow)[kSlotQueries],
                                                                int n) {
-  if (!rows.global)
-    row_dots_of<D, BF16, false>(rows, lds, static_cast<const char*>(x), qrow, n);
-  else
-    row_dots_of<D, BF16, true>(rows, lds, static_cast<const char*>(x), qrow, n);
   wave_sync();
+  if (!rows.global)
+    row_dots_of<D, BF16, false, APART>(rows, lds, static_cast<const char*>(x), qrow, n);
+  else
+    row_dots_of<D, BF16, true, APART>(rows, lds, static_cast<const char*>(x), qrow, n);
+  wave_sync();
+}
+
+// Whether the products have to be formed again row by row: some point of the wave combined them to
+// NaN.
+template <bool BF16>
+__device__ inline __attribute__((always_inline)) bool dots_again(bool nan) {
+  return BF16 && __builtin_amdgcn_ballot_w64(nan) != 0;
 }
 
 // ---------------------------------------------------------------------------- weighted sums
@@ -541,35 +543,88 @@ struct SlotSum {
   static constexpr int kBatch = 8 * kPer;   // slots of eight loads: load i takes slots 8 k + i
 };
 
-// Clears the coefficients of n slots (and of the rest of the last batch).
-__device__ inline __attribute__((always_inline)) void clear_coefs(SlotLds& lds, int n) {
-  const int lane = lane_id();
+// val[query][s] = the sum over the query's corners on slot s of c[r] * (the corner's weight), for
+// rounds of npts points per query; 0 for a slot that the query does not touch, a denormal number
+// (below 2^-141) where it does and the sum is zero.  Needs finite c; the exponents take the place
+// of the list, which waits in registers.
+template <int R>
+__device__ inline __attribute__((always_inline)) void sum_coefs(SlotLds& lds,
+                                                                const SlotPoint (&pt)[R],
+                                                                const float (&c)[R], int npts,
+                                                                int n) {
+  constexpr int L = kSlotLanes;
+  constexpr int kBits = R <= 2 ? 25 : 23;  // npts 2^(kBits + 1) < 2^31
+  static_assert(R * L <= 1 << (30 - kBits), "the sums fit 31 bits");
+  const int lane = lane_id(), lp = lane % L;
+  uint32_t* const val = reinterpret_cast<uint32_t*>(lds.val[lane / L]);
+  uint8_t* const expo = reinterpret_cast<uint8_t*>(lds.list) + (lane / L) * kSlotCap;
+  uint4* const l4 = reinterpret_cast<uint4*>(lds.list) + lane;
+  static_assert(kSlotCap == 640, "two and a half 16-byte words per lane");
   wave_sync();
-  for (int s = 4 * (lane & 15); s < ((n + 63) & ~63); s += 64)
-    *reinterpret_cast<float4*>(&lds.val[lane >> 4][s]) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  const uint4 list0 = l4[0], list1 = l4[64], list2 = lane < 32 ? l4[128] : list0;
+  for (int base = 0; base < n; base += 64)
+    *reinterpret_cast<uint4*>(val + base + 4 * lp) = make_uint4(0u, 0u, 0u, 0u);
   wave_sync();
-}
-
-// The factor that takes coefficients whose magnitudes sum to `sum` to fixed point.
-constexpr float kSlotOne = 1073741824.0f;  // 2^30
-__device__ inline __attribute__((always_inline)) float slot_scale(float sum) {
-  return kSlotOne / fmaxf(sum, 0x1p-60f);
-}
-
-// Adds a point's corner coefficients c * (its corner weights) to its query's slots; c in fixed
-// point.
-__device__ inline __attribute__((always_inline)) void add_coefs(const SlotPoint& pt, float* val,
-                                                                float c) {
-  float w[8];
-  pt.weights(w);
+  // the largest of the slot's magnitudes, exponent + 1 in the top byte (0: untouched)
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    int* p = reinterpret_cast<int*>(val) + pt.slot(e);
-    __hip_atomic_fetch_add(p, __float2int_rn(w[2 * e] * c), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_WAVEFRONT);
-    __hip_atomic_fetch_add(p + 1, __float2int_rn(w[2 * e + 1] * c), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_WAVEFRONT);
+  for (int r = 0; r < R; ++r) {
+    if (r * L >= npts) break;
+    if (r * L + lp >= npts) continue;
+    float w[8];
+    pt[r].weights(w, c[r]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      __hip_atomic_fetch_max(val + pt[r].slot(e >> 1) + (e & 1),
+                             (__float_as_uint(w[e]) << 1) + (1u << 24), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_WAVEFRONT);
   }
+  wave_sync();
+  for (int base = 0; base < n; base += 64) {
+    const int s = base + 4 * lp;
+    const uint4 m = *reinterpret_cast<const uint4*>(val + s);
+    const uint32_t lo = __builtin_amdgcn_perm(m.y, m.x, 0x0c0c0703u);
+    const uint32_t hi = __builtin_amdgcn_perm(m.w, m.z, 0x07030c0cu);
+    *reinterpret_cast<uint32_t*>(expo + s) = lo | hi;
+    *reinterpret_cast<uint4*>(val + s) = make_uint4(0u, 0u, 0u, 0u);
+  }
+  wave_sync();
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (r * L >= npts) break;
+    if (r * L + lp >= npts) continue;
+    float w[8];
+    pt[r].weights(w, c[r]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int s = pt[r].slot(e);
+      uint16_t b;  // of both slots of the pair, at any address
+      __builtin_memcpy(&b, expo + s, 2);
+#pragma unroll
+      for (int cx = 0; cx < 2; ++cx) {
+        const int bits = kBits + 128 - (int)(cx ? b >> 8 : b & 0xff);
+        __hip_atomic_fetch_add(reinterpret_cast<int*>(val) + s + cx,
+                               __float2int_rn(ldexpf(w[2 * e + cx], bits)), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WAVEFRONT);
+      }
+    }
+  }
+  wave_sync();
+  for (int base = 0; base < n; base += 64) {
+    const int s = base + 4 * lp;
+    const uint32_t b = *reinterpret_cast<const uint32_t*>(expo + s);
+    const int4 x = *reinterpret_cast<const int4*>(val + s);
+    auto coef = [](int x, uint32_t b) {
+      const float f = ldexpf((float)x, (int)b - 128 - kBits);
+      return x != 0 ? f : __uint_as_float(b);
+    };
+    *reinterpret_cast<float4*>(val + s) = make_float4(coef(x.x, b & 255u), coef(x.y, (b >> 8) & 255u),
+                                                      coef(x.z, (b >> 16) & 255u), coef(x.w, b >> 24));
+  }
+  wave_sync();
+  l4[0] = list0;
+  l4[64] = list1;
+  if (lane < 32) l4[128] = list2;
+  wave_sync();
 }
 
 // The part that lane l keeps of per-lane sums of the four queries: query l / 16, summed over the
@@ -592,8 +647,8 @@ __device__ inline __attribute__((always_inline)) float keep_sum(const float (&q)
   return __uint_as_float(c[0]) + __uint_as_float(c[1]);
 }
 
-// sum[x] = sum over n slots of val[query][s] * row s (the coefficients as they are, in fixed point),
-// in fp32 on the vector ALU.  SAFE: a row whose coefficient is zero is not touched.
+// sum[x] = sum over n slots of val[query][s] * row s in fp32 on the vector ALU.  SAFE: a row that a
+// query does not touch is not multiplied for it.
 template <int D, bool BF16, bool GLOBAL, bool SAFE>
 __device__ inline __attribute__((always_inline)) void row_sums_valu(
     const SlotRows& rows, const SlotLds& lds, int n, float (&sum)[SlotSum<D, BF16>::kVec]) {
@@ -611,12 +666,17 @@ __device__ inline __attribute__((always_inline)) void row_sums_valu(
     for (int i = 0; i < 8; ++i) a[i] = slot_load<GLOBAL>(rows, lds.list[at + i], 16u * sub);
 #pragma unroll
     for (int w = 0; w < kSlotQueries; ++w) {
-      const int4* c4 = reinterpret_cast<const int4*>(&lds.val[w][at]);
-      const int4 ca = c4[0], cb = c4[1];
-      const int c[8] = {ca.x, ca.y, ca.z, ca.w, cb.x, cb.y, cb.z, cb.w};
+      const float4* c4 = reinterpret_cast<const float4*>(&lds.val[w][at]);
+      const float4 ca = c4[0], cb = c4[1];
+      const float c[8] = {ca.x, ca.y, ca.z, ca.w, cb.x, cb.y, cb.z, cb.w};
 #pragma unroll
       for (int i = 0; i < 8; ++i)
-        if (!SAFE || c[i] != 0) chunk_axpy<BF16>(part[w], (float)c[i], a[i]);
+        if constexpr (SAFE) {  // a sum of zero counts: 0 * infinity
+          const uint32_t u = __float_as_uint(c[i]);
+          if (u != 0u) chunk_axpy<BF16>(part[w], u < 256u ? 0.0f : c[i], a[i]);
+        } else {
+          chunk_axpy<BF16>(part[w], c[i], a[i]);
+        }
     }
   }
 #pragma unroll
@@ -628,10 +688,10 @@ __device__ inline __attribute__((always_inline)) void row_sums_valu(
 
 // The same on the matrix cores (bf16 rows).  Lane l reads the row of slot base + 8 (l / kLanes) +
 // i; as the products' B its column is l % 16 and its K group l / 16, so a 16-lane group holds
-// SETS = 16 / kLanes sets of rows side by side.  A's row 4 s + p holds byte p (the top one signed) of
-// the coefficients of set s % SETS for query SETS (s / SETS) + t in product t; result element p
-// of lane group G is then byte p's share of the sum of set G % SETS, meant for the columns of
-// that set.
+// SETS = 16 / kLanes sets of rows side by side.  A's row 4 s + p holds part p (the upper, middle and
+// lower 8 bits; p = 3 is not used) of the coefficients of set s % SETS for query SETS (s / SETS) + t
+// in product t; result element p of lane group G is then part p's share of the sum of set
+// G % SETS, meant for the columns of that set.
 template <int D, bool GLOBAL>
 __device__ inline __attribute__((always_inline)) void row_sums_mfma(const SlotRows& rows,
                                                                     const SlotLds& lds, int n,
@@ -641,8 +701,7 @@ __device__ inline __attribute__((always_inline)) void row_sums_mfma(const SlotRo
   static_assert(SETS == 1 || SETS == 2, "head_dim 64 or 128");
   const int lane = lane_id(), sub = lane % U::kLanes, grp = lane / U::kLanes;
   const int a_s = (lane >> 2) & 3, a_set = a_s % SETS, a_q = a_s / SETS * SETS;
-  const int shift = 8 * (lane & 3);
-  const float bias = (lane & 3) == 3 ? 128.0f : 0.0f;
+  const uint32_t m1 = (lane & 3) >= 1 ? 0xffff0000u : 0u, m2 = (lane & 3) >= 2 ? 0xffff0000u : 0u;
   slot_f32x4_t acc[SETS][8];
 #pragma unroll
   for (int t = 0; t < SETS; ++t)
@@ -662,14 +721,16 @@ __device__ inline __attribute__((always_inline)) void row_sums_mfma(const SlotRo
     slot_bf16x8_t a[SETS];
 #pragma unroll
     for (int t = 0; t < SETS; ++t) {
-      const uint4* c4 = reinterpret_cast<const uint4*>(
+      const float4* c4 = reinterpret_cast<const float4*>(
           &lds.val[a_q + t][base + 8 * ((lane >> 4) * SETS + a_set)]);
-      const uint4 ca = c4[0], cb = c4[1];
-      const uint32_t c[8] = {ca.x, ca.y, ca.z, ca.w, cb.x, cb.y, cb.z, cb.w};
+      const float4 ca = c4[0], cb = c4[1];
+      const float c[8] = {ca.x, ca.y, ca.z, ca.w, cb.x, cb.y, cb.z, cb.w};
       uint32_t u[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i)  // this lane's byte: at most 8 bits, so exact as a bf16
-        u[i] = __float_as_uint((float)(((c[i] ^ 0x80000000u) >> shift) & 255u) - bias);
+      for (int i = 0; i < 8; ++i) {  // less the parts above this lane's; its part is the upper half
+        const float mid = c[i] - __uint_as_float(__float_as_uint(c[i]) & m1);
+        u[i] = __float_as_uint(mid - __uint_as_float(__float_as_uint(mid) & m2));
+      }
       a[t] = __builtin_bit_cast(
           slot_bf16x8_t, make_uint4(__builtin_amdgcn_perm(u[1], u[0], 0x07060302u),
                                     __builtin_amdgcn_perm(u[3], u[2], 0x07060302u),
@@ -705,8 +766,7 @@ __device__ inline __attribute__((always_inline)) void row_sums_mfma(const SlotRo
     float s[SETS];
 #pragma unroll
     for (int t = 0; t < SETS; ++t) {
-      s[t] = fmaf(acc[t][x][3], 0x1p24f, fmaf(acc[t][x][2], 0x1p16f,
-                                              fmaf(acc[t][x][1], 0x1p8f, acc[t][x][0])));
+      s[t] = acc[t][x][0] + (acc[t][x][1] + acc[t][x][2]);
       if constexpr (SETS == 2) {
         // lane groups 2 h and 2 h + 1 hold sets 0 and 1 of query 2 h + t: the sum of the two
         s[t] = (lane & 15) / U::kLanes == ((lane >> 4) & 1) ? s[t] : 0.0f;
@@ -721,9 +781,9 @@ __device__ inline __attribute__((always_inline)) void row_sums_mfma(const SlotRo
 }
 
 // sum[x]: channel kVec (l % kLanes) + x of the sum over n slots of coefficient * row for query
-// l / 16, the coefficients in fixed point.  An infinite or NaN row value meets the zero
-// coefficients of the queries that do not sample it, and on the matrix cores the zero bytes of
-// those that do, and gives NaN; a wave that sees a NaN takes its sums again without them.
+// l / 16.  An infinite or NaN row value meets the zero coefficients of the queries that do not
+// sample it, and on the matrix cores the zero parts of those that do, and gives NaN; a wave that
+// sees a NaN takes its sums again over the rows that each query samples.
 template <int D, bool BF16, bool GLOBAL>
 __device__ inline __attribute__((always_inline)) void row_sums_of(
     const SlotRows& rows, const SlotLds& lds, int n, float (&sum)[SlotSum<D, BF16>::kVec]) {

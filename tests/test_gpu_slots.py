@@ -255,13 +255,14 @@ def test_an_infinite_key_reaches_its_own_queries_only(w):
 
 
 @pytest.mark.parametrize("w", [c[0] for c in FINITE_CASES], ids=finite_id)
-@pytest.mark.parametrize("value", [float("inf"), float("nan")])
-def test_an_infinite_value_reaches_its_own_queries_only(w, value):
+@pytest.mark.parametrize("value,offset", [(float("inf"), 0.25), (float("nan"), 0.25),
+                                          (float("inf"), 2.0 ** -12), (float("inf"), 0.0)])
+def test_an_infinite_value_reaches_its_own_queries_only(w, value, offset):
     """An infinite channel of a V row makes that channel of the queries that sample it infinite, as
-    a plain sum does, and touches no other channel or query; in the backward every gradient of
-    those queries is lost, and no other."""
+    a plain sum does, however small its weight is (NaN where the weight is 0), and touches no other
+    channel or query; in the backward every gradient of those queries is lost, and no other."""
     import paper_2607_22696_amd as dsa
-    q, k, v, off, dout = finite_inputs(w)
+    q, k, v, off, dout = finite_inputs(w, offset)
     kern = (w.kt, w.kh, w.kw)
     hit = samplers(w)
     out0, lse = dsa.forward(q, k, v, off, kernel=kern)
@@ -271,10 +272,83 @@ def test_an_infinite_value_reaches_its_own_queries_only(w, value):
     dq, _, _, do = (to_host(x) for x in dsa.backward(q, k, v, off, lse, dout, kernel=kern))
     channel = np.zeros(out.shape, bool)
     channel[..., 5] = hit
-    assert np.array_equal(out[channel], np.full(channel.sum(), value, np.float32), equal_nan=True)
+    if offset == 0.0:
+        # NaN from corners of weight 0 (and inf - inf never: the weights are not negative)
+        assert not np.isfinite(out[channel]).any() and np.isnan(out[channel]).any()
+    else:
+        assert np.array_equal(out[channel], np.full(channel.sum(), value, np.float32),
+                              equal_nan=True)
     assert np.isfinite(out[~channel]).all()
     close(w, out[~channel], to_host(out0)[~channel])
     assert not np.isfinite(dq[hit]).any()
     for name, got, want in (("dq", dq, to_host(dq0)), ("doff", do, to_host(do0))):
         assert np.isfinite(got[~hit]).all(), name
         close(w, got[~hit], want[~hit])
+
+
+@pytest.mark.parametrize("w", [c[0] for c in FINITE_CASES], ids=finite_id)
+def test_powers_of_two_pass_through(w):
+    """Values near 1e30 and gradients near 1e-21: every sum is linear in V, K and dout, and scaling
+    by a power of two changes no bit of it while nothing overflows."""
+    import paper_2607_22696_amd as dsa
+    q, k, v, off, dout = finite_inputs(w)
+    kern, scale = (w.kt, w.kh, w.kw), 2.0 ** -3
+    up, down = 2.0 ** 100, 2.0 ** -70
+
+    def both(k, v, dout, scale):
+        out, lse = dsa.forward(q, k, v, off, kernel=kern, scale=scale)
+        dq, _, _, do = dsa.backward(q, k, v, off, lse, dout, kernel=kern, scale=scale)
+        return out, lse, dq, do
+
+    out, lse, dq, do = both(k, v, dout, scale)
+    # V 2^100 times as large and dout 2^-70 times: da, and with it dq and d_offsets, 2^30 times
+    o, s, g, d = both(k, v * up, dout * down, scale)
+    assert torch.equal(o, out * up) and torch.equal(s, lse)
+    assert torch.equal(g, dq * (up * down)) and torch.equal(d, do * (up * down))
+    o, s, g, d = both(k, v, dout * down, scale)
+    assert torch.equal(g, dq * down) and torch.equal(d, do * down)
+    # K 2^100 times as large and the scale 2^-100 times
+    o, s, g, d = both(k * up, v, dout, scale / up)
+    assert torch.equal(o, out) and torch.equal(s, lse)
+    assert torch.equal(g, dq) and torch.equal(d, do)
+
+
+@pytest.mark.parametrize("w,rounds", [(c[0], c[2]) for c in FINITE_CASES],
+                         ids=lambda x: finite_id(x) if hasattr(x, "dtype") else str(x))
+def test_a_small_weight_on_a_large_value_counts(w, rounds):
+    """Offsets of 2^-10: the upper corner of all three axes has weight 2^-30, about 2^-35 of the
+    row's sum with its softmax weight.  On a value of 2^36 it adds about 2 to a sum of size 1.
+    The coefficients' products and sums are fp32 (2^-24 each); the bf16 output adds 2^-9."""
+    import paper_2607_22696_amd as dsa
+    bf = w.dtype == "bf16"
+    q, k, v, off, _ = testgen.gen_inputs(w)
+    dout = testgen.gen_tensor(w, testgen.TID_DOUT, w.qkv_shape(), w.dout, True)
+    off = np.full_like(off, 2.0 ** -10)
+    voxel = (0, 3, 8, 13, 0, 5)
+    big = np.float32(2.0 ** 36)
+    value = np.uint16(big.view(np.uint32) >> 16) if bf else big
+    kern = (w.kt, w.kh, w.kw)
+    qd, od, gd = to_device(q, bf), to_device(off, False), to_device(dout, bf)
+
+    def check_near(name, got, ref, rel, small):
+        got, ref = got.astype(np.float64)[..., 5], ref.reshape(got.shape)[..., 5]
+        e = np.abs(got - ref) / (rel * np.abs(ref) + small)
+        say(f"  {name}: {e.max():.3f} of the bound")
+        assert e.max() <= 1.0, name
+
+    v1 = v.copy()
+    v1[voxel] = value
+    out, lse = dsa.forward(qd, to_device(k, bf), to_device(v1, bf), od, kernel=kern)
+    ref = oracle.forward(shape9(w), w.dtype, q, k, v1, off)[0]
+    check_near("out", to_host(out), ref, 2.0 ** -8 if bf else 1e-5, 1e-5)
+    if rounds == 0:  # the gathering dq subtracts Delta sum alpha k at the end: it cancels here
+        return
+    # K: channel 5 of q is 0, so that the logits stay as they are
+    q0, k1 = q.copy(), k.copy()
+    q0[..., 5] = 0
+    k1[voxel] = value
+    qd, kd, vd = to_device(q0, bf), to_device(k1, bf), to_device(v, bf)
+    out, lse = dsa.forward(qd, kd, vd, od, kernel=kern)
+    dq = dsa.backward(qd, kd, vd, od, lse, gd, kernel=kern)[0]
+    ref = oracle.backward(shape9(w), w.dtype, q0, k1, v, off, dout)[0]
+    check_near("dq", to_host(dq), ref, 2e-4, 2e-4)
