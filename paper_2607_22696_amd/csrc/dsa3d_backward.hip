@@ -28,7 +28,7 @@
 //     sums as matrix products (weights x q / dout rows) on the matrix cores; fp32: one
 //     L-lane group per 2 x 2 block of a frame, w_c * coefficient * q and * dout accumulated
 //     in registers.
-// Where rows are large enough (backward_rounds), a tile whose points lie close together leaves the
+// Where rows are large enough (backward_rounds), a wave whose points lie close together leaves the
 // V corners to phase 3: phase 1 only counts its points, and phase 3 reads each distinct voxel of
 // four neighbouring queries once per sweep (bwd_slots_tile, dsa3d_slots.h): dots of the V rows with
 // dout, of the K rows with q, and the sum of K rows for dq with Delta known.  V and K pass at
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_sweep_k
   int i, j;
   // All lanes of a group share the token: a whole group is idle or active, so neither the
   // group reductions nor the point sharing ever mix an idle group into an active one.
-  if (!query_token<false>(po, g, tl, wave * LY::kGroups + grp, i, j)) return;
+  if (!query_token<false, LY::kGroups>(po, g, tl, wave, grp, i, j)) return;
   const int n = t * HW + i * g.W + j;
   const int64_t row = ((int64_t)b * g.N + n) * g.heads + m;
 
@@ -379,14 +379,14 @@ __device__ inline __attribute__((always_inline)) void vpass_tile(
   // fetch indices and fractions with ds_bpermute and rebuild the rest, which measured faster
   // there (2.98 against 3.10 ms at 64x34x60; 88.7 against 87.2 ms at 64x68x120, head_dim 128).
   constexpr bool kSlots = L >= 16;
-  int4* const mine_at = pts + (kSlots ? slot_of<L, 9>(threadIdx.x) : 0);
+  int4* const mine_at = pts + (kSlots ? slot_of<L, 9>(lane) : 0);
 
   const int bh = tl.group;
   const int b = bh / g.by_heads, m = bh - b * g.heads;
   const int t = tl.frame;
   const RowWindow win = make_window<LY::kRowBytes>(g, v, v, b, m, t);  // V rows only
   int i, j;
-  if (!query_token<SLOTS>(po, g, tl, wave * LY::kGroups + grp, i, j)) return;  // a whole group idles
+  if (!query_token<SLOTS, LY::kGroups>(po, g, tl, wave, grp, i, j)) return;  // a whole group idles
   const int n = t * HW + i * g.W + j;
   const int64_t row = ((int64_t)b * g.N + n) * g.heads + m;
   const uint4 gr = load16(gb, row * LY::kRowBytes + lane_off);
@@ -446,7 +446,7 @@ __device__ inline __attribute__((always_inline)) void vpass_tile(
           gz[e] = pt.ax[e & 1] * pt.ay[e >> 1];
         }
       } else {
-        const int4* at = pts + slot_of<L, 9>(wave * 64 + grp * L) + kk * 9;
+        const int4* at = pts + slot_of<L, 9>(grp * L) + kk * 9;
         int vidx[8];
         const int4 i0 = at[0], i1 = at[1];
         vidx[0] = i0.x; vidx[1] = i0.y; vidx[2] = i0.z; vidx[3] = i0.w;
@@ -489,7 +489,7 @@ __device__ inline __attribute__((always_inline)) void vpass_tile(
 
 constexpr int kCountPoints = 4;
 
-// The counting alone, for the tiles whose points the slots will take: 16 lanes per token.
+// The counting alone, for the waves whose points the slots will take: 16 lanes per token.
 __device__ inline __attribute__((always_inline)) void count_tile(
     const Geometry& g, const PencilOrder& po, const PencilTile& tl,
     const float* __restrict__ offsets, uint32_t* __restrict__ counts,
@@ -526,23 +526,28 @@ __device__ inline __attribute__((always_inline)) void count_tile(
   }
 }
 
-// SLOTS: compact tiles are only counted here.
+// SLOTS: compact waves are only counted here.
 template <int D, bool BF16, bool SLOTS>
 __global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_vpass_kernel(
     Geometry g, const void* __restrict__ v, const float* __restrict__ offsets,
     const void* __restrict__ dout, RecV* __restrict__ recv, uint32_t* __restrict__ counts,
     uint32_t* __restrict__ ranks, PencilOrder po, int64_t vt0) {
   constexpr int L = Layout<D, BF16>::kLanes;
-  __shared__ int4 pts[L >= 16 ? slot_words<L, 9>() : 1];  // 8 words used, 9 for the banks
+  constexpr int kWords = slot_words<L, 9>();  // 8 words used, 9 for the banks
+  __shared__ int4 pts[L >= 16 ? kWavesPerBlock * kWords : 1];
   PencilTile tl;
   if (!pencil_tile(po, vt0 + blockIdx.x, tl)) return;
   if constexpr (SLOTS) {
-    if (compact_tile(g, po, tl, offsets, kBackwardBox)) {
+    const bool compact = g.P > 2 * kSlotLanes
+                             ? compact_wave<4>(g, po, tl, offsets, backward_box(BF16, g.P))
+                             : compact_wave<2>(g, po, tl, offsets, backward_box(BF16, g.P));
+    if (compact) {
       count_tile(g, po, tl, offsets, counts, ranks);
       return;
     }
   }
-  vpass_tile<D, BF16, SLOTS>(g, po, tl, v, offsets, dout, recv, counts, ranks, pts);
+  vpass_tile<D, BF16, SLOTS>(g, po, tl, v, offsets, dout, recv, counts, ranks,
+                             L >= 16 ? pts + (threadIdx.x >> 6) * kWords : pts);
 }
 
 // K pass: alpha_p from the logit and the forward's LSE, A_p = sum_c dw_c/dpos <q, K_c> (the
@@ -575,14 +580,14 @@ __device__ inline __attribute__((always_inline)) void kpass_tile(
   // magnitudes of the weights' position derivatives (the products of two axis weights),
   // window flag and cell, and the point's da_p.  The owner forms them once instead of every
   // lane of the row rebuilding them, which the VALU-bound point loop feels.
-  int4* const mine_at = pts + slot_of<L, 9>(threadIdx.x);
+  int4* const mine_at = pts + slot_of<L, 9>(lane);
 
   const int bh = tl.group;
   const int b = bh / g.by_heads, m = bh - b * g.heads;
   const int t = tl.frame;
   const RowWindow win = make_window<LY::kRowBytes>(g, k, k, b, m, t);  // K rows only
   int i, j;
-  if (!query_token<SLOTS>(po, g, tl, wave * LY::kGroups + grp, i, j)) return;  // a whole group idles
+  if (!query_token<SLOTS, LY::kGroups>(po, g, tl, wave, grp, i, j)) return;  // a whole group idles
   const int n = t * HW + i * g.W + j;
   const int64_t row = ((int64_t)b * g.N + n) * g.heads + m;
   const uint4 qr = load16(qb, row * LY::kRowBytes + lane_off);
@@ -635,7 +640,7 @@ __device__ inline __attribute__((always_inline)) void kpass_tile(
     const int nk = min(L, g.P - p0);
     float4 rec = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     for (int kk = 0; kk < nk; ++kk) {
-      const int4* at = pts + slot_of<L, 9>(wave * 64 + grp * L) + kk * 9;
+      const int4* at = pts + slot_of<L, 9>(grp * L) + kk * 9;
       int vidx[8];
       {
         const int4 i0 = at[0], i1 = at[1];
@@ -738,7 +743,7 @@ __device__ inline __attribute__((always_inline)) float4 corner_sums(const SlotPo
   return make_float4(s, x, y, z);
 }
 
-// Both passes over a compact tile at once (dsa3d_slots.h): the dot products of the slots' V rows
+// Both passes over a compact wave's tokens at once (dsa3d_slots.h): the dot products of the slots' V rows
 // with dout and of their K rows with q, per point da_p, B_p, alpha_p and A_p, Delta, and then,
 // with ds_p known, dq as the slots' weighted sum of K rows.  A row whose points are numbered
 // together keeps their values in registers (R <= 2) or finds them where it left them in the
@@ -950,7 +955,7 @@ __device__ inline __attribute__((always_inline)) void bwd_slots_tile(
   }
 }
 
-// R > 0: compact tiles take the slots, three waves per SIMD.  R = 0: every tile gathers; four
+// R > 0: compact waves take the slots, three waves per SIMD.  R = 0: every tile gathers; four
 // waves per SIMD at head_dim 128 with bf16 (133.2 -> 131.5 ms at 64x68x120, 3x5x5, U[-8, 8]).
 template <int D, bool BF16, int HOLD, int R, bool WHOLE>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((
@@ -961,21 +966,21 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((
     RecV* __restrict__ recv, const uint32_t* __restrict__ starts,
     const uint32_t* __restrict__ ranks, float* __restrict__ doff, Entry* __restrict__ entries,
     PencilOrder po, int64_t vt0) {
-  constexpr size_t kPts = slot_words<Layout<D, BF16>::kLanes, 9>() * sizeof(int4);
-  constexpr size_t kSlots = R > 0 ? kWavesPerBlock * sizeof(SlotLds) : 0;
-  __shared__ __attribute__((aligned(16))) char lds[kPts > kSlots ? kPts : kSlots];
+  constexpr size_t kLds = wave_lds<Layout<D, BF16>::kLanes, 9, (R > 0)>();
+  __shared__ __attribute__((aligned(16))) char block_lds[kWavesPerBlock * kLds];
+  char* const lds = block_lds + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * kLds;
   PencilTile tl;
   if (!pencil_tile(po, vt0 + blockIdx.x, tl)) return;
   if constexpr (R > 0) {
-    if (compact_tile(g, po, tl, offsets, kBackwardBox)) {
-      bwd_slots_tile<D, BF16, R, WHOLE>(
-          g, po, tl, q, k, v, offsets, lse, dout, dq, reck, recv, starts, ranks, doff, entries,
-          reinterpret_cast<SlotLds*>(lds)[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)]);
+    if (compact_wave<(R > 2 ? 4 : 2)>(g, po, tl, offsets, backward_box(BF16, g.P))) {  // as the V pass
+      bwd_slots_tile<D, BF16, R, WHOLE>(g, po, tl, q, k, v, offsets, lse, dout, dq, reck, recv,
+                                        starts, ranks, doff, entries,
+                                        *reinterpret_cast<SlotLds*>(lds));
       return;
     }
   }
-  kpass_tile<D, BF16, HOLD, (R > 0)>(g, po, tl, q, k, offsets, lse, dq, reck, recv, starts, ranks, doff,
-                            entries, reinterpret_cast<int4*>(lds));
+  kpass_tile<D, BF16, HOLD, (R > 0)>(g, po, tl, q, k, offsets, lse, dq, reck, recv, starts, ranks,
+                                     doff, entries, reinterpret_cast<int4*>(lds));
 }
 
 // ---------------------------------------------------------------------------- 2. scan

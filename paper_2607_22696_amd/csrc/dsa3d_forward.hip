@@ -1,8 +1,8 @@
 // Forward kernel of 3D Deformable Slide Attention (MegaSlide-DiT, Section 5.2, Eq. (1)).
 //
 // A query's P points have 8 P corner rows of K and of V, and the rate at which a compute unit takes
-// row requests bounds a kernel that loads them all.  A tile goes one of two ways, by the spread
-// of its points (compact_tile):
+// row requests bounds a kernel that loads them all.  A wave goes one of two ways, by the spread
+// of its points (compact_wave):
 //  * slots_tile: four neighbouring queries of a wave read each distinct voxel of their points
 //    once (dsa3d_slots.h), logits first, then one softmax, then the weighted sum of V;
 //  * gather_tile: an L-lane group owns one query row, loads the 8 K and 8 V rows of each point
@@ -53,13 +53,13 @@ __device__ inline __attribute__((always_inline)) void gather_tile(
   // The point each lane formed for the current chunk, read back by its row's lanes: corner
   // indices, weights, and for the global-load path its window flag and cell.  A row's lanes
   // are in one wave, whose LDS accesses complete in order: no barrier.
-  int4* const mine_at = pts + slot_of<L, 5>(threadIdx.x);
+  int4* const mine_at = pts + slot_of<L, 5>(lane);
 
   const int b = tl.group / g.by_heads, m = tl.group - b * g.heads;
   const int t = tl.frame;
   const RowWindow win = make_window<LY::kRowBytes>(g, k, v, b, m, t);
   int i, j;
-  const bool active = query_token<SLOTS>(po, g, tl, wave * LY::kGroups + grp, i, j);
+  const bool active = query_token<SLOTS, LY::kGroups>(po, g, tl, wave, grp, i, j);
   if (!active) {  // an idle row computes on a valid token and stores nothing
     i = min(i, g.H - 1);
     j = min(j, g.W - 1);
@@ -96,7 +96,7 @@ __device__ inline __attribute__((always_inline)) void gather_tile(
     const int nk = min(L, g.P - p0);
     for (int kk = 0; kk < nk; ++kk) {
       const int src = (grp * L + kk) << 2;
-      const int4* at = pts + slot_of<L, 5>(wave * 64 + grp * L) + kk * 5;
+      const int4* at = pts + slot_of<L, 5>(grp * L) + kk * 5;
       const int4 i0 = at[0], i1 = at[1], w0 = at[2], w1 = at[3];
       Point pt;
       pt.vidx[0] = i0.x; pt.vidx[1] = i0.y; pt.vidx[2] = i0.z; pt.vidx[3] = i0.w;
@@ -155,7 +155,7 @@ __device__ inline __attribute__((always_inline)) void gather_tile(
   }
 }
 
-// The same for tiles whose points lie close together, reading each voxel of four neighbouring
+// The same for waves whose points lie close together, reading each voxel of four neighbouring
 // queries once (dsa3d_slots.h).  A chunk of points (all of them up to 32, or 80) has its logits
 // complete before its softmax, so one maximum is taken per chunk and only rows of several chunks
 // rescale.
@@ -287,7 +287,7 @@ __device__ inline __attribute__((always_inline)) void slots_tile(
   }
 }
 
-// A tile goes one way or the other by the spread of its points (R = 0: every tile gathers).  Three
+// A wave goes one way or the other by the spread of its points (R = 0: every one gathers).  Three
 // waves per SIMD either way, and the same LDS.
 template <int D, bool BF16, bool PW, int R, bool WHOLE>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(R > 0 ? 3 : 1))) void
@@ -295,21 +295,20 @@ fwd_kernel(Geometry g, const void* __restrict__ q, const void* __restrict__ k,
            const void* __restrict__ v, const float* __restrict__ logits,
            const float* __restrict__ offsets, void* __restrict__ out, float* __restrict__ lse,
            PencilOrder po, int64_t vt0) {
-  constexpr size_t kPts = slot_words<Layout<D, BF16>::kLanes, 5>() * sizeof(int4);
-  constexpr size_t kSlots = R > 0 ? kWavesPerBlock * sizeof(SlotLds) : 0;
-  __shared__ __attribute__((aligned(16))) char lds[kPts > kSlots ? kPts : kSlots];
+  constexpr size_t kLds = wave_lds<Layout<D, BF16>::kLanes, 5, (R > 0)>();
+  __shared__ __attribute__((aligned(16))) char block_lds[kWavesPerBlock * kLds];
+  char* const lds = block_lds + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * kLds;
   PencilTile tl;
   if (!pencil_tile(po, vt0 + blockIdx.x, tl)) return;  // no pencil left on this XCD
   if constexpr (R > 0) {
-    if (compact_tile(g, po, tl, offsets, forward_box(D, BF16, R))) {  // the same in every wave
-      slots_tile<D, BF16, PW, R, WHOLE>(
-          g, po, tl, q, k, v, logits, offsets, out, lse,
-          reinterpret_cast<SlotLds*>(lds)[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)]);
+    if (compact_wave<(R > 2 ? 4 : 2)>(g, po, tl, offsets, forward_box(D, BF16, g.P))) {
+      slots_tile<D, BF16, PW, R, WHOLE>(g, po, tl, q, k, v, logits, offsets, out, lse,
+                                        *reinterpret_cast<SlotLds*>(lds));
       return;
     }
   }
   gather_tile<D, BF16, PW, (R > 0)>(g, po, tl, q, k, v, logits, offsets, out, lse,
-                           reinterpret_cast<int4*>(lds));
+                                    reinterpret_cast<int4*>(lds));
 }
 
 // ---------------------------------------------------------------------------- launch

@@ -14,8 +14,8 @@
 // the two bits of its four corner pairs, a scan over the words' bit counts numbers the set bits,
 // and the slot of a pair's lower x corner is the number of bits below it (its upper corner has the
 // next slot).  Points that leave the box, or need more slots than there are, are taken a round at
-// a time with slot = 8 lane + corner and the same sweeps: always correct, but slow, so tiles
-// whose points spread far are left to the kernels that load every corner (compact_tile).
+// a time with slot = 8 lane + corner and the same sweeps: always correct, but slow, so waves
+// whose points spread far are left to the code that loads every corner (compact_wave).
 //
 // The sweeps use the matrix cores for bf16 rows:
 //  * row_dots: lane l reads 16 bytes of the row of slot l / 4, so that four neighbouring lanes
@@ -134,6 +134,9 @@ __device__ inline __attribute__((always_inline)) uint32_t lane_scan(uint32_t v) 
 
 // ---------------------------------------------------------------------------- tiles
 
+// Tokens of a tile.
+DSA3D_TILE_FN int tile_tokens(const PencilOrder& o) { return o.run * o.cell; }
+
 // Token e of a tile (four neighbours to a wave of the slots): of a cell of four tokens along x, or
 // in raster order of the pencil's rectangle.  False if it is past the pencil or the grid.
 __device__ inline __attribute__((always_inline)) bool slot_token(const PencilOrder& po,
@@ -145,34 +148,6 @@ __device__ inline __attribute__((always_inline)) bool slot_token(const PencilOrd
   const bool in = pencil_cell(po, tl, e / kSlotQueries, i, cell);
   j = cell * kSlotQueries + e % kSlotQueries;
   return in && j < g.W;
-}
-
-// Whether a tile is worth numbering: the points (up to 64) of its first token, with their corners,
-// span at most `limit` voxels.
-__device__ inline __attribute__((always_inline)) bool compact_tile(const Geometry& g,
-                                                                   const PencilOrder& po,
-                                                                   const PencilTile& tl,
-                                                                   const float* offsets,
-                                                                   int limit) {
-  const int b = tl.group / g.by_heads, m = tl.group - b * g.heads;
-  int i, j;
-  slot_token(po, g, tl, 0, i, j);
-  i = min(i, g.H - 1);  // a tile past a ragged pencil's end: any token will do
-  j = min(j, g.W - 1);
-  const int64_t row = ((int64_t)b * g.N + ((tl.frame * g.H + i) * g.W + j)) * g.heads + m;
-  const int p = min((int)(threadIdx.x & 63), g.P - 1);
-  const float* off = offsets + (row * g.P + p) * 3;
-  const int it = p / g.by_khw, rp = p - it * (g.kh * g.kw), ih = rp / g.by_kw, iw = rp - ih * g.kw;
-  int x, y, z;
-  float f;
-  axis((float)(j + iw - (g.kw - 1) / 2), off[0], g.W, x, f);
-  axis((float)(i + ih - (g.kh - 1) / 2), off[1], g.H, y, f);
-  axis((float)(tl.frame + it - (g.kt - 1) / 2), off[2], g.T, z, f);
-  // extents, each at most 256 so that the product stays in range
-  const int ex = min(-lane_min<64>(-x) - lane_min<64>(x), 255) + 2;
-  const int ey = min(-lane_min<64>(-y) - lane_min<64>(y), 255) + 2;
-  const int ez = min(-lane_min<64>(-z) - lane_min<64>(z), 255) + 2;
-  return __builtin_amdgcn_readfirstlane(ex * ey * ez) <= limit;
 }
 
 // ---------------------------------------------------------------------------- rows
@@ -275,6 +250,56 @@ struct SlotPoint {
     }
   }
 };
+
+// Whether a wave's queries (every fourth four of the tile's tokens) are worth numbering: the points
+// of each, with their corners, span at most `limit` voxels.  All points up to 16 SAMPLES, else so
+// many of them, evenly spread.  Each wave decides for itself, so that a calm token beside wide ones
+// sends none of those to the rounds without shared slots: with offsets N(0, 0.5) at every second
+// token and U[-8, 8] at the others, 16x34x60, 24 heads x 128 bf16, 3x3x3, a step takes 9.3 ms (9.3
+// loading every corner), and took 13.3 where the first token of a workgroup decided for all of them.
+template <int SAMPLES>
+__device__ inline __attribute__((always_inline)) bool compact_wave(const Geometry& g,
+                                                                   const PencilOrder& po,
+                                                                   const PencilTile& tl,
+                                                                   const float* offsets,
+                                                                   int limit) {
+  constexpr int kPoints = SAMPLES * kSlotLanes;
+  const int lane = threadIdx.x & 63, lp = lane % kSlotLanes;
+  const int b = tl.group / g.by_heads, m = tl.group - b * g.heads;
+  bool wide = false;
+  for (int e0 = kSlotQueries * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+       e0 < tile_tokens(po); e0 += kWavesPerBlock * kSlotQueries) {
+    int i, j;
+    slot_token(po, g, tl, e0 + lane / kSlotLanes, i, j);
+    i = min(i, g.H - 1);  // an idle query: the valid token that stands in for it
+    j = min(j, g.W - 1);
+    const int64_t row = ((int64_t)b * g.N + ((tl.frame * g.H + i) * g.W + j)) * g.heads + m;
+    const float* off = offsets + row * g.P * 3;
+    SlotPoint pt[SAMPLES];
+#pragma unroll
+    for (int u = 0; u < SAMPLES; ++u) {
+      const int s = lp + u * kSlotLanes;
+      const int p = g.P > kPoints ? s * g.P / kPoints : min(s, g.P - 1);
+      pt[u].set(g, tl.frame, i, j, p, off + 3 * p);
+    }
+    int x0 = pt[0].x, x1 = x0, y0 = pt[0].y, y1 = y0, z0 = pt[0].z, z1 = z0;
+#pragma unroll
+    for (int u = 1; u < SAMPLES; ++u) {
+      x0 = min(x0, pt[u].x);
+      x1 = max(x1, pt[u].x);
+      y0 = min(y0, pt[u].y);
+      y1 = max(y1, pt[u].y);
+      z0 = min(z0, pt[u].z);
+      z1 = max(z1, pt[u].z);
+    }
+    // extents with the upper corners, each at most 257 so that the product stays in range
+    const int ex = min(-lane_min<kSlotLanes>(-x1) - lane_min<kSlotLanes>(x0), 255) + 2;
+    const int ey = min(-lane_min<kSlotLanes>(-y1) - lane_min<kSlotLanes>(y0), 255) + 2;
+    const int ez = min(-lane_min<kSlotLanes>(-z1) - lane_min<kSlotLanes>(z0), 255) + 2;
+    wide = wide || ex * ey * ez > limit;
+  }
+  return __builtin_amdgcn_ballot_w64(wide) == 0;
+}
 
 // WHOLE: the window spans all frames, so no corner can lie outside it.
 //
@@ -840,17 +865,28 @@ inline PencilOrder query_order(const Geometry& g, bool slots, bool fill = false)
   return o;
 }
 
-// Tokens of a tile.
-DSA3D_TILE_FN int tile_tokens(const PencilOrder& o) { return o.run * o.cell; }
-
-// Token e of a tile in that order; false if it is past the tile, the pencil or the grid.
-template <bool SLOTS>
+// Token of row group `grp` of a gathering wave; false if it is past the tile, the pencil or the grid.
+// SLOTS: the tokens that the wave would take by slots, four and four.
+template <bool SLOTS, int GROUPS>
 __device__ inline __attribute__((always_inline)) bool query_token(const PencilOrder& po,
                                                                   const Geometry& g,
-                                                                  const PencilTile& tl, int e,
-                                                                  int& i, int& j) {
-  if constexpr (SLOTS) return slot_token(po, g, tl, e, i, j) && e < tile_tokens(po);
-  return pencil_cell(po, tl, e, i, j);
+                                                                  const PencilTile& tl, int wave,
+                                                                  int grp, int& i, int& j) {
+  if constexpr (SLOTS) {
+    constexpr int Q = kSlotQueries;
+    static_assert(GROUPS % Q == 0, "whole fours");
+    const int e = Q * wave + grp % Q + grp / Q * (kWavesPerBlock * Q);
+    return slot_token(po, g, tl, e, i, j) && e < tile_tokens(po);
+  }
+  return pencil_cell(po, tl, wave * GROUPS + grp, i, j);
+}
+
+// LDS of one wave of a kernel that keeps N 16-byte words per lane and, with SLOTS, may take its tokens
+// by slots instead.
+template <int L, int N, bool SLOTS>
+constexpr size_t wave_lds() {
+  constexpr size_t pts = slot_words<L, N>() * sizeof(int4);
+  return SLOTS && sizeof(SlotLds) > pts ? sizeof(SlotLds) : pts;
 }
 
 // Launches one workgroup per virtual tile, at most kMaxBlocks (a multiple of 8, which keeps a tile

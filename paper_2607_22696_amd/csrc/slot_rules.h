@@ -22,12 +22,18 @@ constexpr bool slot_rows_ok(int D, bool bf16) {
 // channels, 16x34x60 1.14 / 1.06, 3x21x96 (2 heads) 19 / 24 us.  A grid of few rows waits for one
 // wave's sweeps, which are a longer chain than the points' (4x14x21, 2 heads, forward: 64 fp32
 // channels 3x3x3 57 / 82 us, 3x5x5 119 / 144; 64 bf16 3x3x3 39 / 64, 3x7x7 122 / 194) except for
-// rows of 32 fp32 channels, eight to a load (4x8x8, 3x3x3 17 / 11), and many points of 128 bf16
-// channels (4x14x21, 3x7x7 238 / 207).
+// many points of 128 bf16 channels (forward, 3x5x5 and 3x7x7: 2x6x6, 1 head 52 / 23 and 98 / 40 us,
+// 4x8x8, 2 heads 54 / 23 and 101 / 44, 4x14x21, 2 heads 116 / 46 and 221 / 87) and for rows of 32
+// fp32 channels, eight to a load (3x3x3, 3x5x5 and 3x7x7: 2x6x6, 1 head 16.5 / 13.1, 39 / 19 and 73 /
+// 32, 4x8x8, 2 heads 17.1 / 13.0, 40 / 19 and 73 / 34, 4x14x21, 2 heads 17.6 / 20.8, 40 / 36 and 74 /
+// 69, 6x16x16, 4 heads 29.5 / 27.2, 74 / 48 and 140 / 93); of these, up to 32 points gather from
+// kFewRows32 to kSlotRows32 rows (3x12x20, 2 heads 17.4 / 21.8).
 constexpr int64_t kSlotRows = 16384;
+constexpr int64_t kFewRows32 = 1024, kSlotRows32 = 4096;
 
 constexpr bool few_rows(int D, bool bf16, int64_t rows, int P) {
-  return D > 32 && !(bf16 && D == 128 && P > 2 * kSlotLanes) && rows < kSlotRows;
+  if (D <= 32) return P <= 2 * kSlotLanes && rows >= kFewRows32 && rows < kSlotRows32;
+  return !(bf16 && D == 128 && P > 2 * kSlotLanes) && rows < kSlotRows;
 }
 
 // The predicted-weights variant reads V only, half of what sharing saves: 64 bf16 channels, 64x34x60,
@@ -50,16 +56,31 @@ constexpr int backward_rounds(int D, bool bf16, int64_t rows, int P) {
   return 5;
 }
 
-// Spread of a compact tile (compact_tile).  Offsets U[-3, 3] span about 700 voxels at 3x3x3 and 1090
-// at 3x5x5, U[-4, 4] 1250 and 1770.  16x34x60 (fp32: 9x33x47), gathering / by slots.  Forward: 24 x
-// 128 bf16, 3x3x3 U[-4, 4] 2.88 / 2.34 ms, 3x5x5 U[-3, 3] 7.32 / 4.64, U[-4, 4] 7.48 / 7.13; 16 x 64
-// bf16, 3x3x3 U[-3, 3] 1.02 / 1.05, U[-4, 4] 1.07 / 1.21; 6 x 64 fp32, 3x3x3 U[-4, 4] 0.30 / 0.37.
-// Backward, V pass + K pass: 24 x 128 bf16, 3x3x3 U[-3, 3] 4.68 / 4.50, U[-4, 4] 4.62 / 5.21, 3x5x5
-// U[-3, 3] 12.0 / 12.0, U[-4, 4] 12.0 / 13.0.
-// 16 x 64 bf16, 3x7x7 N(0, 1) by slots: 3.68 ms with 1000, 3.36 with 1500.
-constexpr int forward_box(int D, bool bf16, int rounds) {
-  return (bf16 && D == 128) || rounds > 2 ? 1500 : 1000;
+// Spread of a compact wave (compact_wave): the largest box of voxels that the points of one of its
+// queries may span.  Offsets N(0, 1) span about 440 voxels at 3x3x3, 800 at 3x5x5 and 1100 at 3x7x7
+// (the largest of four queries), U[-2, 2] 340, 570 and 850, U[-3, 3] 730, 1090 and 1500, U[-4, 4]
+// 1250, 1860 and 2480; beside the grid's faces less.
+// Where the points of most waves span about that much, ms gathering / by slots (grids 16x34x60 with
+// 24 heads x 128 bf16, 16x32x32 with 8 x 64 bf16, 2 x 9x33x47 with 6 heads of 64 or 32 fp32):
+//   forward        3x3x3 U[-3, 3]   3x3x3 U[-4, 4]   3x5x5 U[-3, 3]   3x7x7 U[-3, 3]
+//   128 bf16       2.84 / 2.00      2.84 / 2.43      7.32 / 5.03      14.2 / 11.3
+//   64 fp32        0.547 / 0.551    0.542 / 0.623    1.56 / 1.29      3.09 / 2.97
+//   64 bf16        0.236 / 0.283    0.236 / 0.280    0.620 / 0.658    1.30 / 1.50
+//   32 fp32        0.307 / 0.337    0.304 / 0.335    0.830 / 0.809    1.80 / 1.84
+//   backward (all phases)
+//   128 bf16       6.53 / 6.40      6.44 / 6.59      17.1 / 16.2      32.5 / 32.3
+//   64 fp32                                          3.93 / 4.21      7.78 / 8.92
+// and N(0, 1): forward 128 bf16 2.85 / 1.51, 7.28 / 3.26 and 14.1 / 6.67 (3x3x3, 3x5x5, 3x7x7), 64
+// bf16 0.236 / 0.231, 0.618 / 0.454 and 1.30 / 0.94; backward 128 bf16 6.57 / 5.64, 17.3 / 13.4 and
+// 32.5 / 27.2, 64 fp32 4.02 / 3.64 (3x5x5) and 8.03 / 7.46.  At U[-8, 8] every wave gathers.
+constexpr int forward_box(int D, bool bf16, int P) {
+  const bool small = D * (bf16 ? 2 : 4) == 128;  // 128-byte rows
+  if (P <= 2 * kSlotLanes) return small ? 550 : bf16 ? 1500 : 700;
+  return P <= 5 * kSlotLanes ? (small ? 1000 : bf16 ? 1600 : 1350) : small ? 1300 : 1600;
 }
-constexpr int kBackwardBox = 1000;
+constexpr int backward_box(bool bf16, int P) {
+  if (P <= 2 * kSlotLanes) return 1000;
+  return P <= 5 * kSlotLanes ? (bf16 ? 1150 : 900) : bf16 ? 1350 : 1200;
+}
 
 }  // namespace dsa3d

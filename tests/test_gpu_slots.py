@@ -169,6 +169,29 @@ def test_points_that_leave_the_box(w):
     compare(w, host)
 
 
+MIXED_CASES = [(case("mixed", T=6, H=11, W=20, heads=14, head_dim=d, kt=k[0], kh=k[1], kw=k[2],
+                     dtype=t, seed=95), f, b)
+               for t, d, k, f, b in (("bf16", 128, (3, 3, 3), 2, 2), ("bf16", 64, (3, 5, 5), 5, 0),
+                                     ("f32", 64, (3, 5, 5), 5, 5), ("f32", 32, (3, 7, 7), 5, 5),
+                                     ("bf16", 128, (3, 7, 7), 5, 5))]
+
+
+@pytest.mark.parametrize("w", [c[0] for c in MIXED_CASES],
+                         ids=lambda w: f"{w.dtype}-{w.head_dim}-{w.kt}x{w.kh}x{w.kw}")
+def test_calm_and_wide_tokens_side_by_side(w):
+    """Waves of one workgroup that go different ways: runs of calm and of wide tokens of every
+    length, and single points of calm tokens that lie far away (seen or not by the samples)."""
+    host = list(testgen.gen_inputs(w))
+    host[4] = testgen.gen_tensor(w, testgen.TID_DOUT, w.qkv_shape(), w.dout, True)
+    off = host[3]
+    rng = np.random.default_rng(w.seed)
+    token = np.cumsum(rng.random(off.shape[:4]) < 0.3, axis=3) % 2  # runs along x
+    off[...] = np.where(token[..., None, None, None] == 0, off, off * 16)
+    far = rng.random(off.shape[:6]) < 0.002
+    off[far] += 11.0
+    compare(w, host)
+
+
 def test_window_of_one_frame():
     """Frames of 2.5 GB: the buffer window holds one of the two frames, and every row of the other
     one is a global load.  The same heads on their own (a window of both frames) take the same sums

@@ -42,7 +42,7 @@ def rounds(tmp_path_factory):
 
 
 def test_the_slot_tests_reach_their_kernels(rounds):
-    for w, fwd, bwd in slots.CASES + slots.BOX_CASES + slots.FINITE_CASES:
+    for w, fwd, bwd in slots.CASES + slots.BOX_CASES + slots.FINITE_CASES + slots.MIXED_CASES:
         assert rounds(w)[:2] == (fwd, bwd), w.name
     for w, fwd in slots.PW_CASES:
         assert rounds(w)[2] == fwd, w.name
@@ -64,5 +64,8 @@ def test_workloads(rounds):
     # few rows; rows of a size that the slots are not built for; few points
     few = w["fwdbwd_64x34x60"].with_grid(name="few", T=4, H=14, W=21, heads=2)
     assert rounds(few) == (0, 0, 0)
+    tiny = w["tiny_f32"].with_grid(name="few32", T=3, H=12, W=20)
+    assert rounds(tiny) == (0, 0, 0)
+    assert rounds(tiny.with_grid(name="few32", kh=5, kw=5)) == (5, 5, 5)
     assert rounds(w["full_1080p_256f"].with_grid(name="f", dtype="f32")) == (0, 0, 0)
     assert rounds(w["full_1080p_256f"].with_grid(name="f", kt=1)) == (0, 0, 0)
