@@ -394,6 +394,7 @@ __device__ inline __attribute__((always_inline)) void segment(const ConvGeometry
 // through filter plane a into output frame s + rt - a, for every a.  The KT output frames in
 // progress are held in registers and shift down by one slot per slice; frame t is stored once
 // slice t + rt has been added.
+// fp32 skips the rows outside the grid (in bf16 their zeros are multiplied).
 // SEG: the frames are cut into segments (walking all of them from frame 0 is kept apart, as the
 // bounds cost the loop 6-10%: 1.91 -> 2.10 ms at 64x68x120x3072).
 template <bool BF16, bool OUT_BF16, bool FLIP, bool SEG, int KT, int KH, int KW>
@@ -406,6 +407,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
   __shared__ Pair slices[2][RG::POS * 64];
   constexpr int OS = OUT_BF16 ? 2 : 4;
   constexpr int rt = (KT - 1) / 2;
+  constexpr bool kSkipRows = !BF16 && KH > 1;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int frame_bytes = g.H * g.W * g.C * (BF16 ? 2 : 4);  // below 2^31 on this path
   for (int brick = xcd_tile(blockIdx.x, gridDim.x); brick < bricks; brick += gridDim.x) {
@@ -487,6 +489,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
       const Pair* cur = slices[s & 1];
 #pragma unroll
       for (int e = 0; e < KH; ++e) {
+        if (kSkipRows && (unsigned)(i + e - (KH - 1) / 2) >= (unsigned)g.H) continue;
         const Pair* src = cur + (wave + e) * RG::RX * 64 + lane;
         float2 xv[RG::RX];
 #pragma unroll
@@ -546,7 +549,12 @@ __device__ inline __attribute__((always_inline)) void write_sums(float* __restri
 // segment's frames.  bf16: one unit per block, and wave w of unit u writes slot 4 u + w.  fp32: the
 // workspace has the general kernel's few slots, so block p of a chunk's `blocks` takes units p,
 // p + blocks, ..., adds its four waves' sums in LDS and writes slot p.
-template <bool BF16, int KT, int KH, int KW>
+// A tap whose dy lies outside the grid (fp32) or in another segment (both) is skipped: the zero that
+// stands for it would make an infinite x NaN.  In bf16 without segments the zeros before and after
+// the grid and around it are multiplied (skipping the frames 5.74 -> 5.86 ms for a step at
+// 64x68x120x3072, 3x3x3, and the rows too 6.03; fp32 at 16x34x60x1024 257 -> 252 us).
+// SEG: frames are skipped.
+template <bool BF16, bool SEG, int KT, int KH, int KW>
 __global__ __launch_bounds__(kBlockThreads) void dwconv_stream_wgrad_kernel(
     ConvGeometry g, const void* __restrict__ x, const void* __restrict__ dy,
     float* __restrict__ part, float* __restrict__ part_b, int blocks) {
@@ -556,6 +564,7 @@ __global__ __launch_bounds__(kBlockThreads) void dwconv_stream_wgrad_kernel(
   __shared__ Pair slices[2][RG::POS * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   constexpr int rt = (KT - 1) / 2;
+  constexpr bool kSkipRows = !BF16, kSkipFrames = SEG && KT > 1;
   const int frame_bytes = g.H * g.W * g.C * (BF16 ? 2 : 4);  // below 2^31 on this path
   const int blk = xcd_tile(blockIdx.x, gridDim.x);
   const int cc = blk / blocks, p = blk - cc * blocks;
@@ -629,12 +638,14 @@ __global__ __launch_bounds__(kBlockThreads) void dwconv_stream_wgrad_kernel(
       const Pair* cur = slices[s & 1];
 #pragma unroll
       for (int e = 0; e < KH; ++e) {
+        if (kSkipRows && (i >= g.H || (unsigned)(i + e - (KH - 1) / 2) >= (unsigned)g.H)) continue;
         const Pair* src = cur + (wave + e) * RG::RX * 64 + lane;
         float2 xv[RG::RX];
 #pragma unroll
         for (int q = 0; q < RG::RX; ++q) xv[q] = widen(src[q * 64]);
 #pragma unroll
         for (int a = 0; a < KT; ++a) {
+          if (kSkipFrames && (s + rt - a < t0 || s + rt - a >= t1)) continue;
 #pragma unroll
           for (int f = 0; f < KW; ++f)
 #pragma unroll
@@ -792,8 +803,12 @@ hipError_t launch_stream_wgrad(const ConvGeometry& g, const void* x, const void*
                                float* part_b, hipStream_t s) {
   const int blocks = stream_wgrad_blocks(g);
   void* a[] = {(void*)&g, (void*)&x, (void*)&dy, (void*)&part, (void*)&part_b, (void*)&blocks};
-  return hipLaunchKernel(reinterpret_cast<const void*>(&dwconv_stream_wgrad_kernel<BF16, KT, KH, KW>),
-                         dim3(g.chunks * blocks), dim3(kBlockThreads), a, 0, s);
+  const void* kern =
+      reinterpret_cast<const void*>(&dwconv_stream_wgrad_kernel<BF16, !BF16, KT, KH, KW>);
+  if constexpr (BF16)
+    if (g.segs > 1)
+      kern = reinterpret_cast<const void*>(&dwconv_stream_wgrad_kernel<BF16, true, KT, KH, KW>);
+  return hipLaunchKernel(kern, dim3(g.chunks * blocks), dim3(kBlockThreads), a, 0, s);
 }
 
 // The filter shapes the streaming path covers: every extent 1 or 3.
