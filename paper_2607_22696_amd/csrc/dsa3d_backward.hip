@@ -927,7 +927,10 @@ __device__ inline __attribute__((always_inline)) void bwd_slots_tile(
                         g.scale * sum[x + 3]);
     }
     if (R > 2 || again) {
-      // a lane reads the records it wrote, four points at a time for their loads' sake
+      // four points at a time for their loads' sake.  A row of several chunks reads records that
+      // other lanes of the wave wrote (a chunk starts at any point): the fence keeps the loads
+      // behind the stores, and a wave's vector memory accesses to an address stay in order.
+      wave_sync();
       for (int p0 = lp; p0 < g.P; p0 += 4 * L) {
         SlotPoint pt[4];
         float4 rk[4], rv[4];
