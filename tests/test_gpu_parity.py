@@ -16,7 +16,8 @@ import pytest
 
 import oracle
 import testgen
-from tests.util import io_as_f32, max_abs, rel_err, reach_frames, say, shape9, to_device, to_host
+from tests.util import (io_as_f32, max_abs, reach_frames, rel_err, reorder_bound, say, shape9,
+                        to_device, to_host)
 
 torch = pytest.importorskip("torch")
 
@@ -228,7 +229,7 @@ def test_backward_repeatability():
         assert np.array_equal(r[0], runs[0][0])  # dq is query-owned: bitwise
         assert np.array_equal(r[3], runs[0][3])  # d_offsets too
         for a in (1, 2):
-            assert rel_err(r[a], runs[0][a]) < 1e-4
+            assert max_abs(r[a], runs[0][a]) <= reorder_bound(w.P, runs[0][a])
 
 
 def test_backward_timed_matches_untimed_and_marks_every_phase():
@@ -249,7 +250,7 @@ def test_backward_timed_matches_untimed_and_marks_every_phase():
     timed = [to_host(t) for t in timed]
     assert np.array_equal(timed[0], plain[0]) and np.array_equal(timed[3], plain[3])
     for a in (1, 2):
-        assert rel_err(timed[a], plain[a]) < 1e-4
+        assert max_abs(timed[a], plain[a]) <= reorder_bound(w.P, plain[a])
     ms = [evs[i].elapsed_time(evs[i + 1]) for i in range(dsa.DSA3D_BACKWARD_PHASES)]
     say(f"  phase ms {ms}")
     assert all(t > 0.0 for t in ms)

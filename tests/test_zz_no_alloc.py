@@ -4,15 +4,16 @@ scratch array) against dsa3d_backward with a caller workspace, through the C ABI
 Two calls in a row, the second on a smaller problem, so that the second one runs on the
 scratch contents the first left behind.  dq and d_offsets are query-owned and must match
 bit for bit; dK and dV sum each trilinear bin in the order its points claimed their slots,
-which may differ between calls, so they are held to 1e-4 of the relative metric; all four
-are also checked against the oracle at the bf16 bar (2e-2).
+which may differ between calls, so they are held to the rounding of two fp32 sums in different
+orders (tests.util.reorder_bound); all four are also checked against the oracle at the bf16 bar
+(2e-2).
 """
 import numpy as np
 import pytest
 
 import oracle
 import testgen
-from tests.util import rel_err, say, shape9, to_device, to_host
+from tests.util import max_abs, rel_err, reorder_bound, say, shape9, to_device, to_host
 
 torch = pytest.importorskip("torch")
 
@@ -60,9 +61,9 @@ def test_noalloc_backward_matches_the_workspace_backward_on_two_calls():
         assert np.array_equal(got[0], ref[0]), "dq"
         assert np.array_equal(got[3], ref[3]), "d_offsets"
         for i, name in ((1, "dk"), (2, "dv")):
-            e = rel_err(got[i], ref[i])
-            say(f"  {name} vs workspace backward: rel {e:.2e}")
-            assert e <= 1e-4, name
+            e, bound = max_abs(got[i], ref[i]), reorder_bound(w.P, ref[i])
+            say(f"  {name} vs workspace backward: max-abs {e:.2e}, bound {bound:.2e}")
+            assert e <= bound, name
         rq, rk, rv, roff = oracle.backward(shape9(w), w.dtype, q, k, v, off, dout)
         for g, r, name in zip(got, (rq, rk, rv, roff), ("dq", "dk", "dv", "d_offsets")):
             e = rel_err(g, r)
