@@ -41,7 +41,8 @@ CSRC = os.path.join(ROOT, "paper_2607_22696_amd", "csrc")
 
 # Device sources of each kernel family: counter figures taken from other sources are stale.
 FAMILY_SOURCES = {
-    "dsa": ["dsa3d_device.h", "tile_order.h", "dsa3d_forward.hip", "dsa3d_backward.hip"],
+    "dsa": ["dsa3d_device.h", "dsa3d_slots.h", "slot_rules.h", "tile_order.h",
+            "dsa3d_forward.hip", "dsa3d_backward.hip"],
     "dwconv": ["dsa3d_device.h", "dwconv3d.hip"],
     "win": ["winattn.hip"],
 }

@@ -1704,7 +1704,7 @@ hipError_t bwd_dispatch(const Geometry& g, const void* q, const void* k, const v
   if ((e = mark(0)) != hipSuccess) return e;
   if (split) {
     const void* vkern = reinterpret_cast<const void*>(&bwd_vpass_kernel<D, BF16, false>);
-    if constexpr (slot_rows_ok(D, BF16))
+    if constexpr (backward_slots_ok(D, BF16))
       if (rounds > 0) vkern = reinterpret_cast<const void*>(&bwd_vpass_kernel<D, BF16, true>);
     e = launch_tiles(po.vtiles, [&](int64_t vt0, int blocks) {
       void* a[] = {(void*)&g,        (void*)&v,       (void*)&off, (void*)&dout, (void*)&w.recv,
@@ -1746,7 +1746,7 @@ hipError_t bwd_dispatch(const Geometry& g, const void* q, const void* k, const v
   reinterpret_cast<const void*>(&bwd_kpass_kernel<D, BF16, HOLD, R, WHOLE>)
     const bool whole = g.win_frames == g.T;
     const void* kern = hold ? DSA3D_KPASS(kHoldChunks, 0, false) : DSA3D_KPASS(0, 0, false);
-    if constexpr (slot_rows_ok(D, BF16) && !(BF16 && D == 64)) {
+    if constexpr (backward_slots_ok(D, BF16)) {
       if constexpr (BF16)  // up to 32 points are always held
         if (rounds == 2)
           kern = whole ? DSA3D_KPASS(kHoldChunks, 2, true) : DSA3D_KPASS(kHoldChunks, 2, false);

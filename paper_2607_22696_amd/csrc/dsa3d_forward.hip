@@ -318,17 +318,23 @@ hipError_t fwd_dispatch(const Geometry& g, const void* q, const void* k, const v
                         const float* logits, const float* off, void* out, float* lse,
                         hipStream_t s) {
   const bool pw = logits != nullptr;
-#define DSA3D_FWD(R, WHOLE)                                                    \
-  (pw ? reinterpret_cast<const void*>(&fwd_kernel<D, BF16, true, R, WHOLE>)   \
-      : reinterpret_cast<const void*>(&fwd_kernel<D, BF16, false, R, WHOLE>))
+#define DSA3D_FWD(PW, R, WHOLE) \
+  reinterpret_cast<const void*>(&fwd_kernel<D, BF16, PW, R, WHOLE>)
+#define DSA3D_FWD_OF(R, WHOLE) (pw ? DSA3D_FWD(true, R, WHOLE) : DSA3D_FWD(false, R, WHOLE))
   const int rounds = forward_rounds(D, BF16, (int64_t)g.B * g.N * g.heads, g.P, pw);
   const PencilOrder po = query_order<D, BF16>(g, rounds > 0, true);
   const bool whole = g.win_frames == g.T;
-  const void* kern = DSA3D_FWD(0, false);
+  const void* kern = DSA3D_FWD_OF(0, false);
   if constexpr (slot_rows_ok(D, BF16)) {
-    if (rounds == 2) kern = whole ? DSA3D_FWD(2, true) : DSA3D_FWD(2, false);
-    if (rounds == 5) kern = whole ? DSA3D_FWD(5, true) : DSA3D_FWD(5, false);
+    if (rounds == 2) {
+      if constexpr (pw_two_rounds_ok(D, BF16))
+        kern = whole ? DSA3D_FWD_OF(2, true) : DSA3D_FWD_OF(2, false);
+      else
+        kern = whole ? DSA3D_FWD(false, 2, true) : DSA3D_FWD(false, 2, false);
+    }
+    if (rounds == 5) kern = whole ? DSA3D_FWD_OF(5, true) : DSA3D_FWD_OF(5, false);
   }
+#undef DSA3D_FWD_OF
 #undef DSA3D_FWD
   return launch_tiles(po.vtiles, [&](int64_t vt0, int blocks) {
     void* args[] = {(void*)&g,   (void*)&q,   (void*)&k,   (void*)&v,  (void*)&logits,

@@ -37,10 +37,13 @@ constexpr bool few_rows(int D, bool bf16, int64_t rows, int P) {
 }
 
 // The predicted-weights variant reads V only, half of what sharing saves: 64 bf16 channels, 64x34x60,
-// 16 heads, 3x3x3: 2.40 ms gathering, 2.45 by slots.
+// 16 heads, 3x3x3: 2.40 ms gathering, 2.45 by slots.  (The kernels that a rule never selects are not
+// built.)
+constexpr bool pw_two_rounds_ok(int D, bool bf16) { return slot_rows_ok(D, bf16) && !(bf16 && D == 64); }
+
 constexpr int forward_rounds(int D, bool bf16, int64_t rows, int P, bool pw) {
   if (!slot_rows_ok(D, bf16) || P < kSlotLanes || few_rows(D, bf16, rows, P)) return 0;
-  if (pw && bf16 && D == 64 && P <= 2 * kSlotLanes) return 0;
+  if (pw && P <= 2 * kSlotLanes && !pw_two_rounds_ok(D, bf16)) return 0;
   return P <= 2 * kSlotLanes ? 2 : 5;
 }
 
@@ -50,8 +53,10 @@ constexpr int forward_rounds(int D, bool bf16, int64_t rows, int P, bool pw) {
 // 22.9 / 18.0; 64 bf16 channels, 16 heads: 3x5x5 5.14 / 5.10, 3x7x7 10.2 / 11.1; 64 fp32
 // channels, 9x33x47, 6 heads: 3x3x3 0.84 / 0.84 (two batch items), 3x5x5 1.14 / 0.93, 3x7x7 2.28 /
 // 2.03.
+constexpr bool backward_slots_ok(int D, bool bf16) { return slot_rows_ok(D, bf16) && !(bf16 && D == 64); }
+
 constexpr int backward_rounds(int D, bool bf16, int64_t rows, int P) {
-  if (!slot_rows_ok(D, bf16) || (bf16 && D == 64) || few_rows(D, bf16, rows, P)) return 0;
+  if (!backward_slots_ok(D, bf16) || few_rows(D, bf16, rows, P)) return 0;
   if (P <= 2 * kSlotLanes) return bf16 && P >= kSlotLanes ? 2 : 0;
   return 5;
 }

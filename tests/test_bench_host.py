@@ -167,6 +167,17 @@ def test_pmc_summary_counts_read_requests_by_size(tmp_path, monkeypatch):
     assert doc["copy_check"] == {"mib": 1, "read_bytes_per_byte": 1.0, "write_bytes_per_byte": 1.0}
 
 
+def test_the_source_hashes_cover_every_header_of_their_kernels():
+    """Counters taken before a change of any included device header are stale."""
+    import re
+    for family, names in bench.FAMILY_SOURCES.items():
+        for name in names:
+            with open(os.path.join(bench.CSRC, name), encoding="utf-8") as f:
+                included = re.findall(r'#include "([^"]+)"', f.read())
+            # the interface header holds no kernel code
+            assert set(included) - {"dsa3d_internal.h"} <= set(names), (family, name)
+
+
 def test_kernel_source_hash_ignores_comments_but_not_code(tmp_path, monkeypatch):
     import shutil
     for name in bench.FAMILY_SOURCES["win"]:
