@@ -306,6 +306,22 @@ def vmem_bytes(w):
     return {k: w.queries * b for k, b in per.items()}
 
 
+def loads_every_corner(w, kernel):
+    """Whether the waves of a kernel load the 8 corner rows of every point on workload w, as
+    vmem_bytes counts: false where the dispatch (csrc/slot_rules.h) and the workload's offset law
+    (all but wide uniform offsets) make them take distinct voxels instead."""
+    import testgen
+    row_bytes = w.head_dim * (2 if w.dtype == "bf16" else 4)
+    slots = row_bytes in (128, 256) and w.P >= 16
+    if kernel != "fwd_kernel":
+        slots = slots and not (w.dtype == "bf16" and w.head_dim == 64)
+        slots = slots and (w.P > 32 or w.dtype == "bf16")
+    few = w.head_dim > 32 and w.queries < 16384 and not (row_bytes == 256 and w.dtype == "bf16"
+                                                          and w.P > 32)
+    wide = w.offsets.kind == testgen.UNIFORM and max(-w.offsets.a, w.offsets.b) > 4
+    return not slots or few or wide
+
+
 PROBE_SRC = os.path.join(ROOT, "gather_probe.hip")
 PROBE_LIB = os.path.join(ROOT, "libgather_probe.so")
 
@@ -950,12 +966,12 @@ def main():
     roof["kernel"] = kname
     roof["avg_launch_ms"] = round(kernel_ms[kname], 4)
 
-    # the bound the kernels actually meet: bytes through the per-unit vector-memory path
+    # the bound the gathering kernels meet: bytes through the per-unit vector-memory path
     ceil = gather_ceiling(w.head_dim * (2 if w.dtype == "bf16" else 4))
     vm = vmem_bytes(w)
     gather_path = {"ceiling": ceil}
     for n, b in vm.items():
-        if n in kernel_ms:
+        if n in kernel_ms and loads_every_corner(w, n):
             tbps = b / (kernel_ms[n] * 1e-3) / 1e12
             gather_path[n] = {"bytes_per_launch": b, "achieved_TBps": round(tbps, 2),
                               "frac_of_l1_ceiling": round(tbps / ceil["l1_TBps"], 3),

@@ -69,3 +69,13 @@ def test_workloads(rounds):
     assert rounds(tiny.with_grid(name="few32", kh=5, kw=5)) == (5, 5, 5)
     assert rounds(w["full_1080p_256f"].with_grid(name="f", dtype="f32")) == (0, 0, 0)
     assert rounds(w["full_1080p_256f"].with_grid(name="f", kt=1)) == (0, 0, 0)
+
+
+def test_the_bench_counts_corner_loads_only_where_a_kernel_gathers(rounds):
+    import bench
+    for w in testgen.WORKLOADS.values():
+        wide = w.offsets.kind == testgen.UNIFORM and w.offsets.b > 4
+        fwd, bwd, _ = rounds(w)
+        assert bench.loads_every_corner(w, "fwd_kernel") == (wide or fwd == 0), w.name
+        for k in ("bwd_vpass_kernel", "bwd_kpass_kernel"):
+            assert bench.loads_every_corner(w, k) == (wide or bwd == 0), w.name
