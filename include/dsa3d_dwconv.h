@@ -62,8 +62,11 @@ dsa3d_status dsa3d_dwconv3d_forward(const dsa3d_dwconv_desc* desc, const void* x
 
 /* Bytes of device workspace dsa3d_dwconv3d_backward needs for the weight and bias gradients
  * (partial sums of the grid sweep: 4 bytes per channel and tap, and per channel, for each wave
- * slot: in bf16 with every filter extent 1 or 3 four slots per 4 x 8-token column of the grid;
- * else about 3072 / (ceil(C/128) kt) slots); 0 for a descriptor the backward would reject. */
+ * slot.  In bf16 with every filter extent 1 or 3 and frames below 2 GB: four slots per batch
+ * item, 4 x 8-token column of the grid and segment of its frames; there is one segment unless
+ * batch x columns x ceil(C/128) is below 1024, then as many as bring the product to about 1024,
+ * of at least four frames each.  Else about 3072 / (ceil(C/128) kt) slots, a few MB); 0 for a
+ * descriptor the backward would reject. */
 size_t dsa3d_dwconv3d_backward_workspace_size(const dsa3d_dwconv_desc* desc);
 
 /* Backward of dsa3d_dwconv3d_forward for upstream gradient dy:

@@ -31,8 +31,8 @@
 // Where rows are large enough (backward_rounds), a wave whose points lie close together leaves the
 // V corners to phase 3: phase 1 only counts its points, and phase 3 reads each distinct voxel of
 // four neighbouring queries once per sweep (bwd_slots_tile, dsa3d_slots.h): dots of the V rows with
-// dout, of the K rows with q, and the sum of K rows for dq with Delta known.  V and K pass at
-// 16x34x60, 24 heads x 128, 3x7x7, offsets N(0, 1): 23.0 -> 17.5 ms.
+// dout, of the K rows with q, and the sum of K rows for dq with Delta known.  The backward at
+// 16x34x60, 24 heads x 128, 3x7x7, offsets N(0, 1): 32.5 -> 27.2 ms.
 // The predicted-weights variant reads no K: one sweep (phase 1 with the given logits) and a finalize
 // of one thread per point take phases 1 and 3.
 #include "dsa3d_slots.h"
@@ -1204,7 +1204,8 @@ __device__ inline __attribute__((always_inline)) void gather_run(
 // PW (the predicted-weights variant): dV only (there is no K).
 // WAVE: all groups of a wave share one block, batch by batch, and add their sums at the end: for
 // grids whose blocks would leave the chip idle, where the chain of a block's batches is the time
-// (4x8x8 tokens, 2 heads x 32, 3x3x3: 65 -> 15 us).
+// (a step, 3x3x3: 4x8x8 tokens, 2 heads x 32 123 -> 77 us, 9x33x47, 1 head x 32 384 -> 255 and x 64
+// 455 -> 413).
 template <int D, bool BF16, bool PW, bool WAVE>
 __global__ __launch_bounds__(kBlockThreads) DSA3D_WAVES_HINT(D) void bwd_gather_kernel(
     Geometry g, const void* __restrict__ q, const void* __restrict__ dout,
@@ -1795,7 +1796,9 @@ hipError_t bwd_dispatch(const Geometry& g, const void* q, const void* k, const v
   } else {
     using LY = Layout<D, BF16>;
     // cells: 2 x 2 voxel blocks of a frame; pencils of about 32 x 32 voxels.  Fewer than four waves
-    // per compute unit: a wave per block.
+    // per compute unit: a wave per block.  Up to there it is never slower but by 4% at 9 points
+    // (16x32x32, 1 head x 32: 190 -> 198 us); above it gains up to a third at many points (16x34x60, 6
+    // x 32, 3x7x7: 7.95 -> 7.32 ms) and loses up to 6% at 9 (0.544 -> 0.578).
     const int64_t vblocks = (int64_t)g.B * g.heads * g.T * ((g.H + 1) / 2) * ((g.W + 1) / 2);
     const bool wave = vblocks < 1024 * LY::kGroups;
     const PencilOrder go = plan_pencils(g.B * g.heads, g.T, (g.H + 1) / 2, (g.W + 1) / 2,

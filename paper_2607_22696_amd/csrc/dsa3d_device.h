@@ -332,10 +332,10 @@ constexpr int slot_words() {
 
 // ---------------------------------------------------------------------------- launch shape
 
-constexpr int kMaxBlocks = 1 << 22;  // grid cap; larger problems loop over tiles
+constexpr int kMaxBlocks = 1 << 22;  // workgroups of one launch; larger orders take several
 
-// Workgroups for `vtiles` virtual tiles: at most kMaxBlocks, a multiple of 8 when capped so
-// that a workgroup's later tiles (v += gridDim.x) stay on its XCD.
+// Workgroups of the next launch for `vtiles` virtual tiles that are left: at most kMaxBlocks, a
+// multiple of 8 so that the tiles of a later launch stay on their XCDs.
 inline int grid_blocks(int64_t vtiles) {
   return (int)(vtiles < kMaxBlocks ? vtiles : kMaxBlocks);
 }

@@ -8,9 +8,9 @@
 //  * gather_tile: an L-lane group owns one query row, loads the 8 K and 8 V rows of each point
 //    (16-byte buffer loads, zeros outside the grid) and folds the point into an online softmax.
 // Measured, gather against slots where the points are compact (U[-8, 8] offsets always gather):
-// 64x68x120, 24 heads x 128, 3x3x3, offsets N(0, 1): 48.2 -> 25.6 ms; 16x34x60, 24 x 128, 3x7x7:
-// 14.5 -> 6.6 ms; 64x34x60, 16 x 64, 3x3x3, U[-2, 2]: 4.27 -> 3.9 ms; 2 x 9x33x47, 6 x 64 fp32:
-// 0.67 -> 0.46 ms.  Nothing per point is written to memory; the output row and its LSE are stored
+// 64x68x120, 24 heads x 128, 3x3x3, offsets N(0, 1): 48.2 -> 24.7 ms; 16x34x60, 24 x 128, 3x7x7:
+// 14.1 -> 6.7 ms; 64x34x60, 16 x 64, 3x3x3, U[-2, 2]: 4.07 -> 3.87 ms; 2 x 9x33x47, 6 x 64 fp32:
+// 0.55 -> 0.40 ms.  Nothing per point is written to memory; the output row and its LSE are stored
 // once.
 //
 // Memory order: tiles are handed out in pencils (tile_order.h): each XCD walks one pencil of
