@@ -1,7 +1,8 @@
 """Distinct-voxel slots (csrc/dsa3d_slots.h) against the fp64 oracle, at the sizes where they can
 go wrong: the rounds of 16 points and the chunks of 32 and 80 that are numbered together, rows of
-four tokens cut by the grid's edge, boxes that overflow inside a tile judged by one token, corners
-outside the buffer window, and rows of V that hold infinities.
+four tokens cut by the grid's edge, queries whose points leave a wave's box or need more slots than
+there are, calm and wide tokens side by side, corners outside the buffer window, rows that hold
+infinities, and coefficients and values of very different size.
 
 Tolerances are those of test_gpu_parity: fp32 max-abs 1e-5, bf16 the relative metric 2e-2.
 """
@@ -82,6 +83,9 @@ CASES = [
     (case("k377_bf16_d128", T=3, H=8, W=11, heads=2, head_dim=128, kt=3, kh=7, kw=7, dtype="bf16",
           seed=85), 5, 5),
     (case("k377_f32_d32", T=3, H=8, W=11, heads=2, head_dim=32, kt=3, kh=7, kw=7, seed=86), 5, 5),
+    # four chunks that start at any point
+    (case("k579_bf16_d128", T=5, H=7, W=9, heads=2, head_dim=128, kt=5, kh=7, kw=9, dtype="bf16",
+          seed=96, offsets=N05), 5, 5),
     # an ordinary training step's kernel
     (case("k333_bf16_d128", T=8, H=12, W=24, heads=8, head_dim=128, dtype="bf16", seed=87), 2, 2),
     (case("k355_f32_d64", T=6, H=12, W=24, heads=10, head_dim=64, kt=3, kh=5, kw=5, seed=88), 5, 5),
