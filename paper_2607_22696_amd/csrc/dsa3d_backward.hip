@@ -883,7 +883,7 @@ __device__ inline __attribute__((always_inline)) void bwd_slots_tile(
           }
         }
         bad = group_sum<L>(bad);
-        sum_coefs<R>(lds, pt, ds, npts, ns);
+        sum_coefs<R, BF16>(lds, pt, ds, npts, ns);
         if constexpr (kKeep) {
           if (single) {  // the points are done with before the sums need the registers
             uint32_t slot[R];

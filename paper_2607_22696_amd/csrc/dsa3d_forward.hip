@@ -260,7 +260,7 @@ __device__ inline __attribute__((always_inline)) void slots_tile(
       }
       lc = group_sum<L>(lc);
       l = fmaf(l, corr, lc);
-      sum_coefs<R>(lds, pt, s, npts, n);
+      sum_coefs<R, BF16>(lds, pt, s, npts, n);
       float sum[U::kVec];
       row_sums<D, BF16>(slot_rows<LY::kRowBytes>(g, v, win, b, m, global), lds, n, sum);
 #pragma unroll

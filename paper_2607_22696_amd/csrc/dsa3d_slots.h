@@ -569,10 +569,11 @@ struct SlotSum {
 };
 
 // val[query][s] = the sum over the query's corners on slot s of c[r] * (the corner's weight), for
-// rounds of npts points per query; 0 for a slot that the query does not touch, a denormal number
-// (below 2^-141) where it does and the sum is zero.  Needs finite c; the exponents take the place
-// of the list, which waits in registers.
-template <int R>
+// rounds of npts points per query; 0 for a slot that the query does not touch, a zero with other bits
+// where it does and the sum is zero: -0 for the vector ALU, for the matrix cores a denormal number
+// below 2^-141, none of whose bits are in their parts.  Needs finite c; the exponents take the
+// place of the list, which waits in registers.
+template <int R, bool BF16>
 __device__ inline __attribute__((always_inline)) void sum_coefs(SlotLds& lds,
                                                                 const SlotPoint (&pt)[R],
                                                                 const float (&c)[R], int npts,
@@ -640,7 +641,8 @@ __device__ inline __attribute__((always_inline)) void sum_coefs(SlotLds& lds,
     const int4 x = *reinterpret_cast<const int4*>(val + s);
     auto coef = [](int x, uint32_t b) {
       const float f = ldexpf((float)x, (int)b - 128 - kBits);
-      return x != 0 ? f : __uint_as_float(b);
+      const float zero = BF16 ? __uint_as_float(b) : b != 0u ? -0.0f : 0.0f;
+      return x != 0 ? f : zero;
     };
     *reinterpret_cast<float4*>(val + s) = make_float4(coef(x.x, b & 255u), coef(x.y, (b >> 8) & 255u),
                                                       coef(x.z, (b >> 16) & 255u), coef(x.w, b >> 24));

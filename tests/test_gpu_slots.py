@@ -314,6 +314,25 @@ def test_an_infinite_value_reaches_its_own_queries_only(w, value, offset):
 
 
 @pytest.mark.parametrize("w", [c[0] for c in FINITE_CASES], ids=finite_id)
+def test_a_weight_of_zero_on_the_largest_value_adds_nothing(w):
+    """Offsets of 0: the queries that have a voxel as an upper corner only, with weight 0, do not see
+    a value of 3e38 there."""
+    import paper_2607_22696_amd as dsa
+    q, k, v, off, dout = finite_inputs(w, 0.0)
+    kern = (w.kt, w.kh, w.kw)
+    out0, lse = dsa.forward(q, k, v, off, kernel=kern)
+    v[(0,) + VOXEL + (0, 5)] = 3e38
+    out = to_host(dsa.forward(q, k, v, off, kernel=kern)[0])
+    sampled = np.zeros(samplers(w).shape, bool)
+    at = [slice(max(c - r, 0), c + r + 1) for c, r in
+          zip(VOXEL, ((w.kt - 1) // 2, (w.kh - 1) // 2, (w.kw - 1) // 2))]
+    sampled[0, at[0], at[1], at[2], 0] = True
+    assert (samplers(w) & ~sampled).any()
+    assert np.array_equal(out[~sampled], to_host(out0)[~sampled])
+    assert (np.abs(out[sampled][:, 5]) > 1e30).all()
+
+
+@pytest.mark.parametrize("w", [c[0] for c in FINITE_CASES], ids=finite_id)
 def test_powers_of_two_pass_through(w):
     """Values near 1e30 and gradients near 1e-21: every sum is linear in V, K and dout, and scaling
     by a power of two changes no bit of it while nothing overflows."""
